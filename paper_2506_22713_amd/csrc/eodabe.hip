@@ -2626,15 +2626,29 @@ int eodabe_knn_cv(eodabe_ctx* ctx, const float* F, int64_t m, int d, int64_t ldf
   TRY(check_ctx(ctx));
   if (m < 1 || d < 1 || d > KNN_DMAX || ldf < d || k < 1 || k > KNN_KMAX || nclass < 1 || nclass > KNN_CMAX)
     return EODABE_EINVAL;
-  if (!F || !labels || !fold || !pred) return EODABE_EINVAL;
+  if (!F || !labels || !fold || !pred || m > 0x7fffffff - 16) return EODABE_EINVAL;
   if (!ws || ws_bytes < eodabe_knn_workspace_size(nclass)) return EODABE_EWORKSPACE;
   TRY(check_dev(ctx));
   hipStream_t st = ctx->stream;
   unsigned long long* conf = (unsigned long long*)ws;
   const int64_t nc2 = (int64_t)nclass * nclass;
   hipLaunchKernelGGL(k_zero<unsigned long long>, dim3(1), dim3(256), 0, st, conf, nc2);
-  hipLaunchKernelGGL(k_knn_cv, dim3((unsigned)cdiv(m, 256)), dim3(256), 0, st, F, m, d, ldf, labels, fold, k,
-                     nclass, pred, conf);
+#define KNN_CASE(S)                                                                                          \
+  case S:                                                                                                     \
+    hipLaunchKernelGGL(k_knn_cv<S>, dim3((unsigned)cdiv(m, KNN_NQ)), dim3(64 * KNN_WV), 0, st, F, m, d, ldf, \
+                       labels, fold, k, nclass, pred, conf);                                                  \
+    break
+  switch ((d + 3) / 4) {
+    KNN_CASE(1);
+    KNN_CASE(2);
+    KNN_CASE(3);
+    KNN_CASE(4);
+    KNN_CASE(5);
+    KNN_CASE(6);
+    KNN_CASE(7);
+    KNN_CASE(8);
+  }
+#undef KNN_CASE
   LAUNCHCHK();
   std::vector<unsigned long long> hc((size_t)nc2);
   HIPCHK(hipMemcpyAsync(hc.data(), conf, (size_t)nc2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));

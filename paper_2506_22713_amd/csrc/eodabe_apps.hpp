@@ -169,100 +169,393 @@ constexpr int KNN_DMAX = 32;
 constexpr int KNN_CMAX = 64;
 
 // KNN classification of every point by the points of the other folds
-// (ten-fold cross-validation in one pass).  One thread per query point; the
-// candidates stream through LDS 256 at a time.  Squared distances are
-// summed feature by feature in FP64 from the FP32 features with separate
-// multiply and add (no contraction), so they are the same bits as any
-// implementation of that definition; the k nearest are the smallest
-// (distance, index) pairs (candidates arrive in index order, and a new one
-// enters only when strictly closer); the vote goes to the most frequent
-// label, ties to the smaller label.  pred[i] receives the class and
-// conf[pred * nclass + label] counts it.
-__global__ __launch_bounds__(256) void k_knn_cv(const float* __restrict__ F, int64_t m, int d, int64_t ldf,
-                                                const int32_t* __restrict__ label,
-                                                const int32_t* __restrict__ fold, int k, int nclass,
-                                                int32_t* __restrict__ pred,
-                                                unsigned long long* __restrict__ conf) {
-  __shared__ float cf[256 * KNN_DMAX];
-  __shared__ int32_t cfold[256], clab[256];
-  const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
-  const bool active = i < m;
-  double xi[KNN_DMAX];
-#pragma unroll
-  for (int a = 0; a < KNN_DMAX; ++a) xi[a] = (active && a < d) ? (double)F[i * ldf + a] : 0.0;
-  const int fi = active ? fold[i] : -1;
-  double bd[KNN_KMAX];
-  int32_t bl[KNN_KMAX];
-#pragma unroll
-  for (int s = 0; s < KNN_KMAX; ++s) {
-    bd[s] = INFINITY;
-    bl[s] = -1;
-  }
-  double worst = INFINITY;                          // bd[k - 1], kept with static indices
-  for (int64_t j0 = 0; j0 < m; j0 += 256) {
-    __syncthreads();
-    {
-      const int64_t j = j0 + threadIdx.x;
-      const bool ok = j < m;
-      for (int a = 0; a < d; ++a) cf[threadIdx.x * d + a] = ok ? F[j * ldf + a] : 0.f;
-      cfold[threadIdx.x] = ok ? fold[j] : fi;       // past the end: same fold, skipped
-      clab[threadIdx.x] = ok ? label[j] : 0;
-    }
-    __syncthreads();
-    const int nc = (int)((m - j0) < 256 ? (m - j0) : 256);
-    for (int t = 0; t < nc; ++t) {
-      if (cfold[t] == fi) continue;
-      double dd = 0.0;
-      {
+// (ten-fold cross-validation in one launch).  The answer is defined in FP64:
+// squared distances summed feature by feature from the FP32 features with
+// separate multiply and add (no contraction), the k nearest the smallest
+// (distance, index) pairs, the vote to the most frequent label, ties to the
+// smaller one.  pred[i] receives the class and conf[pred * nclass + label]
+// counts it.
+//
+// Those FP64 sums for all m^2 pairs bound the direct form (one query per
+// thread: 20.5 ms at m = 21025, d = 15, on 83 workgroups).  Here FP32 MFMA
+// products find the few pairs that can matter, and only they are summed in
+// FP64: 0.61 ms there, of which the products of the two passes are 0.23 ms at
+// the FP32 MFMA rate.  A workgroup owns 32 queries; its waves stream 16-candidate tiles.
+//   pass 1: |y|^2 - 2 x.y per pair as 4 S-deep MFMA products plus one for
+//     |y|^2 (each lane's own partial norm against ones: no cross-lane sum),
+//     padded upwards by the rounding bound, its minimum over each of 128
+//     interleaved candidate classes kept per query.  The k-th smallest of
+//     those minima bounds the k-th nearest distance from above (k <= 16
+//     distinct candidates lie within it).
+//   pass 2: the same products padded downwards; pairs below the bound go to
+//     a per-wave queue and are summed in FP64 64 at a time, then kept in a
+//     list per query, from which the k smallest pairs are taken.  The lists'
+//     order varies between runs, the selection does not.
+// A query whose list overflows (more than KNN_CAP pairs within the bound:
+// duplicated points) is answered by scanning all pairs in FP64.
+//
+// Rounding bound: with x', y' the features less a common centre, each off by
+// a relative 2^-24, and K = 4 S + 4 products accumulated in FP32, the value
+// differs from the FP64 distance by less than 8 (d + 8) 2^-24 (|x'|^2 +
+// |y'|^2) (the pieces add to about half of that), plus 1e-36 for results
+// below the normal range.  Norms past 1e37, where a product may overflow,
+// make the pair pass.
+constexpr int KNN_WV = 8;       // waves of a workgroup
+constexpr int KNN_QT = 2;       // 16-query tiles of a workgroup
+constexpr int KNN_NQ = 16 * KNN_QT;
+constexpr int KNN_CAP = 96;     // pairs kept per query
+
+__device__ __forceinline__ double knn_dist(const float* __restrict__ F, int64_t ldf, int d, int64_t i, int64_t j) {
+  const float* x = F + i * ldf;
+  const float* y = F + j * ldf;
+  double dd = 0.0;
+  {
 #pragma clang fp contract(off)
-#pragma unroll
-        for (int a = 0; a < KNN_DMAX; ++a) {
-          if (a < d) {
-            const double u = (double)cf[t * d + a] - xi[a];
-            dd = dd + u * u;
-          }
-        }
-      }
-      if (!(dd < worst)) continue;
-      // insert into the sorted list of the first k entries
-      const int lt = clab[t];
-#pragma unroll
-      for (int s = KNN_KMAX - 1; s > 0; --s) {
-        if (s < k) {
-          if (dd < bd[s - 1]) {
-            bd[s] = bd[s - 1];
-            bl[s] = bl[s - 1];
-          } else if (dd < bd[s]) {
-            bd[s] = dd;
-            bl[s] = lt;
-          }
-        }
-      }
-      if (dd < bd[0]) {
-        bd[0] = dd;
-        bl[0] = lt;
-      }
-#pragma unroll
-      for (int s = 0; s < KNN_KMAX; ++s)
-        if (s == k - 1) worst = bd[s];
+    for (int a = 0; a < d; ++a) {
+      const double u = (double)y[a] - (double)x[a];
+      dd = dd + u * u;
     }
   }
-  if (!active) return;
+  return dd;
+}
+
+template <int S>
+__global__ __launch_bounds__(64 * KNN_WV) void k_knn_cv(const float* __restrict__ F, int64_t m, int d, int64_t ldf,
+                                                        const int32_t* __restrict__ label,
+                                                        const int32_t* __restrict__ fold, int k, int nclass,
+                                                        int32_t* __restrict__ pred,
+                                                        unsigned long long* __restrict__ conf) {
+  typedef Mfma<float> MF;
+  constexpr int NB = KNN_WV * 16;                     // candidate classes of pass 1
+  constexpr int64_t ROWS = 16 * KNN_WV;               // candidates per step of the workgroup
+  __shared__ union {
+    float bmin[NB][KNN_NQ + 1];
+    struct {
+      double dd[KNN_NQ][KNN_CAP];
+      int jj[KNN_NQ][KNN_CAP];
+    } list;
+  } sh;
+  __shared__ int quej[KNN_WV][128];
+  __shared__ unsigned char queq[KNN_WV][128];
+  __shared__ float thr[KNN_NQ];
+  __shared__ int cnt[KNN_NQ], sel[KNN_NQ][KNN_KMAX];
+  __shared__ double wd[KNN_WV];
+  __shared__ int wj[KNN_WV];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, g = lane >> 4;
+  const int64_t q0 = blockIdx.x * (int64_t)KNN_NQ;
+  const int64_t ntile = (m + 15) / 16;
+  const float pad = 8.f * (float)(d + 8) * 5.9604645e-8f;
+
+  // this lane's features are g S .. g S + S - 1 (zero past d), less the mean
+  // of 16 rows spread over the points
+  int off[S];
+  bool in[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    in[s] = s < S - 3 || g * S + s < d;
+    off[s] = in[s] ? g * S + s : d - 1;
+  }
+  float c[S];
+  {
+    const float* p = F + (m * li / 16) * ldf;
+#pragma unroll
+    for (int s = 0; s < S; ++s) c[s] = p[off[s]];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      for (int o = 1; o < 16; o <<= 1) c[s] += __shfl_xor(c[s], o);
+      c[s] = fabsf(c[s]) < 1e18f ? c[s] * 0.0625f : 0.f;
+    }
+  }
+  // query operands -2 x', norms and folds
+  float b[KNN_QT][S], nx[KNN_QT];
+  int qf[KNN_QT];
+#pragma unroll
+  for (int t = 0; t < KNN_QT; ++t) {
+    const int64_t i = q0 + 16 * t + li < m ? q0 + 16 * t + li : m - 1;
+    float n2 = 0.f;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const float x = in[s] ? F[i * ldf + off[s]] - c[s] : 0.f;
+      n2 = fmaf(x, x, n2);
+      b[t][s] = -2.f * x;
+    }
+    n2 += __shfl_xor(n2, 16);
+    n2 += __shfl_xor(n2, 32);
+    nx[t] = n2;
+    qf[t] = fold[i];
+  }
+  if (tid < KNN_NQ) cnt[tid] = 0;
+
+  auto fetch = [&](int64_t tile, float(&x)[S]) {
+    const int64_t j = tile * 16 + li < m ? tile * 16 + li : m - 1;
+#pragma unroll
+    for (int s = 0; s < S; ++s) x[s] = F[j * ldf + off[s]];
+  };
+  // centred candidate operand in place; its padded partial norm.  A norm out
+  // of range becomes `big`; a row past m counts as infinitely far
+  auto centre = [&](int64_t tile, float(&x)[S], float scale, float big) {
+    float p = 0.f;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      x[s] = in[s] ? x[s] - c[s] : 0.f;
+      p = fmaf(x[s], x[s], p);
+    }
+    p = p > 1e37f ? big : p * scale;
+    return tile * 16 + li < m ? p : INFINITY;
+  };
+  auto product = [&](const float(&x)[S], float p, int t) {
+    typename MF::acc_t acc = MF::zero();
+#pragma unroll
+    for (int s = 0; s < S; ++s) acc = MF::op(x[s], b[t][s], acc);
+    return MF::op(p, 1.f, acc);
+  };
+
+  // ---- pass 1
+  {
+    float mn[KNN_QT][4];
+#pragma unroll
+    for (int t = 0; t < KNN_QT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mn[t][e] = INFINITY;
+    float x[S], xn[S];
+    if (wv < ntile) fetch(wv, x);
+    for (int64_t tile = wv; tile < ntile; tile += KNN_WV) {
+      fetch(tile + KNN_WV < ntile ? tile + KNN_WV : tile, xn);
+      int cf[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t j = tile * 16 + MF::row(g, e);
+        cf[e] = fold[j < m ? j : m - 1];
+      }
+      const float p = centre(tile, x, 1.f + pad, INFINITY);
+#pragma unroll
+      for (int t = 0; t < KNN_QT; ++t) {
+        const typename MF::acc_t v = product(x, p, t);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mn[t][e] = (v[e] < mn[t][e] && cf[e] != qf[t]) ? v[e] : mn[t][e];
+      }
+#pragma unroll
+      for (int s = 0; s < S; ++s) x[s] = xn[s];
+    }
+#pragma unroll
+    for (int t = 0; t < KNN_QT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sh.bmin[wv * 16 + g * 4 + e][16 * t + li] = mn[t][e] + nx[t] * (1.f + pad);
+  }
+  __syncthreads();
+  // the k-th smallest class minimum of each query (16 threads a query)
+  {
+    const int q = tid >> 4, sub = tid & 15;
+    float v[NB / 16];
+#pragma unroll
+    for (int e = 0; e < NB / 16; ++e) v[e] = sh.bmin[sub * (NB / 16) + e][q];
+    float last = INFINITY;
+    for (int s = 0; s < k; ++s) {
+      float best = v[0];
+      int at = 0;
+#pragma unroll
+      for (int e = 1; e < NB / 16; ++e)
+        if (v[e] < best) {
+          best = v[e];
+          at = e;
+        }
+      float gb = best;
+      int who = sub;
+      for (int o = 1; o < 16; o <<= 1) {
+        const float ob = __shfl_xor(gb, o);
+        const int ow = __shfl_xor(who, o);
+        if (ob < gb || (ob == gb && ow < who)) {
+          gb = ob;
+          who = ow;
+        }
+      }
+      last = gb;
+#pragma unroll
+      for (int e = 0; e < NB / 16; ++e)
+        if (who == sub && e == at) v[e] = INFINITY;
+    }
+    if (sub == 0) thr[q] = last;
+  }
+  __syncthreads();
+
+  // ---- pass 2
+  {
+    float tq[KNN_QT];
+#pragma unroll
+    for (int t = 0; t < KNN_QT; ++t) {
+      tq[t] = thr[16 * t + li] - nx[t] * (1.f - pad) + 1e-36f;
+      if (!(nx[t] < 1e37f)) tq[t] = INFINITY;
+      if (q0 + 16 * t + li >= m) tq[t] = -INFINITY;
+    }
+    int qn = 0;                                       // queued pairs of this wave
+    auto flush = [&](int n) {
+      if (lane < n) {
+        const int j = quej[wv][lane], q = queq[wv][lane];
+        const double dd = knn_dist(F, ldf, d, q0 + q, j);
+        if (dd < INFINITY) {
+          const int at = atomicAdd(&cnt[q], 1);
+          if (at < KNN_CAP) {
+            sh.list.dd[q][at] = dd;
+            sh.list.jj[q][at] = j;
+          }
+        }
+      }
+      const int left = qn - n;
+      int j = 0, q = 0;
+      if (lane < left) {
+        j = quej[wv][n + lane];
+        q = queq[wv][n + lane];
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (lane < left) {
+        quej[wv][lane] = j;
+        queq[wv][lane] = (unsigned char)q;
+      }
+      __builtin_amdgcn_wave_barrier();
+      qn = left;
+    };
+    float x[S], xn[S];
+    if (wv < ntile) fetch(wv, x);
+    for (int64_t tile = wv; tile < ntile; tile += KNN_WV) {
+      fetch(tile + KNN_WV < ntile ? tile + KNN_WV : tile, xn);
+      const float p = centre(tile, x, 1.f - pad, -INFINITY);
+      typename MF::acc_t v[KNN_QT];
+      bool any = false;
+#pragma unroll
+      for (int t = 0; t < KNN_QT; ++t) {
+        v[t] = product(x, p, t);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) any |= !(v[t][e] >= tq[t]);
+      }
+      if (__any(any)) {
+#pragma unroll
+        for (int t = 0; t < KNN_QT; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            bool h = !(v[t][e] >= tq[t]);
+            if (!__any(h)) continue;
+            const int64_t j = tile * 16 + MF::row(g, e);
+            h = h && j < m && q0 + 16 * t + li < m;
+            h = h && fold[j] != qf[t];
+            const unsigned long long mk = __ballot(h);
+            if (h) {
+              const int at = qn + __popcll(mk & ((1ull << lane) - 1));
+              quej[wv][at] = (int)j;
+              queq[wv][at] = (unsigned char)(16 * t + li);
+            }
+            __builtin_amdgcn_wave_barrier();
+            qn += __popcll(mk);
+            if (qn >= 64) flush(64);
+          }
+      }
+#pragma unroll
+      for (int s = 0; s < S; ++s) x[s] = xn[s];
+    }
+    flush(qn);
+  }
+  __syncthreads();
+
+  // ---- the k smallest (distance, index) pairs of each query's list
+  {
+    const int q = tid >> 4, sub = tid & 15;
+    const int n = cnt[q] < KNN_CAP ? cnt[q] : KNN_CAP;
+    double dv[KNN_CAP / 16];
+    int jv[KNN_CAP / 16];
+#pragma unroll
+    for (int e = 0; e < KNN_CAP / 16; ++e) {
+      const bool ok = sub + 16 * e < n;
+      dv[e] = ok ? sh.list.dd[q][sub + 16 * e] : INFINITY;
+      jv[e] = ok ? sh.list.jj[q][sub + 16 * e] : 0x7fffffff;
+    }
+    for (int s = 0; s < k; ++s) {
+      double bd = dv[0];
+      int bj = jv[0];
+#pragma unroll
+      for (int e = 1; e < KNN_CAP / 16; ++e)
+        if (dv[e] < bd || (dv[e] == bd && jv[e] < bj)) {
+          bd = dv[e];
+          bj = jv[e];
+        }
+      for (int o = 1; o < 16; o <<= 1) {
+        const double od = __shfl_xor(bd, o);
+        const int oj = __shfl_xor(bj, o);
+        if (od < bd || (od == bd && oj < bj)) {
+          bd = od;
+          bj = oj;
+        }
+      }
+      if (sub == 0) sel[q][s] = bj;
+#pragma unroll
+      for (int e = 0; e < KNN_CAP / 16; ++e)
+        if (jv[e] == bj) {
+          dv[e] = INFINITY;
+          jv[e] = 0x7fffffff;
+        }
+    }
+  }
+  __syncthreads();
+  // overflowed lists: the successive minima over all pairs
+  for (int q = 0; q < KNN_NQ; ++q) {
+    if (cnt[q] <= KNN_CAP) continue;
+    const int64_t i = q0 + q;
+    const int fi = fold[i];
+    double ld = -1.0;
+    int lj = -1;
+    for (int s = 0; s < k; ++s) {
+      double bd = INFINITY;
+      int bj = 0x7fffffff;
+      for (int64_t j = tid; j < m; j += 64 * KNN_WV) {
+        if (fold[j] == fi) continue;
+        const double dd = knn_dist(F, ldf, d, i, j);
+        if ((dd > ld || (dd == ld && j > lj)) && dd < bd) {
+          bd = dd;
+          bj = (int)j;
+        }
+      }
+      for (int o = 1; o < 64; o <<= 1) {
+        const double od = __shfl_xor(bd, o);
+        const int oj = __shfl_xor(bj, o);
+        if (od < bd || (od == bd && oj < bj)) {
+          bd = od;
+          bj = oj;
+        }
+      }
+      __syncthreads();
+      if (lane == 0) {
+        wd[wv] = bd;
+        wj[wv] = bj;
+      }
+      __syncthreads();
+      for (int w = 0; w < KNN_WV; ++w)
+        if (wd[w] < bd || (wd[w] == bd && wj[w] < bj)) {
+          bd = wd[w];
+          bj = wj[w];
+        }
+      if (tid == 0) sel[q][s] = bj;
+      ld = bd;
+      lj = bj;
+    }
+  }
+  __syncthreads();
+  if (tid >= KNN_NQ || q0 + tid >= m) return;
+  int bl[KNN_KMAX];
+#pragma unroll
+  for (int s = 0; s < KNN_KMAX; ++s) bl[s] = (s < k && sel[tid][s] != 0x7fffffff) ? label[sel[tid][s]] : -1;
   int best = KNN_CMAX, bestc = -1;
 #pragma unroll
   for (int s = 0; s < KNN_KMAX; ++s) {
     if (s >= k || bl[s] < 0) continue;
-    int cnt = 0;
+    int n = 0;
 #pragma unroll
-    for (int t = 0; t < KNN_KMAX; ++t) cnt += (t < k && bl[t] == bl[s]) ? 1 : 0;
-    if (cnt > bestc || (cnt == bestc && bl[s] < best)) {
-      bestc = cnt;
+    for (int t = 0; t < KNN_KMAX; ++t) n += (t < k && bl[t] == bl[s]) ? 1 : 0;
+    if (n > bestc || (n == bestc && bl[s] < best)) {
+      bestc = n;
       best = bl[s];
     }
   }
   if (bestc < 0) best = 0;   // no candidate in other folds
-  pred[i] = best;
-  atomicAdd(&conf[(int64_t)best * nclass + label[i]], 1ull);
+  pred[q0 + tid] = best;
+  atomicAdd(&conf[(int64_t)best * nclass + label[q0 + tid]], 1ull);
 }
 
 }  // namespace eodabe

@@ -122,3 +122,34 @@ def test_knn_hand_example_on_gpu():
     pred, conf, oa = E.knn_cv(F, lab, fold, 1, 2)
     assert pred.cpu().tolist() == [0, 0, 0, 1, 1, 1]
     assert conf.tolist() == [[2, 1], [1, 2]] and abs(oa - 4 / 6) <= 1e-15
+
+
+@pytest.mark.parametrize("m,d,k,nclass,kind", [
+    (1, 3, 2, 2, "spread"), (16, 1, 1, 2, "spread"), (17, 4, 16, 3, "spread"), (33, 5, 3, 4, "offset"),
+    (129, 15, 5, 6, "spread"), (300, 32, 16, 64, "spread"), (257, 29, 9, 5, "offset"), (400, 7, 4, 5, "grid"),
+    (350, 12, 5, 4, "same"), (200, 16, 5, 4, "onefold"), (150, 6, 3, 3, "huge"), (150, 6, 3, 3, "tiny")])
+def test_knn_filter_edges(m, d, k, nclass, kind):
+    """The FP32 filter never changes an answer: ragged tiles, every feature
+    tile width, features far from the origin, ties and duplicates (more pairs
+    within the bound than a list holds), no candidate at all, and values whose
+    squares leave the FP32 range.  Predictions are integers: equality."""
+    rng = np.random.default_rng(m + 7 * d + k)
+    F = rng.standard_normal((m, d))
+    if kind == "offset":
+        F = 1e-3 * F + 1000.0
+    elif kind == "grid":
+        F = np.round(F)
+    elif kind == "same":
+        F[: m - 20] = 0.25
+    elif kind == "huge":
+        F[::3] *= 1e30
+    elif kind == "tiny":
+        F *= 1e-25
+    buf = np.full((m, d + 3), 7.0, np.float32)          # rows of a wider buffer
+    buf[:, :d] = F
+    lab = rng.integers(0, nclass, m).astype(np.int32)
+    fold = (np.zeros(m) if kind == "onefold" else rng.integers(0, 10, m)).astype(np.int32)
+    Fd = torch.from_numpy(buf).cuda()[:, :d]
+    pred, conf, oa = E.knn_cv(Fd, torch.from_numpy(lab).cuda(), torch.from_numpy(fold).cuda(), k, nclass)
+    p_ref, c_ref, oa_ref = P.knn_cv(buf[:, :d], lab, fold, k, nclass)
+    assert np.array_equal(pred.cpu().numpy(), p_ref) and np.array_equal(conf, c_ref) and oa == oa_ref
