@@ -1764,80 +1764,31 @@ int eodabe_tune_batched(eodabe_ctx* ctx, int ntiles, const void* const* A, const
 }  // extern "C"
 namespace {
 struct MlpWS {
-  float *z1, *h1, *z2, *h2, *z3, *h3, *y, *dy, *g1, *g2;
+  MlpTape tape;
   double* loss;
   size_t total;
 };
 MlpWS mlp_carve(void* base, int B) {
   Carver c(base);
   MlpWS w{};
-  const int64_t bh = (int64_t)std::max(B, 1) * MLP_H;
-  w.z1 = c.take<float>(bh);
-  w.h1 = c.take<float>(bh);
-  w.z2 = c.take<float>(bh);
-  w.h2 = c.take<float>(bh);
-  w.z3 = c.take<float>(bh);
-  w.h3 = c.take<float>(bh);
-  w.y = c.take<float>(2 * (int64_t)std::max(B, 1));
-  w.dy = c.take<float>(2 * (int64_t)std::max(B, 1));
-  w.g1 = c.take<float>(bh);
-  w.g2 = c.take<float>(bh);
+  const int64_t b = std::max(B, 1);
+  for (int l = 0; l < 3; ++l) {
+    w.tape.h[l] = c.take<float>(b * MLP_H);
+    w.tape.g[l] = c.take<float>(b * MLP_H);
+  }
+  w.tape.dy = c.take<float>(MLP_OUT * b);
+  w.tape.loss_row = c.take<double>(b);
   w.loss = c.take<double>(1);
   w.total = c.off + 256;
   return w;
 }
-template <bool TA, bool TB>
-int mlp_gemm(eodabe_ctx* ctx, hipStream_t st, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
-             int M, int N, int K, const float* bias) {
-  dim3 grid((unsigned)cdiv(N, 64), (unsigned)cdiv(M, 64));
-  hipLaunchKernelGGL((k_mlp_gemm<TA, TB>), grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K, bias);
+// Y (forward) or the tape (grad) of a batch, see k_mlp_net.
+template <bool GRAD>
+int mlp_net(eodabe_ctx* ctx, hipStream_t st, const float* P, const float* X, const float* T, int B, float* Y,
+            const MlpTape& tape) {
+  hipLaunchKernelGGL((k_mlp_net<GRAD>), dim3((unsigned)cdiv(B, MLP_ROWS)), dim3(64 * MLP_H / 16), 0, st, P, X, T, B, Y,
+                     tape, (uintptr_t)P % 16 == 0 ? 1 : 0);
   LAUNCHCHK();
-  return 0;
-}
-int mlp_act(eodabe_ctx* ctx, hipStream_t st, const float* Z, float* H, int64_t cnt) {
-  hipLaunchKernelGGL(k_gelu_fwd, dim3((unsigned)std::min<int64_t>(cdiv(cnt, 256), 2048)), dim3(256), 0, st, Z, H,
-                     cnt);
-  LAUNCHCHK();
-  return 0;
-}
-int mlp_act_grad(eodabe_ctx* ctx, hipStream_t st, float* G, const float* Z, int64_t cnt) {
-  hipLaunchKernelGGL(k_gelu_bwd, dim3((unsigned)std::min<int64_t>(cdiv(cnt, 256), 2048)), dim3(256), 0, st, G, Z, G,
-                     cnt);
-  LAUNCHCHK();
-  return 0;
-}
-int mlp_forward_impl(eodabe_ctx* ctx, hipStream_t st, const float* P, const float* X, int B, const MlpWS& w) {
-  TRY((mlp_gemm<false, true>(ctx, st, X, MLP_IN, P + MLP_W1, MLP_IN, w.z1, MLP_H, B, MLP_H, MLP_IN, P + MLP_B1)));
-  TRY(mlp_act(ctx, st, w.z1, w.h1, (int64_t)B * MLP_H));
-  TRY((mlp_gemm<false, true>(ctx, st, w.h1, MLP_H, P + MLP_W2, MLP_H, w.z2, MLP_H, B, MLP_H, MLP_H, P + MLP_B2)));
-  TRY(mlp_act(ctx, st, w.z2, w.h2, (int64_t)B * MLP_H));
-  TRY((mlp_gemm<false, true>(ctx, st, w.h2, MLP_H, P + MLP_W3, MLP_H, w.z3, MLP_H, B, MLP_H, MLP_H, P + MLP_B3)));
-  TRY(mlp_act(ctx, st, w.z3, w.h3, (int64_t)B * MLP_H));
-  TRY((mlp_gemm<false, true>(ctx, st, w.h3, MLP_H, P + MLP_W4, MLP_H, w.y, MLP_OUT, B, MLP_OUT, MLP_H,
-                             P + MLP_B4)));
-  return 0;
-}
-// dW = dZ^T H_prev, db = column sums of dZ, dH_prev = dZ W (then times GELU'(Z_prev))
-int mlp_layer_grad(eodabe_ctx* ctx, hipStream_t st, const float* dZ, int nout, const float* Hprev, int nin, int B,
-                   const float* W, float* dW, float* db, float* dHprev) {
-  TRY((mlp_gemm<true, false>(ctx, st, dZ, nout, Hprev, nin, dW, nin, nout, nin, B, nullptr)));
-  hipLaunchKernelGGL(k_colsum, dim3((unsigned)cdiv(nout, 256)), dim3(256), 0, st, dZ, B, nout, db);
-  LAUNCHCHK();
-  if (dHprev) TRY((mlp_gemm<false, false>(ctx, st, dZ, nout, W, nin, dHprev, nin, B, nin, nout, nullptr)));
-  return 0;
-}
-int mlp_backward_impl(eodabe_ctx* ctx, hipStream_t st, const float* P, const float* X, const float* T, int B,
-                      float* G, const MlpWS& w) {
-  hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(256), 0, st, w.y, T, B, w.dy, w.loss);
-  LAUNCHCHK();
-  const int64_t bh = (int64_t)B * MLP_H;
-  TRY(mlp_layer_grad(ctx, st, w.dy, MLP_OUT, w.h3, MLP_H, B, P + MLP_W4, G + MLP_W4, G + MLP_B4, w.g1));
-  TRY(mlp_act_grad(ctx, st, w.g1, w.z3, bh));
-  TRY(mlp_layer_grad(ctx, st, w.g1, MLP_H, w.h2, MLP_H, B, P + MLP_W3, G + MLP_W3, G + MLP_B3, w.g2));
-  TRY(mlp_act_grad(ctx, st, w.g2, w.z2, bh));
-  TRY(mlp_layer_grad(ctx, st, w.g2, MLP_H, w.h1, MLP_H, B, P + MLP_W2, G + MLP_W2, G + MLP_B2, w.g1));
-  TRY(mlp_act_grad(ctx, st, w.g1, w.z1, bh));
-  TRY(mlp_layer_grad(ctx, st, w.g1, MLP_H, X, MLP_IN, B, P + MLP_W1, G + MLP_W1, G + MLP_B1, nullptr));
   return 0;
 }
 }  // namespace
@@ -1855,8 +1806,7 @@ int eodabe_mlp_forward(eodabe_ctx* ctx, const float* params, const float* X, int
   if (!ws || ws_bytes < w.total) return EODABE_EWORKSPACE;
   TRY(check_dev(ctx));
   hipStream_t st = ctx->stream;
-  TRY(mlp_forward_impl(ctx, st, params, X, batch, w));
-  HIPCHK(hipMemcpyAsync(Y, w.y, sizeof(float) * 2 * (size_t)batch, hipMemcpyDeviceToDevice, st));
+  TRY(mlp_net<false>(ctx, st, params, X, nullptr, batch, Y, w.tape));
   return 0;
 }
 
@@ -1868,8 +1818,9 @@ int eodabe_mlp_grad(eodabe_ctx* ctx, const float* params, const float* X, const 
   if (!ws || ws_bytes < w.total) return EODABE_EWORKSPACE;
   TRY(check_dev(ctx));
   hipStream_t st = ctx->stream;
-  TRY(mlp_forward_impl(ctx, st, params, X, batch, w));
-  TRY(mlp_backward_impl(ctx, st, params, X, T, batch, grads, w));
+  TRY(mlp_net<true>(ctx, st, params, X, T, batch, nullptr, w.tape));
+  hipLaunchKernelGGL(k_mlp_wgrad, dim3(MLP_WG_TILES + 1), dim3(256), 0, st, X, w.tape, batch, grads, w.loss);
+  LAUNCHCHK();
   if (loss) {
     HIPCHK(hipMemcpyAsync(loss, w.loss, sizeof(double), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));

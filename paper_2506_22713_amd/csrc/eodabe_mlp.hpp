@@ -54,103 +54,257 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
   return cdf + z * pdf;
 }
 
-// ---------------------------------------------------------------------------
-// C (M x N, row-major ldc) = op(A) op(B) (+ bias[j]) in FP32 on MFMA:
-// op(A)(i,k) = TA ? A[k*lda + i] : A[i*lda + k], op(B)(k,j) = TB ?
-// B[j*ldb + k] : B[k*ldb + j].  A 64 x 64 tile per workgroup; K in chunks of
-// 16 staged through LDS; wave w computes rows 32 (w / 2) .. + 32 and columns
-// 32 (w % 2) .. + 32 as 2 x 2 MFMA tiles.
-// ---------------------------------------------------------------------------
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void k_mlp_gemm(const float* __restrict__ A, int lda, const float* __restrict__ B,
-                                                  int ldb, float* __restrict__ C, int ldc, int M, int N, int K,
-                                                  const float* __restrict__ bias) {
+constexpr int MLP_ROWS = 16;          // samples of one workgroup
+constexpr int MLP_LDH = MLP_H + 4;    // row stride of a layer in LDS
+
+// acc += (LDS rows of `h`) W^T for the 16 columns of this wave: W row-major
+// (nout x MLP_H), lane (li, g) takes row li of the tile and four K at a time.
+__device__ __forceinline__ f32x4 mlp_fwd_tile(const float (*h)[MLP_LDH], const float* __restrict__ Wr, int li, int g,
+                                              bool vec) {
   typedef Mfma<float> MF;
-  __shared__ float As[64][17], Bs[16][65];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r = lane & 15, g = lane >> 4;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  const int wi = 32 * (wv >> 1), wj = 32 * (wv & 1);
-  MF::acc_t acc[2][2];
+  f32x4 a0 = MF::zero(), a1 = MF::zero();
+#pragma unroll 8
+  for (int t = 0; t < MLP_H / 16; ++t) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(&h[li][16 * t + 4 * g]);
+    f32x4 w;
+    if (vec) {
+      w = *reinterpret_cast<const f32x4*>(Wr + 16 * t + 4 * g);
+    } else {
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int c = 0; c < 2; ++c) acc[a][c] = MF::zero();
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int idx = tid; idx < 64 * 16; idx += 256) {
-      // A tile: rows i0..i0+63, k0..k0+15 ; B tile: k0..k0+15, cols j0..j0+63
-      const int ii = TA ? (idx & 63) : (idx >> 4), kk = TA ? (idx >> 6) : (idx & 15);
-      const int gi = i0 + ii, gk = k0 + kk;
-      As[ii][kk] = (gi < M && gk < K) ? (TA ? A[(int64_t)gk * lda + gi] : A[(int64_t)gi * lda + gk]) : 0.f;
-      const int jj = TB ? (idx >> 4) : (idx & 63), kb = TB ? (idx & 15) : (idx >> 6);
-      const int gj = j0 + jj, gkb = k0 + kb;
-      Bs[kb][jj] = (gj < N && gkb < K) ? (TB ? B[(int64_t)gj * ldb + gkb] : B[(int64_t)gkb * ldb + gj]) : 0.f;
+      for (int e = 0; e < 4; ++e) w[e] = Wr[16 * t + 4 * g + e];
     }
+    a0 = MF::op(x[0], w[0], a0);
+    a1 = MF::op(x[1], w[1], a1);
+    a0 = MF::op(x[2], w[2], a0);
+    a1 = MF::op(x[3], w[3], a1);
+  }
+  return a0 + a1;
+}
+// acc += (LDS rows of `d`) W for the 16 columns of this wave (Wc = W + column).
+__device__ __forceinline__ f32x4 mlp_bwd_tile(const float (*d)[MLP_LDH], const float* __restrict__ Wc, int li, int g) {
+  typedef Mfma<float> MF;
+  f32x4 a0 = MF::zero(), a1 = MF::zero();
+#pragma unroll 8
+  for (int t = 0; t < MLP_H / 16; ++t) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(&d[li][16 * t + 4 * g]);
+    float w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = Wc[(int64_t)(16 * t + 4 * g + e) * MLP_H];
+    a0 = MF::op(x[0], w[0], a0);
+    a1 = MF::op(x[1], w[1], a1);
+    a0 = MF::op(x[2], w[2], a0);
+    a1 = MF::op(x[3], w[3], a1);
+  }
+  return a0 + a1;
+}
+
+// What the weight gradients need of a batch, in the workspace (row-major):
+// inputs h[l] of layers 2..4 and the gradients g[l] at the sums of layers
+// 1..3 (B x H each), dy (B x 2) at the heads, and each sample's loss.
+struct MlpTape {
+  float *h[3], *g[3], *dy;
+  double* loss_row;
+};
+
+// The whole network on 16 samples per workgroup, and with GRAD its backward
+// pass down to the sums of layer 1.  The layers are too small to be worth a
+// launch each (256 samples: eleven GEMM launches of 25-35 us on 4 to 16
+// workgroups, and as many elementwise ones): here the activations of a strip
+// stay in LDS, a wave owns 16 of the 256 columns of every layer, and the sums z
+// stay in its registers until GELU'(z) needs them, since the forward and the
+// backward tile of a column have the same lane layout.  What is left is the
+// weights' way from L2 (256 KB a layer and workgroup) and 64 MFMAs in a row.
+// A training step of 256 samples (both kernels, Adam, the loss on the host):
+// 568 -> 77 us.
+template <bool GRAD>
+__global__ __launch_bounds__(64 * MLP_H / 16) void k_mlp_net(const float* __restrict__ P,
+                                                             const float* __restrict__ X,
+                                                             const float* __restrict__ T, int B,
+                                                             float* __restrict__ Y, MlpTape tape, int vec) {
+  typedef Mfma<float> MF;
+  __shared__ float h[MLP_ROWS][MLP_LDH], x[MLP_ROWS][84], sdy[MLP_ROWS][2];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, g = lane >> 4;
+  const int64_t b0 = blockIdx.x * (int64_t)MLP_ROWS;
+  const int col = 16 * wv + li;
+  for (int i = tid; i < MLP_ROWS * 80; i += 64 * MLP_H / 16) {
+    const int r = i / 80, c = i % 80;
+    x[r][c] = (c < MLP_IN && b0 + r < B) ? X[(b0 + r) * MLP_IN + c] : 0.f;
+  }
+  f32x4 z[3];
+  {
+    float w[20];
+#pragma unroll
+    for (int s = 0; s < 20; ++s) w[s] = 4 * s + g < MLP_IN ? P[MLP_W1 + (int64_t)col * MLP_IN + 4 * s + g] : 0.f;
     __syncthreads();
+    f32x4 acc = MF::zero();
 #pragma unroll
-    for (int ks = 0; ks < 16; ks += 4) {
+    for (int s = 0; s < 20; ++s) acc = MF::op(x[li][4 * s + g], w[s], acc);
+    z[0] = acc + P[MLP_B1 + col];
+  }
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+  for (int l = 0; l < 3; ++l) {
+    if (l) {
+      const int64_t W = l == 1 ? MLP_W2 : MLP_W3, b = l == 1 ? MLP_B2 : MLP_B3;
+      z[l] = mlp_fwd_tile(h, P + W + (int64_t)col * MLP_H, li, g, vec) + P[b + col];
+    }
+    __syncthreads();                                   // every wave has read the layer below
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
-          acc[a][c] = MF::op(As[wi + 16 * a + r][ks + g], Bs[ks + g][wj + 16 * c + r], acc[a][c]);
+    for (int e = 0; e < 4; ++e) {
+      const int r = MF::row(g, e);
+      const float a = gelu_f(z[l][e]);
+      h[r][col] = a;
+      if (GRAD && b0 + r < B) tape.h[l][(b0 + r) * MLP_H + col] = a;
     }
     __syncthreads();
   }
+  // heads: wave r takes sample r
+  {
+    float y0 = 0.f, y1 = 0.f;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int j = j0 + wj + 16 * c + r;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int i = i0 + wi + 16 * a + MF::row(g, e);
-        if (i < M && j < N) C[(int64_t)i * ldc + j] = acc[a][c][e] + (bias ? bias[j] : 0.f);
+    for (int e = 0; e < 4; ++e) {
+      const float a = h[wv][64 * e + lane];
+      y0 = fmaf(a, P[MLP_W4 + 64 * e + lane], y0);
+      y1 = fmaf(a, P[MLP_W4 + MLP_H + 64 * e + lane], y1);
+    }
+    for (int o = 1; o < 64; o <<= 1) {
+      y0 += __shfl_xor(y0, o);
+      y1 += __shfl_xor(y1, o);
+    }
+    y0 += P[MLP_B4];
+    y1 += P[MLP_B4 + 1];
+    const int64_t b = b0 + wv;
+    if (!GRAD) {
+      if (lane == 0 && b < B) {
+        Y[2 * b] = y0;
+        Y[2 * b + 1] = y1;
       }
+      return;
     }
-}
-
-__global__ void k_gelu_fwd(const float* __restrict__ Z, float* __restrict__ H, int64_t count) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
-    H[i] = gelu_f(Z[i]);
-}
-
-// dZ = dH * GELU'(Z) (in place over dH allowed)
-__global__ void k_gelu_bwd(const float* __restrict__ dH, const float* __restrict__ Z, float* __restrict__ dZ,
-                           int64_t count) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
-    dZ[i] = dH[i] * gelu_grad_f(Z[i]);
-}
-
-// Loss (1/B) sum_b [(y_b0 - t_b)^2 + rho_tau(t_b - y_b1)] on one workgroup
-// (FP64 accumulation, fixed order) and its gradient dY (B x 2).
-__global__ __launch_bounds__(256) void k_mlp_loss(const float* __restrict__ Y, const float* __restrict__ T, int B,
-                                                  float* __restrict__ dY, double* __restrict__ loss) {
-  __shared__ double red[256];
-  double s = 0.0;
-  const double invB = 1.0 / B;
-  for (int b = threadIdx.x; b < B; b += 256) {
-    const double y0 = Y[2 * b], y1 = Y[2 * b + 1], t = T[b];
-    const double u = t - y1;
-    s += (y0 - t) * (y0 - t) + (u > 0 ? MLP_TAU * u : (MLP_TAU - 1.0) * u);
-    dY[2 * b] = (float)(2.0 * (y0 - t) * invB);
-    dY[2 * b + 1] = (float)((u > 0 ? -MLP_TAU : 1.0 - MLP_TAU) * invB);
+    if (lane == 0) {
+      float d0 = 0.f, d1 = 0.f;
+      if (b < B) {
+        const double invB = 1.0 / B, t = T[b], u = t - (double)y1, v = (double)y0 - t;
+        tape.loss_row[b] = v * v + (u > 0 ? MLP_TAU * u : (MLP_TAU - 1.0) * u);
+        d0 = (float)(2.0 * v * invB);
+        d1 = (float)((u > 0 ? -MLP_TAU : 1.0 - MLP_TAU) * invB);
+        tape.dy[2 * b] = d0;
+        tape.dy[2 * b + 1] = d1;
+      }
+      sdy[wv][0] = d0;
+      sdy[wv][1] = d1;
+    }
   }
-  red[threadIdx.x] = s;
   __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-    __syncthreads();
+#pragma unroll
+  for (int l = 2; l >= 0; --l) {
+    f32x4 d;
+    if (l == 2) {
+      const float w0 = P[MLP_W4 + col], w1 = P[MLP_W4 + MLP_H + col];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[e] = fmaf(sdy[MF::row(g, e)][0], w0, sdy[MF::row(g, e)][1] * w1);
+    } else {
+      d = mlp_bwd_tile(h, P + (l == 1 ? MLP_W3 : MLP_W2) + col, li, g);
+      __syncthreads();                                 // every wave has read the layer above
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = MF::row(g, e);
+      const float v = d[e] * gelu_grad_f(z[l][e]);
+      if (l) h[r][col] = v;
+      if (b0 + r < B) tape.g[l][(b0 + r) * MLP_H + col] = v;
+    }
+    if (l) __syncthreads();
   }
-  if (threadIdx.x == 0) *loss = red[0] * invB;
 }
 
-// out[j] = sum_b G[b*N + j] (bias gradients)
-__global__ void k_colsum(const float* __restrict__ G, int B, int N, float* __restrict__ out) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= N) return;
-  float s = 0.f;
-  for (int b = 0; b < B; ++b) s += G[(int64_t)b * N + j];
-  out[j] = s;
+// All weight and bias gradients in one launch: dW = g^T h and db = column
+// sums of g, a 16 x 16 tile of one layer per workgroup, the batch split over
+// its four waves and summed in wave order.  The last workgroup sums the loss
+// (FP64, fixed order).  At 256 samples that is 608 workgroups of 16 MFMAs a
+// wave; with a launch per product the chip was at most a quarter full.
+constexpr int MLP_HT = MLP_H / 16, MLP_IT = (MLP_IN + 15) / 16;
+constexpr int MLP_WG_TILES = 2 * MLP_HT * MLP_HT + MLP_HT * MLP_IT + MLP_HT;
+__global__ __launch_bounds__(256) void k_mlp_wgrad(const float* __restrict__ X, MlpTape tape, int B,
+                                                   float* __restrict__ G, double* __restrict__ loss) {
+  typedef Mfma<float> MF;
+  __shared__ f32x4 part[4][64];
+  __shared__ float bpart[4][64];
+  __shared__ double red[256];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, g = lane >> 4;
+  int t = blockIdx.x;
+  if (t == MLP_WG_TILES) {
+    double s = 0.0;
+    for (int b = tid; b < B; b += 256) s += tape.loss_row[b];
+    red[tid] = s;
+    __syncthreads();
+    for (int off = 128; off > 0; off >>= 1) {
+      if (tid < off) red[tid] += red[tid + off];
+      __syncthreads();
+    }
+    if (tid == 0) *loss = red[0] * (1.0 / B);
+    return;
+  }
+  const float *a, *h;              // gradient (B x na) and layer input (B x nh)
+  int na = MLP_H, nh = MLP_H, it, jt;
+  int64_t ow, ob;
+  if (t < 2 * MLP_HT * MLP_HT) {
+    const int l = t / (MLP_HT * MLP_HT);
+    t %= MLP_HT * MLP_HT;
+    it = t / MLP_HT;
+    jt = t % MLP_HT;
+    a = l ? tape.g[2] : tape.g[1];
+    h = l ? tape.h[1] : tape.h[0];
+    ow = l ? MLP_W3 : MLP_W2;
+    ob = l ? MLP_B3 : MLP_B2;
+  } else if (t < 2 * MLP_HT * MLP_HT + MLP_HT * MLP_IT) {
+    t -= 2 * MLP_HT * MLP_HT;
+    it = t / MLP_IT;
+    jt = t % MLP_IT;
+    a = tape.g[0];
+    h = X;
+    nh = MLP_IN;
+    ow = MLP_W1;
+    ob = MLP_B1;
+  } else {
+    it = 0;
+    jt = t - 2 * MLP_HT * MLP_HT - MLP_HT * MLP_IT;
+    a = tape.dy;
+    h = tape.h[2];
+    na = MLP_OUT;
+    ow = MLP_W4;
+    ob = MLP_B4;
+  }
+  const int i = 16 * it + li, j = 16 * jt + li;
+  const bool iok = i < na, jok = j < nh;
+  const int kper = ((B + 3) / 4 + 3) / 4 * 4;          // samples of a wave, a multiple of 4
+  const int k0 = wv * kper, k1 = k0 + kper < B ? k0 + kper : B;
+  f32x4 acc = MF::zero();
+  float bs = 0.f;
+#pragma unroll 8
+  for (int k = k0; k < k1; k += 4) {
+    const bool ok = k + g < k1;
+    const int64_t b = ok ? k + g : k;
+    const float av = iok && ok ? a[b * na + i] : 0.f;
+    const float hv = jok && ok ? h[b * nh + j] : 0.f;
+    acc = MF::op(av, hv, acc);
+    bs += av;
+  }
+  part[wv][lane] = acc;
+  bpart[wv][lane] = bs;
+  __syncthreads();
+  if (wv) return;
+  acc = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int r = 16 * it + MF::row(g, e);
+    if (r < na && jok) G[ow + (int64_t)r * nh + j] = acc[e];
+  }
+  if (jt == 0 && g == 0 && iok) {
+    float s = 0.f;
+    for (int w = 0; w < 4; ++w)
+      for (int q = 0; q < 4; ++q) s += bpart[w][16 * q + li];
+    G[ob + i] = s;
+  }
 }
 
 // One Adam step with bias-corrected moments.  The coefficients come from

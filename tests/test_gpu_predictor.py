@@ -71,6 +71,36 @@ def test_mlp_gradient_matches_oracle(B):
         off += cnt
 
 
+@pytest.mark.parametrize("B,off", [(1, 0), (15, 1), (16, 0), (17, 3), (63, 0), (65, 2), (259, 0)])
+def test_mlp_ragged_batches(B, off):
+    """Strips of 16 samples and the batch split of the weight gradients at
+    their edges, parameters off a 16-byte boundary too, through the C ABI;
+    FP32 sums of at most 260 terms: 1e-5 forward, 1e-4 of the largest gradient
+    entry as for whole batches."""
+    say("mlp ragged", B, off)
+    ctx = E.Context()
+    p = _rand_params(B)
+    rng = np.random.default_rng(B + 7)
+    X = rng.uniform(-1, 1, size=(B, 67)).astype(np.float32)
+    y0, _ = PO.forward(p.astype(np.float64), X.astype(np.float64))
+    T = (y0[:, 1] + np.where(rng.random(B) < 0.5, 0.5, -0.5)).astype(np.float32)
+    buf = torch.zeros(PR.NPARAM + 4, device="cuda")
+    buf[off:off + PR.NPARAM] = torch.from_numpy(p).cuda()
+    pr = PR.Predictor(p)
+    pr.params = buf[off:off + PR.NPARAM]
+    Xd, Td = torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda()
+    assert np.allclose(pr.forward(ctx, Xd).cpu().numpy(), y0, rtol=1e-5, atol=1e-5)
+    loss = pr.grad(ctx, Xd, Td)
+    Lr, gr = PO.grad(p.astype(np.float64), X.astype(np.float64), T.astype(np.float64))
+    g = pr.grads.cpu().numpy().astype(np.float64)
+    assert abs(loss - Lr) <= 1e-5 * max(1.0, abs(Lr))
+    at = 0
+    for name, shp in PO.SHAPES:
+        n = int(np.prod(shp))
+        assert np.abs(g[at:at + n] - gr[at:at + n]).max() <= 1e-4 * max(np.abs(gr[at:at + n]).max(), 1e-3), name
+        at += n
+
+
 def test_mlp_adam_matches_oracle():
     say("mlp adam")
     ctx = E.Context()
