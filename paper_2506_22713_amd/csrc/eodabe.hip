@@ -1066,10 +1066,6 @@ int run_basis(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const 
         a.stop_block = stopb;
         a.block_id = blk;
         a.st = w.st;
-        a.R1 = w.r1;
-        a.R1inv = w.r1inv;
-        a.R2 = w.r2;
-        a.R2inv = w.r2inv;
         a.dead = deadj;
         a.norm_parts = w.normparts;
         a.max_parts = g.lp ? w.maxparts : nullptr;
@@ -1099,10 +1095,6 @@ int run_basis(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const 
         a.stop_block = stopb;
         a.block_id = blk;
         a.st = w.st;
-        a.R1 = w.r1;
-        a.R1inv = w.r1inv;
-        a.R2 = w.r2;
-        a.R2inv = w.r2inv;
         a.dead = deadj;
         a.stop_test = 1;
         a.col0 = col0;
@@ -1337,10 +1329,6 @@ int close_small(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, cons
     a.counter = &w.st->counter[2];
     a.gate = gate;
     a.st = w.st;
-    a.R1 = w.rb1;
-    a.R1inv = w.rb3;
-    a.R2 = w.rb2;
-    a.R2inv = w.rb5;
     a.dead = w.deadbig;
     a.fresh = 1;
     a.count_floors = 1;

@@ -1754,8 +1754,8 @@ __device__ __forceinline__ void lds_gemm(const double* A, const double* B, Out o
 
 // ---------------------------------------------------------------------------
 // Cholesky with inverse, on the four waves of a workgroup, of a symmetric
-// positive semi-definite f x f matrix G (FP64, f <= F): elimination over
-// the augmented rows [G | I].  With G = L U (L unit lower, U = diag(alpha)
+// positive semi-definite f x f matrix G (FP64, f <= F), with every pivot rule
+// (chol_inv below takes the common case): elimination over the augmented rows [G | I].  With G = L U (L unit lower, U = diag(alpha)
 // R) the elimination turns I into L^{-1} = diag(alpha) R^{-T}, so row k of
 // the right half divided by alpha_k is column k of R^{-1}.  Pivot rules:
 //   dead column (flag in dmask_in): R(k,k) = 1, row k and column k of R
@@ -1785,9 +1785,9 @@ __device__ __forceinline__ void lds_gemm(const double* A, const double* B, Out o
 // floored).
 // ---------------------------------------------------------------------------
 template <int F>
-__device__ void chol_inv(double* Gs, double* Ri, double* work, double* dgs, int f,
-                         uint64_t dmask_in, int first_pass, uint64_t* dmask_out, int* nfloor,
-                         const double* dg_in = nullptr, uint64_t* nolive_out = nullptr) {
+__device__ __noinline__ void chol_inv_general(double* Gs, double* Ri, double* work, double* dgs, int f,
+                                              uint64_t dmask_in, int first_pass, uint64_t* dmask_out, int* nfloor,
+                                              const double* dg_in, uint64_t* nolive_out) {
   typedef SmallCfg<F> C;
   constexpr int LD = C::LD, NR = C::NR, NCL = C::NCL, W2 = 2 * F;
   double* P = work;                      // panel rows: P[j*W2 + c], j < 8
@@ -1989,129 +1989,224 @@ __device__ void chol_inv(double* Gs, double* Ri, double* work, double* dgs, int 
 }
 
 
+// v of lane N of this lane's row of 16, in every lane of the row (one DPP
+// move; the intrinsic has no builtin for 64-bit values).
+extern "C" __device__ double eodabe_dpp_f64(double, double, int, int, int, bool) __asm("llvm.amdgcn.update.dpp.f64");
+template <int N>
+__device__ __forceinline__ double row_bcast(double v) {
+  return eodabe_dpp_f64(0.0, v, 0x150 + N, 0xf, 0xf, true);
+}
+
+// Row I.. of the update after pivot K (see chol16).
+template <int K, int I>
+__device__ __forceinline__ void chol16_rows(double (&D)[16], double (&M)[16]) {
+  if constexpr (I < 16) {
+    const double m = row_bcast<I>(D[K]);
+    D[I] = fma(-m, D[K], D[I]);
+    M[I] = fma(-m, M[K], M[I]);
+    // in this order: left to itself the compiler keeps all 120 multipliers
+    // and runs M's updates after D's
+    asm volatile("" : "+v"(D[I]), "+v"(M[I]));
+    chol16_rows<K, I + 1>(D, M);
+  }
+}
+
+// Pivots K..15 of the elimination of a 16 x 16 block S, all in registers:
+// lane (g, r) holds rows 0..15 of column r of S in D (every row of 16 lanes
+// its own copy, upper part read) and of another column in M.  The rows are
+// scaled by the root of their pivot: D becomes R at and above the diagonal,
+// M the solution of R^T M' = M.  al: R(r, r), not a number where a pivot was
+// not positive and finite.  The multipliers come by DPP within the row of
+// lanes; a pivot's chain is broadcast, root, scale, one update, and the other
+// rows' updates fill its waits.
+template <int K = 0>
+__device__ __forceinline__ void chol16(double (&D)[16], double (&M)[16], int r, double& al) {
+  if constexpr (K < 16) {
+    const double p = row_bcast<K>(D[K]);
+    // 1/sqrt(p): hardware estimate (2^-24) and one cubic step
+    const double y0 = __builtin_amdgcn_rsq(p);
+    const double e = fma(-(p * y0), y0, 1.0);
+    const double y = fma(y0 * e, fma(e, 0.375, 0.5), y0);
+    D[K] *= y;
+    M[K] *= y;
+    al = r == K ? D[K] : al;
+    chol16_rows<K, K + 1>(D, M);
+    chol16<K + 1>(D, M, r, al);
+  }
+}
+
 // ---------------------------------------------------------------------------
-// chol_inv for the common case, f <= F <= 32: no dead column and every
-// pivot above the floor.  The rows and columns past f are padded by the
-// identity, so every 8-pivot panel is whole and the elimination runs fully
-// without a branch in its panels; the arithmetic on rows and columns < f is that
-// of chol_inv's fast panels (the same operations in the same order), so R
-// and R^{-1} are bit for bit chol_inv's.  Returns false (uniform) when a
-// pivot fails the floor test or is not finite: R, R^{-1} and Gs are then
-// void and the caller restores G and runs chol_inv.  Gs: G on entry
-// (row-major, ld F+1), R on exit; Ri: R^{-1}; work: 24F doubles; dgs: F
-// doubles.  Layout as in chol_inv: lane c owns column c of [G | I]; wave w
-// holds rows 8(p + s/2) + 4(s%2) + w in slot s during panel p.
+// chol_inv for the common case (no dead column, every pivot above the
+// floor), blocked by 16.  Wave 0 factors a diagonal block in registers
+// (chol16) with the identity and the row panel's blocks in its lane groups,
+// so R_bb^{-1} and the panel of R come out of the same sweep; the other waves
+// meanwhile form the products that column b of R^{-1} needs,
+//   (R^{-1})_ib = -(sum_{i <= k < b} (R^{-1})_ik R_kb) R_bb^{-1},
+// and the trailing update runs as FP64 MFMA tiles on all waves.  What bounds
+// it is the chain of pivots on wave 0 and the LDS round trips between its
+// blocks; chol_inv_general's eight-pivot panels, which every wave repeats
+// from LDS, take 4500 cycles per eight pivots.  Returns false (uniform) when a
+// pivot fails the test of the floor: G is then as on entry and the other
+// arrays are void.  Rows and columns past f are padded by the identity.
+// Arguments as chol_inv_general.
 // ---------------------------------------------------------------------------
 template <int F>
-__device__ __forceinline__ bool chol_inv_fast(double* Gs, double* Ri, double* work, double* dgs, int f) {
-  typedef SmallCfg<F> C;
-  constexpr int LD = C::LD, NR = C::NR, W2 = 2 * F;
-  static_assert(F % 8 == 0 && W2 <= 64, "one column of [G | I] per lane");
-  double* P = work;                      // panel rows: P[j*W2 + c], j < 8
-  double* XT = work + 8 * W2;            // multipliers: XT[j*F + i] = R(kp+j, i)
-  const int tid = threadIdx.x, lane = tid & 63;
+__device__ __forceinline__ bool chol_inv_blocked(double* Gs, double* Ri, double* work, double* dgs, int f,
+                                                 const double* dg_in) {
+  typedef Mfma<double> MF;
+  constexpr int LD = SmallCfg<F>::LD, NB = F / 16;
+  static_assert(F == 16 || F == 32 || F == 64, "blocks of 16, at most four");
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = lane;
-  const bool live = c < W2;
-  for (int i = tid; i < F; i += 256) dgs[i] = i < f ? Gs[i * LD + i] : 1.0;
-  double M[NR];
+  const int nb = (f + 15) / 16;
+  double* flag = work;
+  double* dump = work + 8;               // where lanes without a column store
+  double* keep = work + 8 + 64;          // the diagonal blocks of G, for the way back
+  static_assert(8 + 64 + 256 * NB <= 24 * F, "work area");
 #pragma unroll
-  for (int s = 0; s < NR; ++s) {
-    const int i = 8 * (s / 2) + 4 * (s % 2) + w;
-    double v = 0.0;
-    if (c < F) v = (i < f && c < f) ? Gs[i * LD + c] : (i == c ? 1.0 : 0.0);
-    else if (live) v = (c - F == i) ? 1.0 : 0.0;
-    M[s] = v;
+  for (int b = 0; b < NB; ++b) {         // thread (i, j) of every diagonal block
+    const int i = 16 * b + (tid >> 4), j = 16 * b + (tid & 15);
+    const bool in = i < f && j < f;
+    const double v = Gs[i * LD + j];
+    keep[256 * b + tid] = v;
+    if (!in) Gs[i * LD + j] = i == j ? 1.0 : 0.0;
+    if (i == j) dgs[i] = in ? (dg_in ? dg_in[i] : v) : 1.0;
   }
-  __syncthreads();                       // G consumed: Gs now receives R; dgs ready
-  bool ok = true;
-  const int cl = live ? c : 0;
+  if (f < 16 * nb && f > 16)             // the last block's columns right of the others
+    for (int idx = tid; idx < 16 * (nb - 1) * 16; idx += 256) {
+      const int i = idx >> 4, j = 16 * (nb - 1) + (idx & 15);
+      if (j >= f) Gs[i * LD + j] = 0.0;
+    }
+  __syncthreads();
 #pragma unroll 1
-  for (int p = 0; p < F / 8; ++p) {              // a loop: the code stays small enough for the I-cache
-    const int kp = 8 * p;
-    if (live) {
-      P[w * W2 + c] = M[0];
-      P[(4 + w) * W2 + c] = M[1];
-    }
-    __syncthreads();
-    double d[8][8];
+  for (int b = 0; b < nb; ++b) {
+    const int o = 16 * b;
+    typename MF::acc_t inv = MF::zero(); // wave i + 1: (sum_k (R^{-1})_ik R_kb)^T
+    if (w == 0) {
+      // lane groups: the identity, blocks b+1, b+2, b+3
+      const bool act = g == 0 || b + g < nb;
+      double* src = Gs + o * LD + o + r;
+      double* col = act ? src + 16 * g : src;
+      double D[16], M[16], al = 0.0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < 16; ++i) {
+        D[i] = src[i * LD];
+        M[i] = col[i * LD];
+      }
+      if (g == 0)
 #pragma unroll
-      for (int j = i; j < 8; ++j) d[i][j] = P[i * W2 + kp + j];
-    double yv[8], dgk[8];
+        for (int i = 0; i < 16; ++i) M[i] = i == r ? 1.0 : 0.0;
+      const double flo = FLOOR_C * U64 * dgs[o + r];
+      chol16(D, M, r, al);
+      const double p = al * al;
+      const bool bad = !(p > flo && p > PIV_MIN && p < INFINITY);
+      const unsigned long long fail = __ballot(bad);
+      if (lane == 0) flag[0] = fail != 0ull ? 1.0 : 0.0;
+      // R_bb^{-1} from the identity's lanes (row r, so along the columns),
+      // the panel's blocks down theirs; R_bb by the lanes of group 3, in the
+      // same stores unless they hold block b+3
+      const bool own = g == 3 && !act;
+      double* dst = g == 0 ? Ri + (o + r) * LD + o : (own ? src : (act ? col : dump + lane));
+      const int stride = g == 0 ? 1 : (act || own ? LD : 0);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      yv[j] = P[j * W2 + cl];
-      dgk[j] = dgs[kp + j];
-    }
-    double alpha[8], ia[8];
+      for (int i = 0; i < 16; ++i) {
+        const double d = i <= r ? D[i] : 0.0;
+        dst[i * stride] = own ? d : M[i];
+      }
+      if (NB == 4 && b + 3 < nb && g == 3)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const double piv = d[j][j];
-      ok = ok && piv > FLOOR_C * U64 * dgk[j] && piv > PIV_MIN && piv < INFINITY;
-      double y = __builtin_amdgcn_rsq(piv);
-      y = y * fma(-0.5 * piv, y * y, 1.5);
-      y = y * fma(-0.5 * piv, y * y, 1.5);
-      alpha[j] = piv * y;
-      ia[j] = y;
+        for (int i = 0; i < 16; ++i) src[i * LD] = i <= r ? D[i] : 0.0;
+    } else if (w <= b) {
+      const int i = w - 1;
+      for (int k = i; k < b; ++k)
 #pragma unroll
-      for (int i = j + 1; i < 8; ++i) d[j][i] *= y;
-#pragma unroll
-      for (int i = j + 1; i < 8; ++i)
-#pragma unroll
-        for (int i2 = i; i2 < 8; ++i2) d[i][i2] = fma(-d[j][i], d[j][i2], d[i][i2]);
-    }
-    double X[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      double acc = yv[j];
-#pragma unroll
-      for (int i = 0; i < j; ++i) acc = fma(-d[i][j], X[i], acc);
-      X[j] = acc * ia[j];
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {        // rows kp + 2w + h of R, columns of R^{-1}, multipliers
-      double xj = X[0], aj = alpha[0];
-#pragma unroll
-      for (int j = 1; j < 8; ++j)
-        if (j == 2 * w + h) {
-          xj = X[j];
-          aj = alpha[j];
-        }
-      const int j = 2 * w + h, k = kp + j;
-      if (c < F) {
-        Gs[k * LD + c] = (c == k) ? aj : (c > k ? xj : 0.0);
-        XT[j * F + c] = xj;
-      } else if (live) {
-        const int cc = c - F;
-        Ri[cc * LD + k] = cc <= k ? xj : 0.0;
+        for (int s = 0; s < 4; ++s)
+          inv = MF::op(Gs[(16 * k + 4 * s + g) * LD + o + r], Ri[(16 * i + r) * LD + 16 * k + 4 * s + g], inv);
+    } else if (NB > 1 && b == 0) {       // zeros below the diagonal blocks of R^{-1}
+      for (int idx = tid - 64; idx < F * F; idx += 192) {
+        const int i = idx / F, j = idx - i * F;
+        if ((i >> 4) > (j >> 4)) Ri[i * LD + j] = 0.0;
       }
     }
     __syncthreads();
-#pragma unroll
-    for (int s = 2; s < NR; ++s) {           // rank-8 update of the rows below the panel
-      if (s >= NR - 2 * p) break;            // slots past the matrix
-      const int i = kp + 8 * (s / 2) + 4 * (s % 2) + w;
-      double mj[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) mj[j] = XT[j * F + i];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) M[s] = fma(-mj[j], X[j], M[s]);
+    if (flag[0] != 0.0) {                // uniform: back to G
+      __syncthreads();
+      for (int idx = tid; idx < f * f; idx += 256) {
+        const int i = idx / f, j = idx - i * f;
+        if ((i >> 4) == (j >> 4)) Gs[i * LD + j] = keep[256 * (i >> 4) + (i & 15) * 16 + (j & 15)];
+        else if (i < j) Gs[i * LD + j] = Gs[j * LD + i];
+      }
+      __syncthreads();
+      return false;
     }
+    // column b of R^{-1}: the accumulators hold the products' rows as the
+    // left operand wants them
+    if (w >= 1 && w <= b) {
+      const int i = w - 1;
+      typename MF::acc_t v = MF::zero();
 #pragma unroll
-    for (int s = 0; s + 2 < NR; ++s) M[s] = M[s + 2];
-    M[NR - 2] = 0.0;
-    M[NR - 1] = 0.0;
+      for (int s = 0; s < 4; ++s) v = MF::op(inv[s], Ri[(o + 4 * s + g) * LD + o + r], v);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) Ri[(16 * i + MF::row(g, e)) * LD + o + r] = -v[e];
+    }
+    // trailing blocks S_qt -= R_bq^T R_bt, b < q <= t < nb: the next diagonal
+    // block on wave 0, the others from wave 3 down
+    if (b + 1 < nb) {
+      const int n = (nb - b - 1) * (nb - b) / 2;
+      for (int tile = (4 - w) & 3; tile < n; tile += 4) {
+        int q = b + 1, t = tile;
+        while (t >= nb - q) {
+          t -= nb - q;
+          ++q;
+        }
+        t += q;
+        double* S = Gs + 16 * q * LD + 16 * t + r;
+        typename MF::acc_t acc;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = S[MF::row(g, e) * LD];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          acc = MF::op(-Gs[(o + 4 * k + g) * LD + 16 * q + r], Gs[(o + 4 * k + g) * LD + 16 * t + r], acc);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) S[MF::row(g, e) * LD] = acc[e];
+      }
+    }
+    __syncthreads();
   }
+  // zeros below the diagonal blocks of R, and past f
+  if (NB > 1)
+    for (int idx = tid; idx < 256 * NB * (NB - 1) / 2; idx += 256) {
+      const int t = idx >> 8, q = t < 1 ? 1 : (t < 3 ? 2 : 3);     // block (q, t - q (q - 1) / 2)
+      Gs[(16 * q + ((idx >> 4) & 15)) * LD + 16 * (t - q * (q - 1) / 2) + (idx & 15)] = 0.0;
+    }
+  if (f < F)
+    for (int idx = tid; idx < F * F; idx += 256) {
+      const int i = idx / F, j = idx - i * F;
+      if (i >= f || j >= f) {
+        Gs[i * LD + j] = 0.0;
+        Ri[i * LD + j] = 0.0;
+      }
+    }
   __syncthreads();
-  for (int idx = tid; idx < (F - f) * F; idx += 256) {   // padding rows / columns
-    const int a = f + idx / F, b = idx - (idx / F) * F;
-    Gs[a * LD + b] = 0.0;
-    Ri[b * LD + a] = 0.0;
+  return true;
+}
+
+// Cholesky with inverse of G: the blocked form, and every pivot rule
+// (chol_inv_general, which see for the arguments and the rules) only where a
+// column is dead on entry or a pivot fails the floor test.  G is symmetric,
+// both triangles filled.
+template <int F>
+__device__ __forceinline__ void chol_inv(double* Gs, double* Ri, double* work, double* dgs, int f,
+                                         uint64_t dmask_in, int first_pass, uint64_t* dmask_out, int* nfloor,
+                                         const double* dg_in = nullptr, uint64_t* nolive_out = nullptr) {
+  const uint64_t cols = f >= 64 ? ~0ull : (1ull << f) - 1;
+  if ((dmask_in & cols) == 0ull && chol_inv_blocked<F>(Gs, Ri, work, dgs, f, dg_in)) {
+    *dmask_out = dmask_in;
+    *nfloor = 0;
+    if (nolive_out) *nolive_out = 0ull;
+    return;
   }
-  __syncthreads();
-  return ok;
+  chol_inv_general<F>(Gs, Ri, work, dgs, f, dmask_in, first_pass, dmask_out, nfloor, dg_in, nolive_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -3080,8 +3175,7 @@ __device__ __forceinline__ void grid_barrier(uint32_t* ctr, uint32_t target, Sta
   __syncthreads();
 }
 
-// Arguments of k_cqr2.  Matrices R1, R2 and their inverses: f x f FP64,
-// element (i,j) at j*f + i, written by workgroup 0 when non-null.
+// Arguments of k_cqr2.
 struct Cqr2Args {
   const void* X;             // block: rows x f, element (i,c) at c*ldx + i (read only)
   int64_t ldx, rows;
@@ -3093,7 +3187,6 @@ struct Cqr2Args {
   int block_id;
   Gate gate;                 // closing steps enqueued ahead of the stop flag
   State* st;
-  double *R1, *R1inv, *R2, *R2inv;
   int32_t* dead;             // per-column dead flags: read on the first pass unless fresh, written at the end
   int fresh;
   int count_floors;          // add floored pivots to st->floored
@@ -3146,6 +3239,25 @@ __device__ __forceinline__ void state_send(const Cqr2Args& a) {
   const uint64_t* src = reinterpret_cast<const uint64_t*>(a.st);
   uint64_t* dst = reinterpret_cast<uint64_t*>(a.state_out);
   for (int i = 0; i < (int)(sizeof(State) / 8); ++i) dst[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Whether f u64 |D R^{-1}|_F^2 <= 2^-27 for R^{-1} (LDS, row-major, ld F + 1)
+// and the squares dg of D's entries (uniform; red: 4 doubles of LDS).
+template <int F>
+__device__ __forceinline__ bool chol_tame(const double* Ri, const double* dg, int f, double* red) {
+  constexpr int LD = SmallCfg<F>::LD;
+  double s = 0.0;
+#pragma unroll
+  for (int q = 0; q < F * F / 256; ++q) {
+    const int idx = threadIdx.x + 256 * q, i = idx / F, j = idx % F;
+    if (i <= j && j < f) s = fma(dg[i] * Ri[i * LD + j], Ri[i * LD + j], s);
+  }
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  s = ((red[0] + red[1]) + red[2]) + red[3];
+  __syncthreads();
+  return f * U64 * s <= 0x1p-27;
 }
 
 template <typename T, int F, bool PROJ = false>
@@ -3278,7 +3390,42 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
   unsigned bars = 0;                             // barriers passed (their arrival targets are multiples of G)
   const uint64_t wticks = a.wait_ticks ? a.wait_ticks : CQR2_WAIT_TICKS;
   const int wb = PROJ ? (int)*a.w_dev : 0;       // basis width (uniform; <= Cfg::WMAX by the host's bound)
-  for (int pass = 0; pass < 2; ++pass) {
+  // Stages 0 and 1: the CholeskyQR2 passes of the block; 2 and 3: those of
+  // R^T (closing).  One loop, so that one copy of the Cholesky serves all four
+  // and the later ones find it in the instruction cache: run once per launch
+  // each, three copies cost more in instruction fetches than they saved.
+  int kept = f;                                  // columns kept by the stop test
+  bool one_pass = false;                         // the block's second pass was not needed
+  double* B0 = lds;                              // closing: the panel's area
+  double* B1 = lds + S::SIZE;
+  double* B2 = lds + 2 * S::SIZE;
+  double* Qs = Gs;                               // closing: Qh
+  // U = Uq Qh at the end runs over this workgroup's rows in 16-row tiles,
+  // four per wave at a time; Uq (the basis, final before this launch) is
+  // read early for the first four, so their loads overlap the QR of R^T
+  const T* Uq = reinterpret_cast<const T*>(a.Uq);
+  const int64_t chunk = (((a.m_u + G - 1) / G + 15) / 16) * 16;
+  const int64_t u0 = (int64_t)blockIdx.x * chunk, u1 = min(a.m_u, u0 + chunk);
+  constexpr int NB = 4;
+  T xa[NB][KS];
+  auto load_u = [&](int64_t t0) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int64_t arow = t0 + 64 * b + r;
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) {
+        const int k = 4 * kk + g;
+        xa[b][kk] = (arow < u1 && k < f) ? Uq[(int64_t)k * a.ldq_u + arow] : (T)0;
+      }
+    }
+  };
+  T* Q = reinterpret_cast<T*>(a.Q);
+#pragma unroll 1
+  for (int stage = 0;;) {
+    double *Gc = Gs, *Rc = Ri;                   // this stage's Cholesky
+    uint64_t dmask_in = dmask;
+    if (stage < 2) {
+    const int pass = stage;
     __syncthreads();                             // panel (pass 1: Z1) complete
     if constexpr (PROJ) {
       if (wb > 0 && wb <= Cfg::WMAX) {
@@ -3421,7 +3568,7 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
       }
       __syncthreads();
     }
-    double sum[EPT];                             // G's upper triangle, kept for a second Cholesky
+    double sum[EPT];                             // G's upper triangle
     // one workgroup: its wave fold is the Gram (the same sums as the fold of
     // a single partial), no partial and no barrier.  Compiled into the
     // 16-column form only: the 32-column form's code sits near the size of
@@ -3520,45 +3667,84 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
         st->lp_scale = lp_scale_of(mx, lp_mode);
       }
     }
-    uint64_t dmask_in = dmask;
     if (pass == 0) dmask_in = __ballot(dead0 != 0);
-    __syncthreads();
-    int nfl = 0;
-    // the branch-free elimination first; the full pivot rules only when it
-    // meets a dead column or a pivot at or below the floor
-    const bool fast = dmask_in == 0ull && chol_inv_fast<F>(Gs, Ri, rowbuf, dgs, f);
-    if (!fast) {
-      if (dmask_in == 0ull) {                    // Gs was overwritten: G again from the registers
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-          if (tid + 256 * e < np) {
-            Gs[prr[e] * LD + pcc[e]] = sum[e];
-            Gs[pcc[e] * LD + prr[e]] = sum[e];
-          }
-        }
+    } else if (stage == 2) {                     // M M^T, M = R2 R1 (B0) or R1 (Gs)
+      if (!one_pass) {
+        lds_gemm<F, false, false>(Gs, R1s, [&](int i, int jj, double v) { B0[i * LD + jj] = v; });
         __syncthreads();
       }
-      [[clang::noinline]] chol_inv<F>(Gs, Ri, rowbuf, dgs, f, dmask_in, pass == 0, &dmask, &nfl);
-    } else {
-      dmask = 0ull;
+      const double* M = one_pass ? Gs : B0;
+      lds_gemm<F, false, true>(M, M, [&](int i, int jj, double v) { B1[i * LD + jj] = v; });
+      Gc = B1;
+      Rc = B2;
+      dmask_in = 0ull;
+    } else {                                     // Z^T Z (Z in Ri)
+      lds_gemm<F, true, false>(Ri, Ri, [&](int i, int jj, double v) { B0[i * LD + jj] = v; });
+      Gc = B0;
+      Rc = B2;
     }
-    if (lead) {
-      double* Ro = pass == 0 ? a.R1 : a.R2;
-      double* Rio = pass == 0 ? a.R1inv : a.R2inv;
-      for (int idx = tid; idx < ff; idx += 256) {
-        const int c = idx / f, rr = idx - c * f;  // element (rr, c) at c*f + rr
-        if (Ro) Ro[idx] = Gs[rr * LD + c];
-        if (Rio) Rio[idx] = Ri[rr * LD + c];
+    __syncthreads();
+    int nfl = 0;
+    chol_inv<F>(Gc, Rc, rowbuf, dgs, f, dmask_in, (stage & 1) == 0, &dmask, &nfl);
+    if (lead && a.count_floors && tid == 0 && nfl) atomicAdd(&st->floored, nfl);
+    // closing, FP32 data: a first pass that leaves its columns orthonormal to
+    // well below the data's rounding needs no second one.  Its loss of
+    // orthogonality is about f u64 |D R^{-1}|_F^2, D the column norms (the
+    // Gram's rounding seen through the inverse of the factor with unit
+    // columns; scaling the columns does not change it); 2^-27 is an eighth of
+    // an FP32 rounding.  FP64 data, whose own rounding that loss exceeds, and
+    // basis blocks, whose stop test needs the second factor, take both passes.
+    bool tame = false;
+    if (sizeof(T) == 4 && a.close_qr && (stage & 1) == 0 && dmask == 0ull && nfl == 0)
+      tame = chol_tame<F>(Rc, dgs, f, r1d);
+    if (stage < 2) {
+      if (stage == 0) one_pass = tame;
+      const bool last = stage == 1 || one_pass;
+      if (!last) {
+        if (tid < F) r1d[tid] = Gs[tid * LD + tid];
+        if (a.close_qr)
+          for (int idx = tid; idx < S::SIZE; idx += 256) R1s[idx] = Gs[idx];
+      } else {
+        if (lead && tid < f) a.dead[tid] = (int32_t)((dmask >> tid) & 1ull);
+        // stop test (Alg. 1) on wave 0 of every workgroup: first column whose
+        // |T(c,c)| <= eps
+        if (a.stop_test) {
+          if (wv == 0) {
+            const int j = lane;
+            const bool mine = j < f;
+            const double eps = a.norm_parts ? eps_l : eps_g;
+            const bool nonf = a.norm_parts ? nonf_l : (nonf_g != 0);
+            double d = 0.0;
+            bool hit = false;
+            if (mine) {
+              d = ((dmask >> j) & 1ull) ? 0.0 : Gs[j * LD + j] * r1d[j];
+              hit = ((d <= eps) && (!paired || ((a.col0 + j) & 1) == 0)) || nonf;
+            }
+            const unsigned long long mask = __ballot(hit);
+            const int kp = mask ? (int)__ffsll((long long)mask) - 1 : f;
+            if (lane == 0) sx[0] = kp;
+            if (lead) {
+              if (mine && j <= kp) a.diag_log[a.col0 + j] = d;
+              const double dk = __shfl(d, kp & 63);
+              if (j == 0) {
+                if (mask != 0ull) st->d_stop = dk;
+                const bool stop = (mask != 0ull) || (a.col0 + f >= a.n);
+                a.acc[a.block_id] = kp;
+                const int64_t wn = zoff + kp;
+                a.wlog[a.block_id + 1] = wn;
+                st->rank = wn;
+                if (stop) st->stop_block = a.block_id;
+              }
+            }
+          }
+          __syncthreads();
+          kept = sx[0];
+        }
+        if (a.close_qr && a.Uout) load_u(u0 + 16 * wv);
       }
-      if (a.count_floors && tid == 0 && nfl) atomicAdd(&st->floored, nfl);
-      if (pass == 1 && tid < f) a.dead[tid] = (int32_t)((dmask >> tid) & 1ull);
-    }
-    if (pass == 0) {
-      if (tid < F) r1d[tid] = Gs[tid * LD + tid];
-      if (a.close_qr)
-        for (int idx = tid; idx < S::SIZE; idx += 256) R1s[idx] = Gs[idx];
-      // Z1 = X R1^{-1} in place: wave wv takes 16-row tiles wv, wv + 4, ...
-      // (each tile's rows are read whole before they are written)
+      // X R^{-1}: Z1 in place of the panel, or after the last pass the kept
+      // columns of Q (wave wv takes 16-row tiles wv, wv + 4, ...; each tile's
+      // rows are read whole before they are written)
       for (int rt = wv; rt < RPW / 16; rt += 4) {
         double av[KS];
 #pragma unroll
@@ -3570,135 +3756,67 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
         for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
           for (int u = 0; u < TT; ++u) z[u] = MF::op(av[kk], Ri[(4 * kk + g) * LD + 16 * u + r], z[u]);
+        if (!last) {
 #pragma unroll
-        for (int u = 0; u < TT; ++u)
+          for (int u = 0; u < TT; ++u)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) pan[(16 * u + r) * LDX + 16 * rt + MF::row(g, e)] = (T)z[u][e];
-      }
-    }
-  }
-  // stop test (Alg. 1) on wave 0 of every workgroup: first column whose
-  // |T(c,c)| <= eps
-  int keep = f;
-  if (a.stop_test) {
-    if (wv == 0) {
-      const int j = lane;
-      const bool mine = j < f;
-      const double eps = a.norm_parts ? eps_l : eps_g;
-      const bool nonf = a.norm_parts ? nonf_l : (nonf_g != 0);
-      double d = 0.0;
-      bool hit = false;
-      if (mine) {
-        d = ((dmask >> j) & 1ull) ? 0.0 : Gs[j * LD + j] * r1d[j];
-        hit = ((d <= eps) && (!paired || ((a.col0 + j) & 1) == 0)) || nonf;
-      }
-      const unsigned long long mask = __ballot(hit);
-      const int kp = mask ? (int)__ffsll((long long)mask) - 1 : f;
-      if (lane == 0) sx[0] = kp;
-      if (lead) {
-        if (mine && j <= kp) a.diag_log[a.col0 + j] = d;
-        const double dk = __shfl(d, kp & 63);
-        if (j == 0) {
-          if (mask != 0ull) st->d_stop = dk;
-          const bool stop = (mask != 0ull) || (a.col0 + f >= a.n);
-          a.acc[a.block_id] = kp;
-          const int64_t wn = zoff + kp;
-          a.wlog[a.block_id + 1] = wn;
-          st->rank = wn;
-          if (stop) st->stop_block = a.block_id;
+            for (int e = 0; e < 4; ++e) pan[(16 * u + r) * LDX + 16 * rt + MF::row(g, e)] = (T)z[u][e];
+        } else {
+#pragma unroll
+          for (int u = 0; u < TT; ++u) {
+            const int col = 16 * u + r;
+            if (col >= kept) continue;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int64_t row = rb + 16 * rt + MF::row(g, e);
+              if (row < a.rows) Q[(zoff + col) * a.ldq + row] = (T)z[u][e];
+            }
+          }
         }
       }
-    }
-    __syncthreads();
-    keep = sx[0];
-  }
-  // Q = Z1 R2^{-1} for the kept columns (the apply's tile order and sums)
-  T* Q = reinterpret_cast<T*>(a.Q);
-  for (int rt = wv; rt < RPW / 16; rt += 4) {
-    double av[KS];
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) av[kk] = (double)pan[(4 * kk + g) * LDX + 16 * rt + r];
-    typename MF::acc_t z[TT];
-#pragma unroll
-    for (int u = 0; u < TT; ++u) z[u] = MF::zero();
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk)
-#pragma unroll
-      for (int u = 0; u < TT; ++u) z[u] = MF::op(av[kk], Ri[(4 * kk + g) * LD + 16 * u + r], z[u]);
-#pragma unroll
-    for (int u = 0; u < TT; ++u) {
-      const int col = 16 * u + r;
-      if (col >= keep) continue;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int64_t row = rb + 16 * rt + MF::row(g, e);
-        if (row < a.rows) Q[(zoff + col) * a.ldq + row] = (T)z[u][e];
+      if (!last) {
+        stage = 1;
+        continue;
       }
+      if (!a.close_qr) break;
+      __syncthreads();                           // the panel and R^{-1} are free
+      stage = 2;
+      continue;
     }
+    // closing: Z = M^T Rh1^{-1}, then Qh = Z or Z Rh2^{-1}; Rh = Rh1 or Rh2 Rh1
+    T* Dout = reinterpret_cast<T*>(a.Dout);
+    if (stage == 2) {
+      lds_gemm<F, true, false>(one_pass ? Gs : B0, B2, [&](int i, int jj, double v) {
+        Ri[i * LD + jj] = v;
+        if (tame && lead && i < f && jj < f) a.Qh_out[(int64_t)jj * f + i] = v;
+      });
+      __syncthreads();
+      if (!tame) {
+        stage = 3;
+        continue;
+      }
+      Qs = Ri;
+      if (lead)
+        for (int idx = tid; idx < F * F; idx += 256) {
+          const int i = idx / F, jj = idx - i * F;
+          if (i < f && jj < f) Dout[(int64_t)i * a.ldd + jj] = (T)B1[i * LD + jj];
+        }
+    } else {
+      lds_gemm<F, false, false>(Ri, B2, [&](int i, int jj, double v) {
+        Qs[i * LD + jj] = v;
+        if (lead && i < f && jj < f) a.Qh_out[(int64_t)jj * f + i] = v;
+      });
+      if (lead)
+        lds_gemm<F, false, false>(B0, B1, [&](int i, int jj, double v) {
+          if (i < f && jj < f) Dout[(int64_t)i * a.ldd + jj] = (T)v;
+        });
+    }
+    break;
   }
   if (a.reuse_counter && tid == 0) {            // every workgroup is past its last barrier: reset for the next launch
     if (atomicAdd(a.counter, 1u) == (bars + 1) * G - 1) atomicExch(a.counter, 0u);
   }
   if (!a.close_qr) return;
-  // U = Uq Qh at the end runs over this workgroup's rows in 16-row tiles,
-  // four per wave at a time; Uq (the basis, final before this launch) is
-  // read now for the first four, so their loads overlap the QR of R^T
-  const T* Uq = reinterpret_cast<const T*>(a.Uq);
-  const int64_t chunk = (((a.m_u + G - 1) / G + 15) / 16) * 16;
-  const int64_t u0 = (int64_t)blockIdx.x * chunk, u1 = min(a.m_u, u0 + chunk);
-  constexpr int NB = 4;
-  T xa[NB][KS];
-  auto load_u = [&](int64_t t0) {
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int64_t arow = t0 + 64 * b + r;
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk) {
-        const int k = 4 * kk + g;
-        xa[b][kk] = (arow < u1 && k < f) ? Uq[(int64_t)k * a.ldq_u + arow] : (T)0;
-      }
-    }
-  };
-  if (a.Uout) load_u(u0 + 16 * wv);
-  // closing QR (Alg. 2, QR(R^T)), redundantly on every workgroup
-  __syncthreads();                               // the panel and R2^{-1} are free
-  double* B0 = lds;
-  double* B1 = lds + S::SIZE;
-  double* B2 = lds + 2 * S::SIZE;
-  double* B3 = Ri;
-  double* Qs = Gs;                               // Qh (R2 is dead once M is formed)
-  lds_gemm<F, false, false>(Gs, R1s, [&](int i, int jj, double v) { B0[i * LD + jj] = v; });   // M = R2 R1
-  __syncthreads();
-  lds_gemm<F, false, true>(B0, B0, [&](int i, int jj, double v) { B1[i * LD + jj] = v; });     // M M^T
-  __syncthreads();
-  uint64_t dm1 = 0ull, dm2 = 0ull;
-  int nf1 = 0, nf2 = 0;
-  if (!chol_inv_fast<F>(B1, B2, rowbuf, dgs, f)) {
-    lds_gemm<F, false, true>(B0, B0, [&](int i, int jj, double v) { B1[i * LD + jj] = v; });
-    __syncthreads();
-    [[clang::noinline]] chol_inv<F>(B1, B2, rowbuf, dgs, f, 0ull, 1, &dm1, &nf1);                                 // Rh1, Rh1^{-1}
-  }
-  lds_gemm<F, true, false>(B0, B2, [&](int i, int jj, double v) { B3[i * LD + jj] = v; });     // Z = M^T Rh1^{-1}
-  __syncthreads();
-  lds_gemm<F, true, false>(B3, B3, [&](int i, int jj, double v) { B0[i * LD + jj] = v; });     // Z^T Z
-  __syncthreads();
-  if (!(dm1 == 0ull && chol_inv_fast<F>(B0, B2, rowbuf, dgs, f))) {
-    if (dm1 == 0ull) {
-      lds_gemm<F, true, false>(B3, B3, [&](int i, int jj, double v) { B0[i * LD + jj] = v; });
-      __syncthreads();
-    }
-    [[clang::noinline]] chol_inv<F>(B0, B2, rowbuf, dgs, f, dm1, 0, &dm2, &nf2);                                  // Rh2, Rh2^{-1}
-  }
-  lds_gemm<F, false, false>(B3, B2, [&](int i, int jj, double v) {                            // Qh = Z Rh2^{-1}
-    Qs[i * LD + jj] = v;
-    if (lead && i < f && jj < f) a.Qh_out[(int64_t)jj * f + i] = v;
-  });
-  T* Dout = reinterpret_cast<T*>(a.Dout);
-  if (lead)
-    lds_gemm<F, false, false>(B0, B1, [&](int i, int jj, double v) {                          // Rh = Rh2 Rh1
-      if (i < f && jj < f) Dout[(int64_t)i * a.ldd + jj] = (T)v;
-    });
-  if (lead && a.count_floors && tid == 0 && nf1 + nf2) atomicAdd(&st->floored, nf1 + nf2);
   state_send(a);                                 // the control block is final here
   if (!a.Uout) return;
   __syncthreads();                               // Qh complete

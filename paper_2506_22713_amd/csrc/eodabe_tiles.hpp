@@ -555,7 +555,7 @@ __device__ __forceinline__ void tile_update(float* Yb, int64_t ldy, const float*
 // template width F >= f; R overwrites G, R^{-1} goes to Ri (ld F+1).
 // The leading dimension used is F+1 for the chosen F; callers pass ldF.
 __device__ int chol_width(int f) { return f <= 16 ? 16 : (f <= 32 ? 32 : 64); }
-__device__ void tile_chol(double* Gs, double* Ri, double* work, double* dgs, int f, uint64_t dmask_in,
+__device__ __noinline__ void tile_chol(double* Gs, double* Ri, double* work, double* dgs, int f, uint64_t dmask_in,
                           int first_pass, uint64_t* dmask_out, int* nfl) {
   const int F = chol_width(f);
   if (F == 16) chol_inv<16>(Gs, Ri, work, dgs, f, dmask_in, first_pass, dmask_out, nfl);
