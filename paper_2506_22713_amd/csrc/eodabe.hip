@@ -304,7 +304,7 @@ WS carve(void* base, const Geo& g) {
   w.wpart = c.take<char>((int64_t)g.s_proj * ldw_of(g) * g.bn * e);
   w.w = c.take<char>(ldw_of(g) * g.bn * e);
   w.gpart = c.take<double>((int64_t)std::max(g.s_gram, GRAM_LOOP_WG) * g.bn * g.bn);
-  w.wfp = c.take<char>((int64_t)CQR2_GMAX * CQR2_PROJ_WMAX * 32 * e);   // W partials of the one-launch BCGS2
+  w.wfp = c.take<char>((int64_t)CQR2_GMAX * CQR2_PROJ_WMAX * std::min(g.bn, 32) * e);   // W partials of the one-launch BCGS2
   w.gsum = c.take<double>((int64_t)g.bn * g.bn);
   w.r1 = c.take<double>(g.bn * g.bn);
   w.r2 = c.take<double>(g.bn * g.bn);
@@ -319,9 +319,11 @@ WS carve(void* base, const Geo& g) {
   const int64_t rb = std::max<int64_t>(rc, g.bn);
   // Gram partials of the closing QRs: 64 of up to 128 x 128 (the K-split
   // partials of a Gram of at most 128 columns and their sum), or
-  // GRAM_SPLITS_WIDE + 1 of rb x rb (wider)
+  // GRAM_SPLITS_WIDE + 1 of rb x rb (wider), or those of the one-launch
+  // CholeskyQR2 (768 doubles a workgroup and pass)
   const int64_t rb128 = std::min<int64_t>(rb, 128);
-  w.gbig = c.take<double>(std::max<int64_t>(64 * rb128 * rb128, (GRAM_SPLITS_WIDE + 1) * rb * rb));
+  w.gbig = c.take<double>(std::max<int64_t>({64 * rb128 * rb128, (GRAM_SPLITS_WIDE + 1) * rb * rb,
+                                         2 * 768 * std::min<int64_t>(CQR2_GMAX, cdiv(g.nn, CQR2_RPW))}));
   w.rb1 = c.take<double>(rb * rb);
   w.rb2 = c.take<double>(rb * rb);
   w.rb3 = c.take<double>(rb * rb);
@@ -931,7 +933,6 @@ int run_basis(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const 
   T* q = (T*)w.q;
   T* wbuf = (T*)w.w;
   const int64_t ldw = ldw_of(g);
-  const int32_t* stopb = &w.st->stop_block;
   // blocks enqueued before each host check of the stop flag: 1, 2, 4, 4, ...
   // (speculative blocks after the stop return at once from every kernel)
   int per_sync = ctx->o.blocks_per_sync > 0 ? ctx->o.blocks_per_sync : 1;
@@ -956,6 +957,7 @@ int run_basis(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const 
       const int64_t kw = std::min<int64_t>({(int64_t)(WIDE_COLS / g.b), cdiv(pred_end - j * g.b, g.b), g.nblk - j});
       const int64_t col0 = j * g.b;
       const int fw = (int)std::min<int64_t>(kw * g.b, g.nn - col0);
+      const int32_t* stopb = &w.st->stop_block;
       const int bnw = (int)rup(fw, 16);
       T* omw = (T*)w.omega_w;
       dim3 grid((unsigned)cdiv(cdiv(g.ldk, 4), 256), bnw);
@@ -980,6 +982,8 @@ int run_basis(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const 
     }
     for (; j < jend; ++j) {
       const int blk = (int)j;
+      // block 0 cannot come after the stop: its kernels do not wait for the flag
+      const int32_t* stopb = j > 0 ? &w.st->stop_block : nullptr;
       const int64_t col0 = j * g.b;
       const int f = (int)std::min<int64_t>(g.b, g.nn - col0);
       const bool pre = j >= pre_j0 && j < pre_j1;
@@ -1347,6 +1351,7 @@ int close_small(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, cons
       a.Uout = Uout;
       a.ldu = ldu;
       a.m_u = g.mm;
+      a.u_chunk = rup(cdiv(g.mm, cdiv(g.nn, CQR2_RPW)), 16);
     }
     // the control block to host memory from the same kernel, once final (no
     // later launch of the chunk changes it): the host needs no copy
@@ -2082,7 +2087,8 @@ static int factor_impl(eodabe_ctx* ctx, const void* A, int64_t m, int64_t n, int
       const int64_t rb = std::min<int64_t>(g.nn, jend * (int64_t)g.b);
       bool sent = false;
       if (rb <= 0 || rb > 64) return 0;
-      TRY(close_small<T>(ctx, st, g, w, Ae, rb, Gate{w.st, g.r_cap}, &w.st->rank, (T*)Ut, m, (T*)Vt,
+      // the gate also bounds the rank by r_cap, which sizes the buffers
+      TRY(close_small<T>(ctx, st, g, w, Ae, std::min(rb, g.r_cap), Gate{w.st, g.r_cap}, &w.st->rank, (T*)Ut, m, (T*)Vt,
                          n, (T*)core, g.r_cap, SPEC_BLOCK, &sent));
       return sent ? 2 : 1;
     };

@@ -107,6 +107,11 @@ __device__ __forceinline__ double lp_scale_of(float maxabs, int lp_mode) {
   return ldexp(1.0, 14 - e);
 }
 
+// Keeps the loads above it ahead of the branches below it: a kernel's first
+// data loads then overlap the control words' round trip (about 1 us) instead
+// of waiting for the decision that those words carry.
+__device__ __forceinline__ void loads_first() { asm volatile("" ::: "memory"); }
+
 // Gate of closing-step kernels enqueued before the host has seen the stop
 // flag of the basis loop: they run only once the loop has stopped, ||A||_F
 // is finite and the rank r satisfies 0 < r <= r_cap; otherwise every such
@@ -129,8 +134,10 @@ __device__ __forceinline__ void wg_stores_done() {
 
 __device__ __forceinline__ bool gate_shut(const Gate& g) {
   if (!g.st) return false;
-  return g.st->stop_block == 0x7fffffff || g.st->nonfinite != 0 || g.st->rank <= 0 ||
-         g.st->rank > g.r_cap;
+  const int32_t stop = g.st->stop_block, nonfinite = g.st->nonfinite;   // all three in one round trip
+  const int64_t rank = g.st->rank;
+  loads_first();
+  return (stop == 0x7fffffff) | (nonfinite != 0) | (rank <= 0) | (rank > g.r_cap);
 }
 
 // ---------------------------------------------------------------------------
@@ -375,6 +382,15 @@ __device__ __forceinline__ V4<T> ld4(const T* p) {
     r.v[0] = a.x; r.v[1] = a.y; r.v[2] = b.x; r.v[3] = b.y;
   }
   return r;
+}
+template <typename T>
+__device__ __forceinline__ void st4(T* p, const V4<T>& v) {
+  if constexpr (sizeof(T) == 4) {
+    *reinterpret_cast<f32x4*>(p) = f32x4{v.v[0], v.v[1], v.v[2], v.v[3]};
+  } else {
+    reinterpret_cast<double2*>(p)[0] = double2{v.v[0], v.v[1]};
+    reinterpret_cast<double2*>(p)[1] = double2{v.v[2], v.v[3]};
+  }
 }
 template <typename T>
 __device__ __forceinline__ V4<T> ld4_masked(const T* p, int64_t k, int64_t kend) {
@@ -1148,8 +1164,9 @@ __global__ __launch_bounds__(256) void k_gemm_nn(
     int64_t part_stride, Gate gate, const int64_t* __restrict__ M_dev) {
   typedef Mfma<T> MF;
   constexpr int PF = NnCfg<T, RT>::PF;
-  if (gate_shut(gate)) return;
-  if (M_dev) M = *M_dev;                // row count known on the device only
+  // M: the host's bound of the row count; M_dev: the count itself, known on
+  // the device only.  Gate and count are read behind the first loads, whose
+  // addresses need the bound alone.
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r = lane & 15, g = lane >> 4;
   const int64_t j0 = ((int64_t)blockIdx.y * 4 + wv) * 64;
@@ -1165,6 +1182,11 @@ __global__ __launch_bounds__(256) void k_gemm_nn(
     const int64_t row = m0 + 16 * t + r;
     xp[t] = X + (row < M ? row : (M - 1)) * ldx + 4 * g;
   }
+  auto open = [&]() {
+    if (gate_shut(gate)) return false;
+    if (M_dev) M = *M_dev;
+    return m0 < M;
+  };
   typename MF::acc_t acc[RT][4];
 #pragma unroll
   for (int t = 0; t < RT; ++t)
@@ -1217,6 +1239,8 @@ __global__ __launch_bounds__(256) void k_gemm_nn(
     V4<T> ab[PF][RT], zb[PF][4];
 #pragma unroll
     for (int q = 0; q < PF; ++q) loadf(ab[q], zb[q], kb + 16 * min((int64_t)q, nfull - 1));
+    loads_first();
+    if (!open()) return;
     int64_t i = 0;
     for (; i + 2 * PF <= nfull; i += PF) {
 #pragma unroll
@@ -1243,6 +1267,7 @@ __global__ __launch_bounds__(256) void k_gemm_nn(
   } else {
     // a partial panel of a matrix whose width is not a multiple of 4 (or no
     // full step): one masked step at a time
+    if (!open()) return;
     for (int64_t k = kb; k < ke; k += 16) {
       V4<T> a1[RT], z1[4];
       load(a1, z1, k);
@@ -1449,9 +1474,8 @@ __global__ __launch_bounds__(128) void k_fold_parts(const T* __restrict__ parts,
                                                     const int32_t* __restrict__ stop_block, int block_id,
                                                     Gate gate) {
   static_assert(P >= 1 && P <= 16 && (P & (P - 1)) == 0, "P: power of two up to 16");
-  if (stop_block && *stop_block < block_id) return;
-  if (gate_shut(gate)) return;
   __shared__ T red[P > 1 ? 128 * 4 : 1];
+  auto shut = [&]() { return (stop_block && *stop_block < block_id) || gate_shut(gate); };
   const int p = threadIdx.x % P, grp = threadIdx.x / P;
   const int64_t i0 = ((int64_t)blockIdx.x * (128 / P) + grp) * 4;
   const bool live = i0 < count;
@@ -1461,19 +1485,28 @@ __global__ __launch_bounds__(128) void k_fold_parts(const T* __restrict__ parts,
   for (int e = 0; e < 4; ++e) acc.v[e] = (T)0;
   if (live && vec) {
     constexpr int NB = 16;
-    for (int s0 = p; s0 < nparts; s0 += NB * P) {
-      V4<T> v[NB];
+    V4<T> v[NB];
+    auto load = [&](int s0) {
 #pragma unroll
       for (int q = 0; q < NB; ++q) {
         const int sq = min(s0 + q * P, nparts - 1);  // clamped: the load stays unconditional
         v[q] = ld4(parts + (int64_t)sq * stride + i0);
       }
+    };
+    load(p);
+    loads_first();
+    if (shut()) return;
+    for (int s0 = p; s0 < nparts;) {
 #pragma unroll
       for (int q = 0; q < NB; ++q)
         if (s0 + q * P < nparts)
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc.v[e] += v[q].v[e];
+      s0 += NB * P;
+      if (s0 < nparts) load(s0);
     }
+  } else if (shut()) {
+    return;
   } else if (live) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
@@ -1754,8 +1787,8 @@ __device__ __forceinline__ void lds_gemm(const double* A, const double* B, Out o
 
 // ---------------------------------------------------------------------------
 // Cholesky with inverse, on the four waves of a workgroup, of a symmetric
-// positive semi-definite f x f matrix G (FP64, f <= F), with every pivot rule
-// (chol_inv below takes the common case): elimination over the augmented rows [G | I].  With G = L U (L unit lower, U = diag(alpha)
+// positive semi-definite f x f matrix G (FP64, f <= F), columns dead on entry
+// included (chol_inv below takes the common case): elimination over the augmented rows [G | I].  With G = L U (L unit lower, U = diag(alpha)
 // R) the elimination turns I into L^{-1} = diag(alpha) R^{-T}, so row k of
 // the right half divided by alpha_k is column k of R^{-1}.  Pivot rules:
 //   dead column (flag in dmask_in): R(k,k) = 1, row k and column k of R
@@ -2014,68 +2047,71 @@ __device__ __forceinline__ void chol16_rows(double (&D)[16], double (&M)[16]) {
 // Pivots K..15 of the elimination of a 16 x 16 block S, all in registers:
 // lane (g, r) holds rows 0..15 of column r of S in D (every row of 16 lanes
 // its own copy, upper part read) and of another column in M.  The rows are
-// scaled by the root of their pivot: D becomes R at and above the diagonal,
-// M the solution of R^T M' = M.  al: R(r, r), not a number where a pivot was
-// not positive and finite.  The multipliers come by DPP within the row of
-// lanes; a pivot's chain is broadcast, root, scale, one update, and the other
-// rows' updates fill its waits.
-template <int K = 0>
-__device__ __forceinline__ void chol16(double (&D)[16], double (&M)[16], int r, double& al) {
+// scaled by the root of their pivot: D becomes R above the diagonal, al its
+// diagonal, M the solution of R^T M' = M.  The multipliers come by DPP within
+// the row of lanes; a pivot's chain is broadcast, root, scale, one update, and
+// the other rows' updates fill its waits.
+// With RULES a pivot at or below lo (lane r's for pivot r) or not finite is
+// refused (bits nl): its row becomes zero and eliminates nothing; the
+// identity's columns (id) keep it, to be divided by the stand-in of its root.
+// Without, every pivot is taken as it is (the selects would lengthen the chain
+// by an eighth).
+template <bool RULES, int K = 0>
+__device__ __forceinline__ void chol16(double (&D)[16], double (&M)[16], int r, bool id, double lo, double& al,
+                                       uint32_t& nl) {
   if constexpr (K < 16) {
     const double p = row_bcast<K>(D[K]);
     // 1/sqrt(p): hardware estimate (2^-24) and one cubic step
     const double y0 = __builtin_amdgcn_rsq(p);
     const double e = fma(-(p * y0), y0, 1.0);
     const double y = fma(y0 * e, fma(e, 0.375, 0.5), y0);
-    D[K] *= y;
-    M[K] *= y;
+    if constexpr (RULES) {
+      const bool ok = p > row_bcast<K>(lo) && p < INFINITY;
+      const double d = D[K] * y, m = M[K] * y;
+      D[K] = ok ? d : 0.0;
+      M[K] = ok ? m : (id ? M[K] : 0.0);
+      nl |= ok ? 0u : 1u << K;
+    } else {
+      D[K] *= y;
+      M[K] *= y;
+    }
     al = r == K ? D[K] : al;
     chol16_rows<K, K + 1>(D, M);
-    chol16<K + 1>(D, M, r, al);
+    chol16<RULES, K + 1>(D, M, r, id, lo, al, nl);
   }
 }
 
 // ---------------------------------------------------------------------------
-// chol_inv for the common case (no dead column, every pivot above the
-// floor), blocked by 16.  Wave 0 factors a diagonal block in registers
-// (chol16) with the identity and the row panel's blocks in its lane groups,
-// so R_bb^{-1} and the panel of R come out of the same sweep; the other waves
-// meanwhile form the products that column b of R^{-1} needs,
+// chol_inv_general for matrices without a column that is dead on entry,
+// blocked by 16.  Wave 0 factors a diagonal block in registers (chol16) with
+// the identity and the row panel's blocks in its lane groups, so R_bb^{-1} and
+// the panel of R come out of the same sweep; the other waves meanwhile form
+// the products that column b of R^{-1} needs,
 //   (R^{-1})_ib = -(sum_{i <= k < b} (R^{-1})_ik R_kb) R_bb^{-1},
 // and the trailing update runs as FP64 MFMA tiles on all waves.  What bounds
-// it is the chain of pivots on wave 0 and the LDS round trips between its
-// blocks; chol_inv_general's eight-pivot panels, which every wave repeats
-// from LDS, take 4500 cycles per eight pivots.  Returns false (uniform) when a
-// pivot fails the test of the floor: G is then as on entry and the other
-// arrays are void.  Rows and columns past f are padded by the identity.
-// Arguments as chol_inv_general.
+// it is the chain of pivots on wave 0 (2500 cycles a block) and the LDS round
+// trips between its blocks: about 11000 cycles at F = 32, 23000 at F = 64,
+// where chol_inv_general's eight-pivot panels, which every wave repeats from
+// LDS, take 18400 and 64400.  Rows and columns past f are padded by the
+// identity.  Arguments and rules as chol_inv_general.
 // ---------------------------------------------------------------------------
 template <int F>
-__device__ __forceinline__ bool chol_inv_blocked(double* Gs, double* Ri, double* work, double* dgs, int f,
-                                                 const double* dg_in) {
+__device__ __forceinline__ void chol_inv_blocked(double* Gs, double* Ri, double* work, double* dgs, int f,
+                                                 int first_pass, uint64_t* nolive, const double* dg_in) {
   typedef Mfma<double> MF;
   constexpr int LD = SmallCfg<F>::LD, NB = F / 16;
   static_assert(F == 16 || F == 32 || F == 64, "blocks of 16, at most four");
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nb = (f + 15) / 16;
-  double* flag = work;
+  uint32_t* refused = reinterpret_cast<uint32_t*>(work);   // per block
   double* dump = work + 8;               // where lanes without a column store
-  double* keep = work + 8 + 64;          // the diagonal blocks of G, for the way back
-  static_assert(8 + 64 + 256 * NB <= 24 * F, "work area");
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {         // thread (i, j) of every diagonal block
-    const int i = 16 * b + (tid >> 4), j = 16 * b + (tid & 15);
-    const bool in = i < f && j < f;
-    const double v = Gs[i * LD + j];
-    keep[256 * b + tid] = v;
-    if (!in) Gs[i * LD + j] = i == j ? 1.0 : 0.0;
-    if (i == j) dgs[i] = in ? (dg_in ? dg_in[i] : v) : 1.0;
-  }
-  if (f < 16 * nb && f > 16)             // the last block's columns right of the others
-    for (int idx = tid; idx < 16 * (nb - 1) * 16; idx += 256) {
+  if (tid < F) dgs[tid] = tid < f ? (dg_in ? dg_in[tid] : Gs[tid * LD + tid]) : 1.0;
+  if (f < 16 * nb)                       // the last block's rows and columns past f
+    for (int idx = tid; idx < 16 * nb * 16; idx += 256) {
       const int i = idx >> 4, j = 16 * (nb - 1) + (idx & 15);
-      if (j >= f) Gs[i * LD + j] = 0.0;
+      if (j >= f) Gs[i * LD + j] = i == j ? 1.0 : 0.0;
+      else if (i >= f) Gs[i * LD + j] = 0.0;
     }
   __syncthreads();
 #pragma unroll 1
@@ -2088,20 +2124,35 @@ __device__ __forceinline__ bool chol_inv_blocked(double* Gs, double* Ri, double*
       double* src = Gs + o * LD + o + r;
       double* col = act ? src + 16 * g : src;
       double D[16], M[16], al = 0.0;
+      auto load = [&]() {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        D[i] = src[i * LD];
-        M[i] = col[i * LD];
+        for (int i = 0; i < 16; ++i) {
+          D[i] = src[i * LD];
+          M[i] = col[i * LD];
+        }
+        if (g == 0)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) M[i] = i == r ? 1.0 : 0.0;
+      };
+      load();
+      const double flo = FLOOR_C * U64 * dgs[o + r], lo = flo > PIV_MIN ? flo : PIV_MIN;
+      uint32_t nl = 0;
+      chol16<false>(D, M, r, g == 0, lo, al, nl);
+      if (__any(!(al * al > lo && al * al < INFINITY))) {
+        // a pivot to refuse: the block again (not yet stored), by the rules,
+        // with the stand-ins: the root of the floor, or 1 on a second pass
+        load();
+        chol16<true>(D, M, r, g == 0, lo, al, nl);
+        const double a = first_pass ? sqrt(flo > 1e-300 ? flo : 1e-300) : 1.0;
+        const double ia = 1.0 / a;
+        if ((nl >> r) & 1u) al = a;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const double y = __shfl(ia, i);
+          if (g == 0 && ((nl >> i) & 1u)) M[i] *= y;
+        }
       }
-      if (g == 0)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) M[i] = i == r ? 1.0 : 0.0;
-      const double flo = FLOOR_C * U64 * dgs[o + r];
-      chol16(D, M, r, al);
-      const double p = al * al;
-      const bool bad = !(p > flo && p > PIV_MIN && p < INFINITY);
-      const unsigned long long fail = __ballot(bad);
-      if (lane == 0) flag[0] = fail != 0ull ? 1.0 : 0.0;
+      if (lane == 0) refused[b] = nl;
       // R_bb^{-1} from the identity's lanes (row r, so along the columns),
       // the panel's blocks down theirs; R_bb by the lanes of group 3, in the
       // same stores unless they hold block b+3
@@ -2110,35 +2161,28 @@ __device__ __forceinline__ bool chol_inv_blocked(double* Gs, double* Ri, double*
       const int stride = g == 0 ? 1 : (act || own ? LD : 0);
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const double d = i <= r ? D[i] : 0.0;
+        const double d = i < r ? D[i] : (i == r ? al : 0.0);
         dst[i * stride] = own ? d : M[i];
       }
       if (NB == 4 && b + 3 < nb && g == 3)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) src[i * LD] = i <= r ? D[i] : 0.0;
+        for (int i = 0; i < 16; ++i) src[i * LD] = i < r ? D[i] : (i == r ? al : 0.0);
     } else if (w <= b) {
       const int i = w - 1;
       for (int k = i; k < b; ++k)
 #pragma unroll
         for (int s = 0; s < 4; ++s)
           inv = MF::op(Gs[(16 * k + 4 * s + g) * LD + o + r], Ri[(16 * i + r) * LD + 16 * k + 4 * s + g], inv);
-    } else if (NB > 1 && b == 0) {       // zeros below the diagonal blocks of R^{-1}
+    } else if (NB > 1 && b == 0) {       // zeros below the diagonal blocks
       for (int idx = tid - 64; idx < F * F; idx += 192) {
         const int i = idx / F, j = idx - i * F;
-        if ((i >> 4) > (j >> 4)) Ri[i * LD + j] = 0.0;
+        if ((i >> 4) > (j >> 4)) {
+          Ri[i * LD + j] = 0.0;
+          Gs[i * LD + j] = 0.0;
+        }
       }
     }
     __syncthreads();
-    if (flag[0] != 0.0) {                // uniform: back to G
-      __syncthreads();
-      for (int idx = tid; idx < f * f; idx += 256) {
-        const int i = idx / f, j = idx - i * f;
-        if ((i >> 4) == (j >> 4)) Gs[i * LD + j] = keep[256 * (i >> 4) + (i & 15) * 16 + (j & 15)];
-        else if (i < j) Gs[i * LD + j] = Gs[j * LD + i];
-      }
-      __syncthreads();
-      return false;
-    }
     // column b of R^{-1}: the accumulators hold the products' rows as the
     // left operand wants them
     if (w >= 1 && w <= b) {
@@ -2173,13 +2217,7 @@ __device__ __forceinline__ bool chol_inv_blocked(double* Gs, double* Ri, double*
     }
     __syncthreads();
   }
-  // zeros below the diagonal blocks of R, and past f
-  if (NB > 1)
-    for (int idx = tid; idx < 256 * NB * (NB - 1) / 2; idx += 256) {
-      const int t = idx >> 8, q = t < 1 ? 1 : (t < 3 ? 2 : 3);     // block (q, t - q (q - 1) / 2)
-      Gs[(16 * q + ((idx >> 4) & 15)) * LD + 16 * (t - q * (q - 1) / 2) + (idx & 15)] = 0.0;
-    }
-  if (f < F)
+  if (f < F) {                           // zeros past f
     for (int idx = tid; idx < F * F; idx += 256) {
       const int i = idx / F, j = idx - i * F;
       if (i >= f || j >= f) {
@@ -2187,23 +2225,27 @@ __device__ __forceinline__ bool chol_inv_blocked(double* Gs, double* Ri, double*
         Ri[i * LD + j] = 0.0;
       }
     }
-  __syncthreads();
-  return true;
+    __syncthreads();
+  }
+  uint64_t nl = 0;
+  for (int b = 0; b < nb; ++b) nl |= (uint64_t)refused[b] << (16 * b);
+  *nolive = nl;
 }
 
-// Cholesky with inverse of G: the blocked form, and every pivot rule
-// (chol_inv_general, which see for the arguments and the rules) only where a
-// column is dead on entry or a pivot fails the floor test.  G is symmetric,
-// both triangles filled.
+// Cholesky with inverse of G (both triangles filled): the blocked form, or
+// chol_inv_general, which see for the arguments and the rules, where a column
+// is dead on entry.
 template <int F>
 __device__ __forceinline__ void chol_inv(double* Gs, double* Ri, double* work, double* dgs, int f,
                                          uint64_t dmask_in, int first_pass, uint64_t* dmask_out, int* nfloor,
                                          const double* dg_in = nullptr, uint64_t* nolive_out = nullptr) {
   const uint64_t cols = f >= 64 ? ~0ull : (1ull << f) - 1;
-  if ((dmask_in & cols) == 0ull && chol_inv_blocked<F>(Gs, Ri, work, dgs, f, dg_in)) {
-    *dmask_out = dmask_in;
-    *nfloor = 0;
-    if (nolive_out) *nolive_out = 0ull;
+  if ((dmask_in & cols) == 0ull) {
+    uint64_t nl;
+    chol_inv_blocked<F>(Gs, Ri, work, dgs, f, first_pass, &nl, dg_in);
+    *dmask_out = first_pass ? dmask_in : dmask_in | nl;
+    *nfloor = first_pass ? __popcll(nl) : 0;
+    if (nolive_out) *nolive_out = nl;
     return;
   }
   chol_inv_general<F>(Gs, Ri, work, dgs, f, dmask_in, first_pass, dmask_out, nfloor, dg_in, nolive_out);
@@ -3181,7 +3223,7 @@ struct Cqr2Args {
   int64_t ldx, rows;
   int f;
   const int64_t* f_dev;      // non-null: f read on the device (<= the template width)
-  double* parts;             // 2 * gridDim.x * f * f doubles: the partial Grams of both passes
+  double* parts;             // 2 * gridDim.x * 768 doubles (256 up to 16 columns): the partial Grams of both passes
   uint32_t* counter;         // barrier counter, zero at launch
   const int32_t* stop_block; // non-null: return at once for a block after the stop
   int block_id;
@@ -3213,6 +3255,7 @@ struct Cqr2Args {
   int64_t ldq_u;
   void* Uout;
   int64_t ldu, m_u;
+  int64_t u_chunk;           // rows of U per workgroup (a multiple of 16)
   State* state_out;          // non-null (host-mapped): workgroup 0 copies the control block there
                              // once it is final, whether the gate let the closing run or not
   // block Gram-Schmidt against the basis before each pass (the PROJ form):
@@ -3268,7 +3311,8 @@ struct Cqr2Cfg {
   static constexpr int WD = PROJ ? (WMAX * LDW * (int)sizeof(T) + 7) / 8 : 0;
   static constexpr int LDX = CQR2_RPW + 16 / (int)sizeof(T);      // panel column stride (T elements)
   static constexpr int XD = (F * LDX * (int)sizeof(T) + 7) / 8;    // panel, in doubles
-  static constexpr int RED = (F / 16) * (F / 16) * 256;             // wave fold of a partial Gram
+  static constexpr int NT = (F / 16) * (F / 16 + 1) / 2;            // 16 x 16 tiles of G on or above the diagonal
+  static constexpr int RED = 4 * NT * 256;                          // a partial Gram per wave
   static constexpr int CH = 2 * S::SIZE + 24 * F + F;               // G/R, R^{-1}, elimination rows, diagonal
   static constexpr int WORK = RED > CH ? RED : CH;
   static constexpr int TOTAL = XD + WORK + F + 8 + S::SIZE + WD;    // + R1's diagonal + scalars + R1 + W
@@ -3309,13 +3353,8 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
   constexpr int TT = F / 16, RPW = CQR2_RPW, LDX = Cfg::LDX, LD = S::LD, PW = RPW / 4, KS = F / 4;
   static_assert(F <= 32, "register budget of the Gram tiles");
   static_assert(Cfg::TOTAL * 8 <= 160 * 1024, "LDS budget");
-  // early exits read state written by earlier launches only: the same for every workgroup
-  if (a.stop_block && *a.stop_block < a.block_id) return;
-  const int f = a.f_dev ? (int)*a.f_dev : a.f;
-  if (gate_shut(a.gate) || f <= 0 || f > F) {
-    state_send(a);
-    return;
-  }
+  // the early exits below read state written by earlier launches only: the
+  // same for every workgroup
   __shared__ __align__(16) double lds[Cfg::TOTAL];
   T* pan = reinterpret_cast<T*>(lds);            // pan[c*LDX + row]
   double* Gs = lds + Cfg::XD;                    // G, then R
@@ -3331,19 +3370,22 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
   const T* X = reinterpret_cast<const T*>(a.X);
   const int64_t rb = (int64_t)blockIdx.x * RPW;
   const unsigned G = gridDim.x;
-  const int ff = f * f;
   const bool lead = blockIdx.x == 0;
   State* st = a.st;
+  // everything read from earlier launches is requested now, in one round
+  // trip: ahead of the barriers (after them the caches are invalidated and
+  // each read would be one on the critical path) and of the early exits
+  const int32_t stopped = a.stop_block ? *a.stop_block : 0x7fffffff;
+  const int64_t f_now = a.f_dev ? *a.f_dev : a.f;
+  const int32_t gate_stop = st->stop_block;
+  const int64_t gate_rank = st->rank;
   const int64_t zoff = (a.stop_test && a.wlog) ? a.wlog[a.block_id] : 0;
-  // everything read from earlier launches is requested now, ahead of the
-  // barriers (after them the caches are invalidated and each read would be
-  // a round trip on the critical path)
   const int paired = st->paired;
   const double tol = st->tol;
   const int lp_mode = st->lp_mode;
   const double eps_g = st->eps;
   const int nonf_g = st->nonfinite;
-  const int dead0 = (lane < f && !a.fresh) ? a.dead[lane] : 0;
+  const int dead_in = (lane < a.f && !a.fresh) ? a.dead[lane] : 0;
   double pv0[8];
   float mv0[8];
 #pragma unroll
@@ -3353,37 +3395,37 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
     pv0[q] = in ? a.norm_parts[i] : 0.0;
     mv0[q] = (in && a.max_parts) ? a.max_parts[i] : 0.0f;
   }
-  {                                              // stage the panel (zero outside rows x f), all loads in flight
-    constexpr int NIT = F * RPW / 256;
-    T xv[NIT];
+  // stage the panel: wave wv takes columns wv, wv + 4, ..., a lane four rows.
+  // Loads past rows or a.f (which bounds f) are clamped, not skipped (no
+  // branch between loads; a column's padding up to a multiple of 4 rows is
+  // inside the buffer), and zeroed when they are stored.
+  constexpr int NIT = F / 4;
+  V4<T> xv[NIT];
+  const int64_t xrow = min(rb + 4 * lane, (a.rows - 1) / 4 * 4);
 #pragma unroll
-    for (int q = 0; q < NIT; ++q) {
-      const int idx = tid + 256 * q;
-      const int c = idx / RPW, rl = idx - c * RPW;
-      const int64_t row = rb + rl;
-      xv[q] = (c < f && row < a.rows) ? X[(int64_t)c * a.ldx + row] : (T)0;
-    }
-#pragma unroll
-    for (int q = 0; q < NIT; ++q) {
-      const int idx = tid + 256 * q;
-      const int c = idx / RPW, rl = idx - c * RPW;
-      pan[c * LDX + rl] = xv[q];
-    }
+  for (int q = 0; q < NIT; ++q) xv[q] = ld4(X + (int64_t)min(wv + 4 * q, a.f - 1) * a.ldx + xrow);
+  loads_first();
+  if (stopped < a.block_id) return;
+  const bool shut = a.gate.st && (gate_stop == 0x7fffffff || nonf_g != 0 || gate_rank <= 0 || gate_rank > a.gate.r_cap);
+  if (shut || f_now <= 0 || f_now > a.f || f_now > F) {
+    state_send(a);
+    return;
   }
-  // this thread's elements of the packed upper triangle of G: p = tid + 256 e
-  // is (prr, pcc) with p = pcc (pcc + 1) / 2 + prr, prr <= pcc
-  constexpr int EPT = (F * (F + 1) / 2 + 255) / 256;
-  const int np = f * (f + 1) / 2;
-  int prr[EPT], pcc[EPT];
+  const int f = (int)f_now;
+  const int dead0 = lane < f ? dead_in : 0;
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const int p = tid + 256 * e;
-    int c = (int)((sqrtf(8.0f * (float)p + 1.0f) - 1.0f) * 0.5f);
-    while (c > 0 && c * (c + 1) / 2 > p) --c;
-    while ((c + 1) * (c + 2) / 2 <= p) ++c;
-    pcc[e] = c;
-    prr[e] = p - c * (c + 1) / 2;
+  for (int q = 0; q < NIT; ++q) {
+    const int c = wv + 4 * q;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (c >= f || rb + 4 * lane + e >= a.rows) xv[q].v[e] = (T)0;
+    st4(pan + c * LDX + 4 * lane, xv[q]);
   }
+  // A Gram travels as its tiles on or above the diagonal, each as the MFMA
+  // leaves it: element e of lane l of tile q at 256 q + 64 e + l.  This thread
+  // folds element tid of every tile: (prr + 16 t, pcc + 16 u) of tile (t, u).
+  constexpr int NT = Cfg::NT;
+  const int prr = MF::row(g, wv), pcc = r;
   uint64_t dmask = 0;
   double eps_l = 0.0;
   bool nonf_l = false;
@@ -3404,8 +3446,7 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
   // four per wave at a time; Uq (the basis, final before this launch) is
   // read early for the first four, so their loads overlap the QR of R^T
   const T* Uq = reinterpret_cast<const T*>(a.Uq);
-  const int64_t chunk = (((a.m_u + G - 1) / G + 15) / 16) * 16;
-  const int64_t u0 = (int64_t)blockIdx.x * chunk, u1 = min(a.m_u, u0 + chunk);
+  const int64_t u0 = (int64_t)blockIdx.x * a.u_chunk, u1 = min(a.m_u, u0 + a.u_chunk);
   constexpr int NB = 4;
   T xa[NB][KS];
   auto load_u = [&](int64_t t0) {
@@ -3415,11 +3456,28 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
         const int k = 4 * kk + g;
-        xa[b][kk] = (arow < u1 && k < f) ? Uq[(int64_t)k * a.ldq_u + arow] : (T)0;
+        xa[b][kk] = Uq[(int64_t)min(k, f - 1) * a.ldq_u + min(arow, a.m_u - 1)];   // clamped: no branch between loads
       }
     }
   };
   T* Q = reinterpret_cast<T*>(a.Q);
+  // columns 0 .. nc-1 of the panel to rows r0 .. (below r1) of out, whole
+  // columns at a time: a lane's MFMA results are single rows of 16 columns,
+  // which as stores would be 16-byte pieces
+  auto panel_out = [&](T* out, int64_t ldo, int nc, int64_t r0, int64_t r1) {
+    const int64_t row = r0 + 4 * lane;
+    const bool vec = row + 3 < r1 && (((uintptr_t)out | (uintptr_t)(ldo * sizeof(T))) & 15) == 0;
+    for (int c = wv; c < nc; c += 4) {
+      const V4<T> v = ld4(pan + c * LDX + 4 * lane);
+      if (vec) {
+        st4(out + (int64_t)c * ldo + row, v);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (row + e < r1) out[(int64_t)c * ldo + row + e] = v.v[e];
+      }
+    }
+  };
 #pragma unroll 1
   for (int stage = 0;;) {
     double *Gc = Gs, *Rc = Ri;                   // this stage's Cholesky
@@ -3554,82 +3612,63 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
 #pragma unroll
           for (int u = t; u < TT; ++u) acc[t][u] = MF::op(av[t].v[v], av[u].v[v], acc[t][u]);
     }
-    for (int w = 0; w < 4; ++w) {                // fold the 4 waves (fixed order)
-      if (wv == w) {
+    {
+      int q = 0;
 #pragma unroll
-        for (int t = 0; t < TT; ++t)
+      for (int t = 0; t < TT; ++t)
 #pragma unroll
-          for (int u = t; u < TT; ++u)
+        for (int u = t; u < TT; ++u, ++q)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              double* qq = &red[((t * TT + u) * 4 + e) * 64 + lane];
-              *qq = (w == 0) ? acc[t][u][e] : *qq + acc[t][u][e];
-            }
-      }
-      __syncthreads();
+          for (int e = 0; e < 4; ++e) red[(wv * NT + q) * 256 + e * 64 + lane] = acc[t][u][e];
     }
-    double sum[EPT];                             // G's upper triangle
-    // one workgroup: its wave fold is the Gram (the same sums as the fold of
-    // a single partial), no partial and no barrier.  Compiled into the
-    // 16-column form only: the 32-column form's code sits near the size of
-    // the instruction cache, and the branch alone slowed it measurably.
+    __syncthreads();
+    double sum[NT];
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {               // the 4 waves in order
+      sum[q] = red[q * 256 + tid];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) sum[q] += red[(w * NT + q) * 256 + tid];
+    }
+    // one workgroup: its wave fold is the Gram, no partial and no barrier
+    // (in the 16-column form; the 32-column form's code sits near the size of
+    // the instruction cache, and the branch alone slowed it measurably)
     bool one = false;
     if constexpr (!PROJ && F <= 16) one = G == 1;
-    if (one) {
+    if (!one) {
+      double* pp = a.parts + (int64_t)pass * G * (NT * 256);
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        sum[e] = 0.0;
-        if (tid + 256 * e < np) {
-          const int i = prr[e], jj = pcc[e], il = i & 15;
-          sum[e] += red[(((i >> 4) * TT + (jj >> 4)) * 4 + (il >> 2)) * 64 + (il & 3) * 16 + (jj & 15)];
-        }
-      }
-      __syncthreads();                           // the fold area (Gs) read before Gs is written
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        if (tid + 256 * e < np) {
-          Gs[prr[e] * LD + pcc[e]] = sum[e];
-          Gs[pcc[e] * LD + prr[e]] = sum[e];
-        }
-      }
-    } else {
-      // partials hold G's upper triangle packed column by column: (i, j), i <= j, at j(j+1)/2 + i
-      double* pp = a.parts + (int64_t)pass * G * ff;
-      double* Pw = pp + (int64_t)blockIdx.x * np;  // this workgroup's partial
-      for (int idx = tid; idx < TT * TT * 256; idx += 256) {
-        const int l = idx & 63, e = (idx >> 6) & 3, tu = idx >> 8;
-        const int t = tu / TT, u = tu - t * TT;
-        if (u < t) continue;
-        const int i = 16 * t + MF::row(l >> 4, e), jj = 16 * u + (l & 15);
-        if (i <= jj && jj < f) Pw[jj * (jj + 1) / 2 + i] = red[idx];
-      }
+      for (int q = 0; q < NT; ++q) pp[((int64_t)blockIdx.x * NT + q) * 256 + tid] = sum[q];
       grid_barrier(a.counter, (++bars) * G + a.wait_extra, st, wticks);
-      {                                            // all partials, order b = 0, 1, ...
-        constexpr int PB = 16;
+      // all partials, order b = 0, 1, ...
+      constexpr int PB = 16;
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) sum[e] = 0.0;
-        for (unsigned b = 0; b < G; b += PB) {
-          double v[EPT][PB];
+      for (int q = 0; q < NT; ++q) sum[q] = 0.0;
+      for (unsigned b = 0; b < G; b += PB) {
+        double v[NT][PB];
 #pragma unroll
-          for (int e = 0; e < EPT; ++e) {
-            const int idx = tid + 256 * e;
-            const bool ok = idx < np;
+        for (int q = 0; q < NT; ++q)
 #pragma unroll
-            for (int q = 0; q < PB; ++q) v[e][q] = (ok && b + q < G) ? pp[(int64_t)(b + q) * np + idx] : 0.0;
-          }
+          for (int k = 0; k < PB; ++k)           // clamped: the loads stay unconditional
+            v[q][k] = pp[((int64_t)min(b + k, G - 1) * NT + q) * 256 + tid];
 #pragma unroll
-          for (int e = 0; e < EPT; ++e)
+        for (int q = 0; q < NT; ++q)
 #pragma unroll
-            for (int q = 0; q < PB; ++q) sum[e] += v[e][q];
-        }
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-          if (tid + 256 * e < np) {
-            Gs[prr[e] * LD + pcc[e]] = sum[e];
-            Gs[pcc[e] * LD + prr[e]] = sum[e];
-          }
-        }
+          for (int k = 0; k < PB; ++k)
+            if (b + k < G) sum[q] += v[q][k];
       }
+    }
+    __syncthreads();                             // the fold area (Gs) read before Gs is written
+    {
+      int q = 0;
+#pragma unroll
+      for (int t = 0; t < TT; ++t)
+#pragma unroll
+        for (int u = t; u < TT; ++u, ++q) {
+          const int i = 16 * t + prr, jj = 16 * u + pcc;
+          const bool up = i <= jj;               // a diagonal tile's lower half mirrors its upper one
+          if (up) Gs[i * LD + jj] = sum[q];
+          if (up) Gs[jj * LD + i] = sum[q];
+        }
     }
     if (pass == 0 && a.norm_parts && wv == 0) {  // ||A||_F from the sketch partials (fixed order)
       double s = 0.0;
@@ -3740,11 +3779,14 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
           __syncthreads();
           kept = sx[0];
         }
-        if (a.close_qr && a.Uout) load_u(u0 + 16 * wv);
+        if (a.close_qr && a.Uout) {
+          load_u(u0 + 16 * wv);
+          loads_first();                         // not moved down to their use
+        }
       }
-      // X R^{-1}: Z1 in place of the panel, or after the last pass the kept
-      // columns of Q (wave wv takes 16-row tiles wv, wv + 4, ...; each tile's
-      // rows are read whole before they are written)
+      // X R^{-1} in place of the panel: Z1, or after the last pass Q (wave wv
+      // takes 16-row tiles wv, wv + 4, ...; each tile's rows are read whole
+      // before they are written)
       for (int rt = wv; rt < RPW / 16; rt += 4) {
         double av[KS];
 #pragma unroll
@@ -3756,28 +3798,17 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
         for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
           for (int u = 0; u < TT; ++u) z[u] = MF::op(av[kk], Ri[(4 * kk + g) * LD + 16 * u + r], z[u]);
-        if (!last) {
 #pragma unroll
-          for (int u = 0; u < TT; ++u)
+        for (int u = 0; u < TT; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) pan[(16 * u + r) * LDX + 16 * rt + MF::row(g, e)] = (T)z[u][e];
-        } else {
-#pragma unroll
-          for (int u = 0; u < TT; ++u) {
-            const int col = 16 * u + r;
-            if (col >= kept) continue;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int64_t row = rb + 16 * rt + MF::row(g, e);
-              if (row < a.rows) Q[(zoff + col) * a.ldq + row] = (T)z[u][e];
-            }
-          }
-        }
+          for (int e = 0; e < 4; ++e) pan[(16 * u + r) * LDX + 16 * rt + MF::row(g, e)] = (T)z[u][e];
       }
       if (!last) {
         stage = 1;
         continue;
       }
+      __syncthreads();
+      panel_out(Q + zoff * a.ldq, a.ldq, kept, rb, a.rows);
       if (!a.close_qr) break;
       __syncthreads();                           // the panel and R^{-1} are free
       stage = 2;
@@ -3820,10 +3851,11 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
   state_send(a);                                 // the control block is final here
   if (!a.Uout) return;
   __syncthreads();                               // Qh complete
-  // U = Uq Qh (the apply's operand order and sums)
+  // U = Uq Qh (the apply's operand order and sums), 256 rows at a time
+  // through the panel
   T* U = reinterpret_cast<T*>(a.Uout);
-  for (int64_t t0 = u0 + 16 * wv; t0 < u1; t0 += 64 * NB) {
-    if (t0 != u0 + 16 * wv) load_u(t0);
+  for (int64_t t0 = u0; t0 < u1; t0 += 64 * NB) {
+    if (t0 != u0) load_u(t0 + 16 * wv);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       typename MF::acc_t z[TT];
@@ -3832,18 +3864,16 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
-        for (int u = 0; u < TT; ++u) z[u] = MF::op((double)xa[b][kk], Qs[(4 * kk + g) * LD + 16 * u + r], z[u]);
+        for (int u = 0; u < TT; ++u)
+          z[u] = MF::op(4 * kk + g < f ? (double)xa[b][kk] : 0.0, Qs[(4 * kk + g) * LD + 16 * u + r], z[u]);
 #pragma unroll
-      for (int u = 0; u < TT; ++u) {
-        const int col = 16 * u + r;
-        if (col >= f) continue;
+      for (int u = 0; u < TT; ++u)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int64_t row = t0 + 64 * b + MF::row(g, e);
-          if (row < u1) U[col * a.ldu + row] = (T)z[u][e];
-        }
-      }
+        for (int e = 0; e < 4; ++e) pan[(16 * u + r) * LDX + 64 * b + 16 * wv + MF::row(g, e)] = (T)z[u][e];
     }
+    __syncthreads();
+    panel_out(U, a.ldu, f, t0, u1);
+    __syncthreads();
   }
 }
 
