@@ -696,15 +696,16 @@ CholArgs chol_args(const WS& w, double* R, int32_t* dead, int first, int fresh, 
 // R, R^{-1} column-major, leading dimension f; G overwritten by the Schur
 // complements): one workgroup on each diagonal block, the independent 64 x 64
 // block products of a step on separate workgroups, R^{-1} by recursive
-// doubling.  dg: f doubles; cbmask: two words per 64-column panel.
+// doubling.  dg: f doubles; cbmask: two words per 64-column panel.  one_pass,
+// R2one (65-128 columns): see CholArgs.
 void cb_chol(hipStream_t st, double* G, int f, double* R, double* Rinv, double* dg, int32_t* dead,
              uint64_t* cbmask, int first_pass, int fresh, State* state, int count_floors,
-             const int32_t* stopb = nullptr, int blk = 0) {
+             const int32_t* stopb = nullptr, int blk = 0, int32_t* one_pass = nullptr, double* R2one = nullptr) {
   const int P = (int)cdiv(f, 64);
   const int64_t ff = (int64_t)f * f;
   if (P == 2) {                          // two panels: one workgroup, every block in LDS
     hipLaunchKernelGGL(k_chol2p, dim3(1), dim3(256), 0, st, G, f, f, R, Rinv, dead, first_pass, fresh, state,
-                       count_floors, stopb, blk);
+                       count_floors, stopb, blk, one_pass, R2one);
     return;
   }
   hipLaunchKernelGGL(k_cb_init, dim3((unsigned)std::min<int64_t>(cdiv(ff, 256), 1024)), dim3(256), 0, st, G, f, f,
@@ -811,7 +812,7 @@ int gram_chol(eodabe_ctx* ctx, hipStream_t st, const WS& w, T* X, int64_t ld, in
   // panel-blocked, one kernel per step (see k_cb_*); every step returns at
   // once for a speculative block after the stop
   cb_chol(st, parts, f, ca.R, ca.Rinv, w.dg, ca.dead, w.cbmask, ca.first_pass, ca.fresh, w.st, ca.count_floors,
-          stopb, blk);
+          stopb, blk, ca.one_pass, ca.R2one);
   if (ca.R1)
     hipLaunchKernelGGL(k_decide, dim3(1), dim3(64), 0, st, ca.R1, ca.R, ca.dead, f, ca.col0, ca.n, w.st,
                        ca.wlog, ca.acc, ca.diag_log, blk);
@@ -821,74 +822,83 @@ int gram_chol(eodabe_ctx* ctx, hipStream_t st, const WS& w, T* X, int64_t ld, in
 
 // CholeskyQR2 of X (rows x f, element (i,c) at c*ld + i), first Cholesky
 // pass floored.  The orthonormal factor goes to Zout (leading dimension ldz;
-// X itself when Zout is null).  Blocks wider than 64 columns also write
-// R = R2 R1 (element (i,j) at j*f + i, or its transpose when transpose_R) to
-// Rout and optionally R in the data type, row-major, to Dout (ldd), and
-// overwrite X.
+// X itself when Zout is null).  f32: the factorization's data is FP32, so the
+// second pass runs only where chol_tame asks for it.  Blocks wider than 64
+// columns also write R = R2 R1 (element (i,j) at j*f + i, or its transpose
+// when transpose_R) to Rout (unless null), and overwrite X.
 template <typename T>
-int cholqr2(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, T* X, int64_t ld,
-            int64_t rows, int f, double* Rout, int transpose_R, T* tmp, T* Zout = nullptr,
-            int64_t ldz = 0, T* Dout = nullptr, int64_t ldd = 0) {
-  (void)g;
+int cholqr2(eodabe_ctx* ctx, hipStream_t st, const WS& w, T* X, int64_t ld, int64_t rows, int f, bool f32,
+            double* Rout, int transpose_R, T* tmp, T* Zout = nullptr, int64_t ldz = 0) {
   Ops<T> ops{ctx, st};
   if (f <= 0 || rows <= 0) return 0;
   if (!Zout) {
     Zout = X;
     ldz = ld;
   }
+  int32_t* one = f32 ? &w.st->one_pass[0] : nullptr;
   if (f <= 128) {
     // [Gram, Cholesky with inverse] -> R1 (rb1), R1^{-1} (rb3); [X := X R1^{-1},
     // Gram, Cholesky with inverse] -> R2 (rb2), R2^{-1} (rb5); Z = X R2^{-1}.
     // Up to 64 columns the normalisation is fused into the second Gram
-    // kernel.  Rout and Dout are not written on this path (the closing
-    // steps take R1, R2 from rb1, rb2).
+    // kernel.  One pass: R2 = I, Z = X R1^{-1}, the launches between return at
+    // once.  Rout is not written on this path (the closing steps take R1, R2
+    // from rb1, rb2).
     CholArgs c1 = chol_args(w, w.rb1, w.deadbig, 1, 1, 1);
     c1.Rinv = w.rb3;
+    c1.one_pass = one;
+    c1.R2one = w.rb2;
     TRY(gram_chol<T>(ctx, st, w, X, ld, rows, f, w.gbig, c1));
     CholArgs c2 = chol_args(w, w.rb2, w.deadbig, 0, 0, 1);
     c2.Rinv = w.rb5;
     if (f <= 64) {
-      TRY(gram_chol<T>(ctx, st, w, X, ld, rows, f, w.gbig, c2, nullptr, 0, w.rb3));
+      TRY(gram_chol<T>(ctx, st, w, X, ld, rows, f, w.gbig, c2, one, 1, w.rb3));
     } else {
       const ApplyJob a1{X, ld, X, ld, w.rb3, rows, 0, f, f, nullptr, nullptr, nullptr};
-      TRY(ops.apply(a1, nullptr, f));
-      TRY(gram_chol<T>(ctx, st, w, X, ld, rows, f, w.gbig, c2));
+      TRY(ops.apply(a1, nullptr, f, one, 1));
+      TRY(gram_chol<T>(ctx, st, w, X, ld, rows, f, w.gbig, c2, one, 1));
     }
-    const ApplyJob a{X, ld, Zout, ldz, w.rb5, rows, 0, f, f, nullptr, nullptr, nullptr};
+    const ApplyJob a{X, ld, Zout, ldz, w.rb5, rows, 0, f, f, nullptr, nullptr, nullptr, one, w.rb3};
     TRY(ops.apply(a, nullptr, f));
     return 0;
   }
   // wider: [Gram, blocked Cholesky with inverse] twice, X := X R^{-1} through
-  // scratch after each (explicit inverse, FP64 weights)
+  // scratch after each (explicit inverse, FP64 weights).  A second pass is
+  // dozens of launches, so the host waits for the test's outcome instead of
+  // sending them to return at once (about 20 us against 100).
   double* Rs[2] = {w.rb1, w.rb2};
   double* Ris[2] = {w.rb3, w.rb5};
-  for (int pass = 0; pass < 2; ++pass) {
+  bool once = false;
+  for (int pass = 0; pass < 2 && !once; ++pass) {
     CholArgs ca = chol_args(w, Rs[pass], w.deadbig, pass == 0, pass == 0, 1);
     ca.Rinv = Ris[pass];
     TRY(gram_chol<T>(ctx, st, w, X, ld, rows, f, w.gbig, ca));
-    TRY(ops.update_d(tmp, ld, X, ld, rows, f, f, Ris[pass], f));
-    const int64_t cnt = ld * (int64_t)f;
-    hipLaunchKernelGGL((k_copy2d<T, T>), dim3((unsigned)cdiv(cnt, 32), 1), dim3(32, 8), 0, st, tmp,
-                       cnt, X, cnt, (int64_t)1, cnt, 0);
-    LAUNCHCHK();
+    if (pass == 0 && one) {
+      hipLaunchKernelGGL(k_tame, dim3(64), dim3(256), 0, st, Ris[0], f, w.dg, w.cbmask, w.gbig, &w.st->counter[4], one);
+      LAUNCHCHK();
+      HIPCHK(hipMemcpyAsync(ctx->host_state, w.st, sizeof(State), hipMemcpyDeviceToHost, st));
+      HIPCHK(hipStreamSynchronize(st));
+      once = ctx->host_state->one_pass[0] == 0;
+    }
+    const bool last = pass == 1 || once;
+    if (last && Zout != X) {
+      TRY(ops.update_d(Zout, ldz, X, ld, rows, f, f, Ris[pass], f));
+    } else {
+      TRY(ops.update_d(tmp, ld, X, ld, rows, f, f, Ris[pass], f));
+      const int64_t cnt = ld * (int64_t)f;
+      hipLaunchKernelGGL((k_copy2d<T, T>), dim3((unsigned)cdiv(cnt, 32), 1), dim3(32, 8), 0, st, tmp, cnt, X, cnt,
+                         (int64_t)1, cnt, 0);
+      LAUNCHCHK();
+    }
   }
-  const int64_t ff = (int64_t)f * f;
-  hipLaunchKernelGGL(k_trimul, dim3((unsigned)(cdiv(f, 64) * cdiv(f, 64))), dim3(256), 0, st, w.rb2, w.rb1, f,
-                     Rout, transpose_R);
-  LAUNCHCHK();
-  if (Zout != X) {
-    dim3 grid((unsigned)cdiv(rows, 32), (unsigned)cdiv(f, 32));
-    hipLaunchKernelGGL((k_copy2d<T, T>), grid, dim3(32, 8), 0, st, X, ld, Zout, ldz, (int64_t)f, rows,
-                       0);
-    LAUNCHCHK();
-  }
-  if (Dout) {
-    if (transpose_R) return EODABE_EINVAL;
+  if (Rout && once) {
     dim3 grid((unsigned)cdiv(f, 32), (unsigned)cdiv(f, 32));
-    hipLaunchKernelGGL((k_copy2d<double, T>), grid, dim3(32, 8), 0, st, Rout, (int64_t)f, Dout, ldd,
-                       (int64_t)f, (int64_t)f, 1);
-    LAUNCHCHK();
+    hipLaunchKernelGGL((k_copy2d<double, double>), grid, dim3(32, 8), 0, st, w.rb1, (int64_t)f, Rout, (int64_t)f,
+                       (int64_t)f, (int64_t)f, transpose_R);
+  } else if (Rout) {
+    hipLaunchKernelGGL(k_trimul, dim3((unsigned)(cdiv(f, 64) * cdiv(f, 64))), dim3(256), 0, st, w.rb2, w.rb1, f,
+                       Rout, transpose_R);
   }
+  LAUNCHCHK();
   return 0;
 }
 
@@ -1246,16 +1256,25 @@ int small_qr(eodabe_ctx* ctx, hipStream_t st, const double* R1, const double* R2
     const dim3 grid((unsigned)cdiv(f, 32), (unsigned)cdiv(f, 32));
     const double* Mr = R2;
     if (R1) {
-      hipLaunchKernelGGL((k_sq_prod<double, true, true, false>), grid, dim3(256), 0, st, R2, R1, f, M, (int64_t)f);
+      hipLaunchKernelGGL((k_sq_prod<double, true, true, false>), grid, dim3(256), 0, st, R2, R1, f, M, (int64_t)f,
+                         nullptr, 0, nullptr);
       Mr = M;
     }
-    hipLaunchKernelGGL((k_sq_prod<double, true, false, false>), grid, dim3(256), 0, st, Mr, Mr, f, G, (int64_t)f);
-    cb_chol(st, G, f, H1, H1i, dg_scr, dead_scr, mask_scr, 1, 1, state, 1);
-    hipLaunchKernelGGL((k_sq_prod<double, false, true, false>), grid, dim3(256), 0, st, Mr, H1i, f, Z1, (int64_t)f);
-    hipLaunchKernelGGL((k_sq_prod<double, false, true, false>), grid, dim3(256), 0, st, Z1, Z1, f, G, (int64_t)f);
-    cb_chol(st, G, f, H2, H2i, dg_scr, dead_scr, mask_scr, 0, 0, state, 1);
-    hipLaunchKernelGGL((k_sq_prod<double, true, true, false>), grid, dim3(256), 0, st, Z1, H2i, f, Qout, (int64_t)f);
-    hipLaunchKernelGGL((k_sq_prod<T, true, true, true>), grid, dim3(256), 0, st, H2, H1, f, Dout, ldd);
+    hipLaunchKernelGGL((k_sq_prod<double, true, false, false>), grid, dim3(256), 0, st, Mr, Mr, f, G, (int64_t)f, nullptr,
+                       0, nullptr);
+    // FP32 data: the second pass only where chol_tame asks for it (H2 = I,
+    // Q_hat = M^T H1^{-1} otherwise)
+    int32_t* one = sizeof(T) == 4 ? &state->one_pass[1] : nullptr;
+    cb_chol(st, G, f, H1, H1i, dg_scr, dead_scr, mask_scr, 1, 1, state, 1, nullptr, 0, one, H2);
+    hipLaunchKernelGGL((k_sq_prod<double, false, true, false>), grid, dim3(256), 0, st, Mr, H1i, f, Z1, (int64_t)f,
+                       nullptr, 0, one ? Qout : nullptr);
+    hipLaunchKernelGGL((k_sq_prod<double, false, true, false>), grid, dim3(256), 0, st, Z1, Z1, f, G, (int64_t)f, one,
+                       1, nullptr);
+    cb_chol(st, G, f, H2, H2i, dg_scr, dead_scr, mask_scr, 0, 0, state, 1, one, 1);
+    hipLaunchKernelGGL((k_sq_prod<double, true, true, false>), grid, dim3(256), 0, st, Z1, H2i, f, Qout, (int64_t)f,
+                       one, 1, nullptr);
+    hipLaunchKernelGGL((k_sq_prod<T, true, true, true>), grid, dim3(256), 0, st, H2, H1, f, Dout, ldd, nullptr, 0,
+                       nullptr);
     LAUNCHCHK();
     return 0;
   }
@@ -1268,9 +1287,6 @@ int small_qr(eodabe_ctx* ctx, hipStream_t st, const double* R1, const double* R2
   else if (f <= 64)
     hipLaunchKernelGGL((k_small_qr<T, 64>), dim3(1), dim3(256), 0, st, R1, R2, f, Qout, Dout, ldd, state, 1,
                        gate, f_dev);
-  else if (f <= 128 && scr && !gate.st && !f_dev)
-    hipLaunchKernelGGL((k_small_qr128<T>), dim3(1), dim3(256), 0, st, R1, R2, f, Qout, Dout, ldd, state, 1,
-                       scr);
   else
     return EODABE_EINVAL;
   LAUNCHCHK();
@@ -1366,25 +1382,28 @@ int close_small(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, cons
     }
     return 0;
   }
+  int32_t* one = sizeof(T) == 4 ? &w.st->one_pass[0] : nullptr;   // as in cholqr2
   CholArgs c1 = chol_args(w, w.rb1, w.deadbig, 1, 1, 1);
   c1.Rinv = w.rb3;
   c1.gate = gate;
   c1.f_dev = r_dev;
+  c1.one_pass = one;
+  c1.R2one = w.rb2;
   TRY(gram_chol<T>(ctx, st, w, cb, g.ldk, g.nn, (int)r, w.gbig, c1));
   CholArgs c2 = chol_args(w, w.rb2, w.deadbig, 0, 0, 1);
   c2.Rinv = w.rb5;
   c2.gate = gate;
   c2.f_dev = r_dev;
   if (r <= 64) {
-    TRY(gram_chol<T>(ctx, st, w, cb, g.ldk, g.nn, (int)r, w.gbig, c2, nullptr, 0, w.rb3));
+    TRY(gram_chol<T>(ctx, st, w, cb, g.ldk, g.nn, (int)r, w.gbig, c2, one, 1, w.rb3));
   } else {
     const ApplyJob a1{cb, g.ldk, cb, g.ldk, w.rb3, g.nn, 0, (int)r, (int)r, nullptr, nullptr, nullptr};
-    TRY(ops.apply(a1, nullptr, (int)r));
-    TRY(gram_chol<T>(ctx, st, w, cb, g.ldk, g.nn, (int)r, w.gbig, c2));
+    TRY(ops.apply(a1, nullptr, (int)r, one, 1));
+    TRY(gram_chol<T>(ctx, st, w, cb, g.ldk, g.nn, (int)r, w.gbig, c2, one, 1));
   }
   TRY(small_qr<T>(ctx, st, w.rb1, w.rb2, (int)r, w.rb4, Dout, ldd, w.st, gate, r_dev, w.sq128, w.deadbig, w.dg,
                   w.cbmask));
-  const ApplyJob jv{cb, g.ldk, Vout, ldv, w.rb5, g.nn, 0, (int)r, (int)r, nullptr, nullptr, r_dev};
+  const ApplyJob jv{cb, g.ldk, Vout, ldv, w.rb5, g.nn, 0, (int)r, (int)r, nullptr, nullptr, r_dev, one, w.rb3};
   const ApplyJob ju{q, g.ldy, Uout, ldu, w.rb4, g.mm, 0, (int)r, (int)r, nullptr, nullptr, r_dev};
   TRY(ops.apply(jv, &ju, (int)r, nullptr, 0, gate));
   return 0;
@@ -1420,11 +1439,11 @@ int run_close(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const 
     }
     TRY(ops.reduce_wide((const T*)w.cpart, eff_splits(g.mm, s_core), cstride, cstride, cb));
     TRY(pair_fix<T>(ctx, st, g.paired, cb, g.ldk, g.nn, r));
-    TRY(cholqr2<T>(ctx, st, g, w, cb, g.ldk, g.nn, (int)r, w.rb4, 0, (T*)w.tbig));
+    TRY(cholqr2<T>(ctx, st, w, cb, g.ldk, g.nn, (int)r, sizeof(T) == 4, nullptr, 0, (T*)w.tbig));
     // Y = A Q~ (mm x r), QR(Y) -> Q
     TRY(ops.template gemm_nt<T>(Ae, g.lda_eff, cb, g.ldk, g.mm, r, g.nn, 1, q, g.ldy, g.ldy * r));
     TRY(pair_fix<T>(ctx, st, g.paired, q, g.ldy, g.mm, r));
-    TRY(cholqr2<T>(ctx, st, g, w, q, g.ldy, g.mm, (int)r, w.rb4, 0, (T*)w.tbig));
+    TRY(cholqr2<T>(ctx, st, w, q, g.ldy, g.mm, (int)r, sizeof(T) == 4, nullptr, 0, (T*)w.tbig));
   }
   if (r <= 128)
     return close_small<T>(ctx, st, g, w, Ae, r, Gate{}, nullptr, Uout, ldu, Vout, ldv, Dout, ldd, 0);
@@ -1440,10 +1459,9 @@ int run_close(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const 
   // a10: C^T = V R  (C^T is nn x r with element (j,a) at a*ldk + j = cbuf);
   //      V^T rows go straight to Vout, R^T (row-major R) to rb4 as a
   //      column-major r x r matrix.
-  TRY(cholqr2<T>(ctx, st, g, w, cb, g.ldk, g.nn, (int)r, w.rb4, 1, (T*)w.tbig, Vout, ldv));
+  TRY(cholqr2<T>(ctx, st, w, cb, g.ldk, g.nn, (int)r, sizeof(T) == 4, w.rb4, 1, (T*)w.tbig, Vout, ldv));
   // R^T = Q_hat R_hat (FP64, r x r, column-major in rb4); D_hat = R_hat -> Dout
-  TRY(cholqr2<double>(ctx, st, g, w, w.rb4, r, r, (int)r, w.rb3, 0, (double*)w.tbig, nullptr, 0,
-                      nullptr, 0));
+  TRY(cholqr2<double>(ctx, st, w, w.rb4, r, r, (int)r, sizeof(T) == 4, w.rb3, 0, (double*)w.tbig));
   {
     dim3 grid((unsigned)cdiv(r, 32), (unsigned)cdiv(r, 32));
     hipLaunchKernelGGL((k_copy2d<double, T>), grid, dim3(32, 8), 0, st, w.rb3, r, Dout, ldd, r, r, 1);
@@ -2154,7 +2172,7 @@ static int factor_impl(eodabe_ctx* ctx, const void* A, int64_t m, int64_t n, int
         hipLaunchKernelGGL((k_copy2d<T, double>), dim3((unsigned)cdiv(cnt, 32), 1), dim3(32, 8), 0, st,
                            (const T*)w.tbig, cnt, w.rb4, cnt, (int64_t)1, cnt, 0);
         LAUNCHCHK();
-        TRY(cholqr2<double>(ctx, st, g, w, w.rb4, rank, rank, (int)rank, w.rb3, 0, (double*)w.tbig));
+        TRY(cholqr2<double>(ctx, st, w, w.rb4, rank, rank, (int)rank, sizeof(T) == 4, w.rb3, 0, (double*)w.tbig));
         // U_out = V' Q'' : V' column-major m x r is cbuf (element (i,a) at a*ldk + i)
         TRY(ops.update_d((T*)Ut, m, (const T*)w.cbuf, g.ldk, m, rank, (int)rank, w.rb4, rank));
         // Vt_out = U'^T : U' column-major n x r (ld ldy) -> row a = column a

@@ -51,6 +51,8 @@ struct State {
   int32_t lp_mode;       // 0: none, 1: FP16, 2: BF16 (low-precision sketch form)
   int32_t sync_fail;     // a barrier across workgroups timed out (outputs void)
   double d_stop;         // |T(l,l)| of the column whose test stopped the loop (0: none)
+  int32_t one_pass[2];   // 0: the second pass of the current QR is not needed (chol_tame; [0] a block's or C^T's,
+                         // [1] R^T's), else INT32_MAX: the second pass's launches test it as their stop flag
 };
 static_assert(sizeof(State) % 8 == 0, "the control block is copied in 8-byte words");
 
@@ -76,6 +78,7 @@ __device__ __forceinline__ void init_state_part(const StateInit& a, int64_t t, i
     st->stop_block = 0x7fffffff; st->nonfinite = 0; st->floored = 0; st->paired = a.paired; st->rank = 0;
     for (int i = 0; i < 8; ++i) st->counter[i] = 0u;
     st->lp_scale = 1.0; st->lp_mode = a.lp_mode; st->sync_fail = 0; st->d_stop = 0.0;
+    st->one_pass[0] = st->one_pass[1] = 0x7fffffff;
   }
   for (int64_t i = t; i < a.nwlog; i += nt) a.wlog[i] = 0;
   for (int64_t i = t; i < a.ndead; i += nt) a.dead[i] = 0;
@@ -2251,6 +2254,42 @@ __device__ __forceinline__ void chol_inv(double* Gs, double* Ri, double* work, d
   chol_inv_general<F>(Gs, Ri, work, dgs, f, dmask_in, first_pass, dmask_out, nfloor, dg_in, nolive_out);
 }
 
+// A first CholeskyQR pass of FP32 data that leaves its columns orthonormal to
+// well below the data's rounding needs no second one.  Its loss of
+// orthogonality is about f u64 |D R^{-1}|_F^2, D the column norms (the Gram's
+// rounding seen through the inverse of the factor with unit columns; scaling
+// the columns does not change it); the bound 2^-27 is an eighth of an FP32
+// rounding.  FP64 data, whose own rounding that loss exceeds, and basis
+// blocks, whose stop test needs the second factor, take both passes.
+__device__ __forceinline__ bool chol_tame_sum(double s, int f, double* red) {
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  s = ((red[0] + red[1]) + red[2]) + red[3];
+  __syncthreads();
+  return f * U64 * s <= 0x1p-27;
+}
+// The test for R^{-1} in LDS (row-major, ld F + 1) and the squares dg of D's
+// entries, f <= F (uniform over the 256 threads; red: 4 doubles of LDS).
+template <int F>
+__device__ __forceinline__ bool chol_tame(const double* Ri, const double* dg, int f, double* red) {
+  constexpr int LD = SmallCfg<F>::LD;
+  double s = 0.0;
+#pragma unroll
+  for (int q = 0; q < F * F / 256; ++q) {
+    const int idx = threadIdx.x + 256 * q, i = idx / F, j = idx % F;
+    if (i <= j && j < f) s = fma(dg[i] * Ri[i * LD + j], Ri[i * LD + j], s);
+  }
+  return chol_tame_sum(s, f, red);
+}
+// Its outcome for the launches that follow: the flag, and the identity as the
+// second factor (f x f, element (i,j) at j*f + i) when there will be no other.
+__device__ __forceinline__ void one_pass_out(bool tame, int32_t* flag, double* R2, int f) {
+  if (threadIdx.x == 0) *flag = tame ? 0 : 0x7fffffff;
+  if (tame)
+    for (int idx = threadIdx.x; idx < f * f; idx += 256) R2[idx] = idx % (f + 1) == 0 ? 1.0 : 0.0;
+}
+
 // ---------------------------------------------------------------------------
 // C = op(A) op(B) for FP64 matrices in global or LDS memory (M, N, K <=
 // 128): element (i,k) of op(A) at TA ? A[k*lda + i] : A[i*lda + k], (k,j)
@@ -2527,7 +2566,9 @@ __device__ int small_qr_mid(double* lds, const double* R1g, const double* R2g, i
 // ldo, rounded to T.
 template <typename T, bool TA, bool TB, bool ROWOUT>
 __global__ __launch_bounds__(256) void k_sq_prod(const double* __restrict__ A, const double* __restrict__ B, int f,
-                                                 T* __restrict__ out, int64_t ldo) {
+                                                 T* __restrict__ out, int64_t ldo, const int32_t* __restrict__ stopb,
+                                                 int blk, T* __restrict__ out2) {
+  if (stopb && *stopb < blk) return;       // a second pass not needed
   const int i0 = blockIdx.x * 32, j0 = blockIdx.y * 32;
   if (i0 >= f || j0 >= f) return;
   const int mt = min(32, f - i0), nt = min(32, f - j0);
@@ -2535,23 +2576,11 @@ __global__ __launch_bounds__(256) void k_sq_prod(const double* __restrict__ A, c
   const double* Bs = TB ? B + (int64_t)j0 * f : B + j0;
   gmm64<TA, TB>(As, f, Bs, f, mt, nt, f, [&](int i, int j, double v) {
     if constexpr (ROWOUT) out[(int64_t)(i0 + i) * ldo + (j0 + j)] = (T)v;
-    else out[(int64_t)(j0 + j) * f + (i0 + i)] = (T)v;
+    else {
+      out[(int64_t)(j0 + j) * f + (i0 + i)] = (T)v;
+      if (out2) out2[(int64_t)(j0 + j) * f + (i0 + i)] = (T)v;
+    }
   });
-}
-
-// Closing QR (as k_small_qr) for 64 < f <= 128: R1, R2 column-major f x f
-// (R1 may be null), Qh -> Qout (column-major), Rh -> Dout (type T,
-// row-major ldd); scr: 7 x 128 x 128 doubles.
-template <typename T>
-__global__ __launch_bounds__(256) void k_small_qr128(const double* __restrict__ R1g,
-                                                     const double* __restrict__ R2g, int f,
-                                                     double* __restrict__ Qout, T* __restrict__ Dout,
-                                                     int64_t ldd, State* st, int count_floors, double* scr) {
-  __shared__ double lds[CHOL128_LDS];
-  const int nf = small_qr_mid<true>(lds, R1g, R2g, f, f, scr,
-                                    [&](int i, int j, double v) { Qout[(int64_t)j * f + i] = v; },
-                                    [&](int i, int j, double v) { Dout[(int64_t)i * ldd + j] = (T)v; });
-  if (count_floors && threadIdx.x == 0 && nf && st) atomicAdd(&st->floored, nf);
 }
 
 // ---------------------------------------------------------------------------
@@ -2770,11 +2799,12 @@ __global__ __launch_bounds__(256) void k_cb_inv(const double* __restrict__ R, do
 __global__ __launch_bounds__(256) void k_chol2p(const double* __restrict__ G, int ld, int f,
                                                 double* __restrict__ R, double* __restrict__ Rinv,
                                                 int32_t* __restrict__ dead, int first_pass, int fresh, State* st,
-                                                int count_floors, const int32_t* __restrict__ stopb, int blk) {
-  if (stopb && *stopb < blk) return;       // a speculative block after the stop
+                                                int count_floors, const int32_t* __restrict__ stopb, int blk,
+                                                int32_t* __restrict__ one_pass, double* __restrict__ R2one) {
+  if (stopb && *stopb < blk) return;       // a speculative block after the stop, or a second pass not needed
   typedef SmallCfg<64> S;
   constexpr int LD = S::LD;
-  __shared__ double A[S::SIZE], B[S::SIZE], C[S::SIZE], D[S::SIZE], work[24 * 64], dgs[64], dg1[64];
+  __shared__ double A[S::SIZE], B[S::SIZE], C[S::SIZE], D[S::SIZE], work[24 * 64], dgs[64], dg0[64], dg1[64];
   const int tid = threadIdx.x, w1 = f - 64;
   // lower-left blocks of R and R^{-1}
   for (int idx = tid; idx < w1 * 64; idx += 256) {
@@ -2805,7 +2835,10 @@ __global__ __launch_bounds__(256) void k_chol2p(const double* __restrict__ G, in
       A[i * LD + j] = va[q];
       C[i * LD + j] = vc[q];
       D[i * LD + j] = vd[q];
-      if (i == j) dg1[i] = vd[q];
+      if (i == j) {
+        dg0[i] = va[q];
+        dg1[i] = vd[q];
+      }
     }
   }
   __syncthreads();
@@ -2840,12 +2873,58 @@ __global__ __launch_bounds__(256) void k_chol2p(const double* __restrict__ G, in
   // T = R12 R22^{-1} into D, then (R^{-1})12 = -R11^{-1} T
   lds_gemm<64, false, false>(A, C, [&](int i, int j, double v) { D[i * LD + j] = v; });
   __syncthreads();
+  double ts = 0.0;                         // this thread's part of |D R^{-1}|_F^2
   lds_gemm<64, false, false>(B, D, [&](int i, int j, double v) {
-    if (j < w1) Rinv[(int64_t)(64 + j) * ld + i] = -v;
+    if (j < w1) {
+      Rinv[(int64_t)(64 + j) * ld + i] = -v;
+      ts = fma(dg0[i] * v, v, ts);
+    }
   });
+  if (one_pass) {
+    for (int idx = tid; idx < 64 * 64; idx += 256) {
+      const int i = idx / 64, j = idx % 64;
+      ts = fma(dg0[i] * B[i * LD + j], B[i * LD + j], ts);
+      ts = fma(dg1[i] * C[i * LD + j], C[i * LD + j], ts);
+    }
+    const bool tame = chol_tame_sum(ts, f, work);
+    one_pass_out(tame && (nl0 | nl1) == 0ull && (dm0 | dm1) == 0ull, one_pass, R2one, f);
+  }
   for (int c = tid; c < f; c += 256)
     dead[c] = (int32_t)(c < 64 ? ((dmo0 >> c) & 1ull) : ((dmo1 >> (c - 64)) & 1ull));
   if (tid == 0 && count_floors && (nf0 + nf1) && st) atomicAdd(&st->floored, nf0 + nf1);
+}
+
+// chol_tame for the wide Cholesky: R^{-1} and dg in global memory, column by
+// column over the workgroups, the partial sums folded in order by the last to
+// arrive; nolive: the panels' masks of refused pivots.
+__global__ __launch_bounds__(256) void k_tame(const double* __restrict__ Rinv, int f, const double* __restrict__ dg,
+                                              const uint64_t* __restrict__ nolive, double* __restrict__ parts,
+                                              uint32_t* __restrict__ counter, int32_t* __restrict__ one_pass) {
+  __shared__ double red[4];
+  __shared__ int s_last;
+  double s = 0.0;
+  for (int j = blockIdx.x; j < f; j += gridDim.x)
+    for (int i = threadIdx.x; i <= j; i += 256) {
+      const double v = Rinv[(int64_t)j * f + i];
+      s = fma(dg[i] * v, v, s);
+    }
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    parts[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    s_last = atomicAdd(counter, 1u) == gridDim.x - 1;
+    if (s_last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  }
+  __syncthreads();
+  if (!s_last || threadIdx.x != 0) return;
+  double t = 0.0;
+  uint64_t nl = 0;
+  for (unsigned b = 0; b < gridDim.x; ++b) t += parts[b];
+  for (int p = 0; p < (f + 63) / 64; ++p) nl |= nolive[p];
+  *one_pass = f * U64 * t <= 0x1p-27 && nl == 0ull ? 0 : 0x7fffffff;
+  *counter = 0u;
 }
 
 // Arguments of the Cholesky that closes a Gram pass (k_gram_rows, and the
@@ -2868,6 +2947,8 @@ struct CholArgs {
   int64_t n_norm;
   Gate gate;               // closing steps enqueued ahead of the stop flag
   const int64_t* f_dev;    // non-null: block width read on the device (<= the template width)
+  int32_t* one_pass;       // non-null: chol_tame's outcome (FP32 data, first pass), with R2one = I if it holds
+  double* R2one;
 };
 
 // ---------------------------------------------------------------------------
@@ -3149,6 +3230,11 @@ __global__ __launch_bounds__(256) void k_gram_rows(
   }
   if (tid < f) ca.dead[tid] = (int32_t)((dmask >> tid) & 1ull);
   if (ca.count_floors && tid == 0 && nfl) atomicAdd(&st->floored, nfl);
+  if (ca.one_pass) {
+    const bool plain = dmask == 0ull && nfl == 0;
+    const bool tame = chol_tame<F>(Ri, dgs, f, rowbuf);
+    one_pass_out(plain && tame, ca.one_pass, ca.R2one, f);
+  }
   if (!ca.R1 || wv != 0) return;
   // stop test (Alg. 1) on wave 0: first column whose |T(c,c)| <= eps
   const int j = lane;
@@ -3282,25 +3368,6 @@ __device__ __forceinline__ void state_send(const Cqr2Args& a) {
   const uint64_t* src = reinterpret_cast<const uint64_t*>(a.st);
   uint64_t* dst = reinterpret_cast<uint64_t*>(a.state_out);
   for (int i = 0; i < (int)(sizeof(State) / 8); ++i) dst[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Whether f u64 |D R^{-1}|_F^2 <= 2^-27 for R^{-1} (LDS, row-major, ld F + 1)
-// and the squares dg of D's entries (uniform; red: 4 doubles of LDS).
-template <int F>
-__device__ __forceinline__ bool chol_tame(const double* Ri, const double* dg, int f, double* red) {
-  constexpr int LD = SmallCfg<F>::LD;
-  double s = 0.0;
-#pragma unroll
-  for (int q = 0; q < F * F / 256; ++q) {
-    const int idx = threadIdx.x + 256 * q, i = idx / F, j = idx % F;
-    if (i <= j && j < f) s = fma(dg[i] * Ri[i * LD + j], Ri[i * LD + j], s);
-  }
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
-  s = ((red[0] + red[1]) + red[2]) + red[3];
-  __syncthreads();
-  return f * U64 * s <= 0x1p-27;
 }
 
 template <typename T, int F, bool PROJ = false>
@@ -3726,13 +3793,7 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
     int nfl = 0;
     chol_inv<F>(Gc, Rc, rowbuf, dgs, f, dmask_in, (stage & 1) == 0, &dmask, &nfl);
     if (lead && a.count_floors && tid == 0 && nfl) atomicAdd(&st->floored, nfl);
-    // closing, FP32 data: a first pass that leaves its columns orthonormal to
-    // well below the data's rounding needs no second one.  Its loss of
-    // orthogonality is about f u64 |D R^{-1}|_F^2, D the column norms (the
-    // Gram's rounding seen through the inverse of the factor with unit
-    // columns; scaling the columns does not change it); 2^-27 is an eighth of
-    // an FP32 rounding.  FP64 data, whose own rounding that loss exceeds, and
-    // basis blocks, whose stop test needs the second factor, take both passes.
+    // closing, FP32 data: the second pass only where chol_tame asks for it
     bool tame = false;
     if (sizeof(T) == 4 && a.close_qr && (stage & 1) == 0 && dmask == 0ull && nfl == 0)
       tame = chol_tame<F>(Rc, dgs, f, r1d);
@@ -3900,6 +3961,8 @@ struct ApplyJob {
   const int64_t* zoff_dev;
   const int32_t* ncols_dev;
   const int64_t* f_dev;          // if set: f = ncols = *f_dev (closing steps)
+  const int32_t* one_pass = nullptr;   // if set: W is W1 where *one_pass is 0 (no second CholeskyQR pass)
+  const double* W1 = nullptr;
 };
 
 template <typename T, int F>
@@ -3935,8 +3998,9 @@ __global__ __launch_bounds__(256) void k_apply(ApplyJob j0, ApplyJob j1,
   };
   // the first block's X rows requested first, then W: both round trips overlap
   load_x(rb);
+  const double* W = jb.one_pass && *jb.one_pass == 0 ? jb.W1 : jb.W;
   if constexpr (F <= 64) {
-    stage_small<F>({jb.W}, f, {Wl}, LD);
+    stage_small<F>({W}, f, {Wl}, LD);
   } else {
     // 16 loads per thread in flight at a time, coalesced down each column of W
     for (int q0 = 0; q0 < F * F / 256; q0 += 16) {
@@ -3945,7 +4009,7 @@ __global__ __launch_bounds__(256) void k_apply(ApplyJob j0, ApplyJob j1,
       for (int q = 0; q < 16; ++q) {
         const int idx = tid + 256 * (q0 + q);
         const int jj = idx / F, i = idx - jj * F;
-        wq[q] = (i < f && jj < f) ? jb.W[(int64_t)jj * f + i] : 0.0;
+        wq[q] = (i < f && jj < f) ? W[(int64_t)jj * f + i] : 0.0;
       }
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
@@ -4027,6 +4091,7 @@ __global__ __launch_bounds__(256) void k_apply_cols(ApplyJob j0, ApplyJob j1,
     const int k = 4 * kk + g;
     xa[kk] = (aok && k < f) ? X[(int64_t)k * jb.ldx + arow] : (T)0;
   }
+  const double* W = jb.one_pass && *jb.one_pass == 0 ? jb.W1 : jb.W;
   {                                     // W's slice: all loads in flight, coalesced down each column
     constexpr int NQ = F * CW / 256;
     double wq[NQ];
@@ -4034,7 +4099,7 @@ __global__ __launch_bounds__(256) void k_apply_cols(ApplyJob j0, ApplyJob j1,
     for (int q = 0; q < NQ; ++q) {
       const int idx = tid + 256 * q;
       const int jj = idx / F, i = idx - jj * F;
-      wq[q] = (i < f && c0 + jj < f) ? jb.W[(int64_t)(c0 + jj) * f + i] : 0.0;
+      wq[q] = (i < f && c0 + jj < f) ? W[(int64_t)(c0 + jj) * f + i] : 0.0;
     }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -4099,6 +4164,17 @@ __global__ __launch_bounds__(256) void k_small_qr(const double* __restrict__ R1g
   uint64_t dm1, dm2;
   int nf1, nf2;
   chol_inv<F>(B1, B2, rowbuf, dgs, f, 0ull, 1, &dm1, &nf1);                 // Rh1 (B1), Rh1^{-1} (B2)
+  nf2 = 0;
+  if (sizeof(T) == 4 && dm1 == 0ull && nf1 == 0 && chol_tame<F>(B2, dgs, f, rowbuf)) {
+    lds_gemm<F, true, false>(B0, B2, [&](int i, int jj, double v) {         // Qh = M^T Rh1^{-1}, Rh = Rh1
+      if (i < f && jj < f) Qout[(int64_t)jj * f + i] = v;
+    });
+    for (int idx = tid; idx < F * F; idx += 256) {
+      const int i = idx / F, jj = idx - i * F;
+      if (i < f && jj < f) Dout[(int64_t)i * ldd + jj] = (T)B1[i * LD + jj];
+    }
+    return;
+  }
   lds_gemm<F, true, false>(B0, B2, [&](int i, int jj, double v) { B3[i * LD + jj] = v; });   // Z1 = M^T Rh1^{-1}
   __syncthreads();
   lds_gemm<F, true, false>(B3, B3, [&](int i, int jj, double v) { B0[i * LD + jj] = v; });   // Z1^T Z1
