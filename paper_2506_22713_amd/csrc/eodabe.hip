@@ -413,22 +413,22 @@ struct Ops {
   template <typename Tacc>
   int gemm_nt(const T* X, int64_t ldx, const T* Z, int64_t ldz, int64_t M, int64_t N, int64_t K,
               int splits, Tacc* out, int64_t ldo, int64_t part_stride, double* sumsq = nullptr,
-              const int64_t* wlog = nullptr, const int32_t* stopb = nullptr, int blk = 0) {
+              const int64_t* wlog = nullptr, const int32_t* stopb = nullptr, int blk = 0, int upper = 0) {
     if (M <= 0 || N <= 0) return 0;
     const int64_t kchunk = split_chunk(K, splits);
     splits = eff_splits(K, splits);
     if (N <= 16) {
       dim3 grid((unsigned)cdiv(M, 128), splits, 1);
       hipLaunchKernelGGL((k_gemm_nt<T, Tacc, 2, 1>), grid, dim3(256), 0, st, X, ldx, Z, ldz, M, N, K,
-                         kchunk, out, ldo, part_stride, sumsq, wlog, stopb, blk);
+                         kchunk, out, ldo, part_stride, sumsq, wlog, stopb, blk, upper);
     } else if (N <= 32) {
       dim3 grid((unsigned)cdiv(M, 128), splits, 1);
       hipLaunchKernelGGL((k_gemm_nt<T, Tacc, 2, 2>), grid, dim3(256), 0, st, X, ldx, Z, ldz, M, N, K,
-                         kchunk, out, ldo, part_stride, sumsq, wlog, stopb, blk);
+                         kchunk, out, ldo, part_stride, sumsq, wlog, stopb, blk, upper);
     } else {
       dim3 grid((unsigned)cdiv(M, 128), splits, (unsigned)cdiv(N, 64));
       hipLaunchKernelGGL((k_gemm_nt<T, Tacc, 2, 4>), grid, dim3(256), 0, st, X, ldx, Z, ldz, M, N, K,
-                         kchunk, out, ldo, part_stride, sumsq, wlog, stopb, blk);
+                         kchunk, out, ldo, part_stride, sumsq, wlog, stopb, blk, upper);
     }
     LAUNCHCHK();
     return 0;
@@ -613,7 +613,8 @@ struct Ops {
     if (nparts <= 4) return reduce(parts, nparts, stride, count, out, stopb, blk, gate);
     // many partials over few elements: spread each element group's partials
     // over P threads (few elements: count below 2^17, fewer than 256 workgroups)
-    const int P = (count <= (1 << 17) && nparts >= 128) ? 16 : (count <= (1 << 17) && nparts >= 48) ? 4 : 1;
+    const int P = (count <= (1 << 17) && nparts >= 128) ? 16
+                  : (count <= (1 << 17) && nparts >= (sizeof(U) == 8 ? 12 : 48)) ? 4 : 1;
 #define FOLD_P(PP)                                                                                       \
   hipLaunchKernelGGL((k_fold_parts<U, PP>), dim3((unsigned)cdiv(count, 512 / PP)), dim3(128), 0, st, parts, \
                      nparts, stride, count, out, stopb, blk, gate)
@@ -653,13 +654,14 @@ struct Ops {
     return 0;
   }
 
-  // Y = Q W with an FP64 W (column-major, ldw); FP64 accumulation.
+  // Y = Q W with an FP64 W (column-major, ldw; upper: upper triangular); FP64
+  // accumulation.
   int update_d(T* Y, int64_t ldy, const T* Q, int64_t ldq, int64_t m, int64_t w, int f,
-               const double* W, int64_t ldw) {
+               const double* W, int64_t ldw, int upper = 0) {
     if (m <= 0 || f <= 0) return 0;
-    dim3 grid((unsigned)cdiv(m, 64), (unsigned)cdiv(f, 64));
-    hipLaunchKernelGGL((k_update_rows<T, double>), grid, dim3(256), 0, st, Y, ldy, Q, ldq, m, w, f,
-                       W, ldw, 0, (const int64_t*)nullptr, (const int32_t*)nullptr, 0);
+    if (cdiv(m, ROWS_WG) > 0x7fffffff || cdiv(f, 64) > 65535) return EODABE_EINVAL;
+    dim3 grid((unsigned)cdiv(m, ROWS_WG), (unsigned)cdiv(f, 64));
+    hipLaunchKernelGGL((k_rows_gemm<T>), grid, dim3(256), 0, st, Y, ldy, Q, ldq, m, w, f, W, ldw, upper);
     LAUNCHCHK();
     return 0;
   }
@@ -801,13 +803,17 @@ int gram_chol(eodabe_ctx* ctx, hipStream_t st, const WS& w, T* X, int64_t ld, in
   // G = X^T X as K-split partials summed in fixed order: up to 63 splits of
   // at least 64 rows for f <= 128 (the partial buffers hold 64 such
   // matrices; more splits put more workgroups on the FP64 products),
-  // GRAM_SPLITS_WIDE of at least 512 rows above
+  // GRAM_SPLITS_WIDE of at least 512 rows above; one split less where the
+  // partials' stride is rounded up for the fold's vector loads (f odd), so
+  // that they fit the same buffer.  Blocks below the diagonal are not formed:
+  // the Cholesky reads none of them.
+  const int64_t ff = (int64_t)f * f, fs = rup(ff, 4);
+  const int pad = fs != ff ? 1 : 0;
   const int gs = (int)std::max<int64_t>(
-      1, f <= 128 ? std::min<int64_t>(63, rows / 64) : std::min<int64_t>(GRAM_SPLITS_WIDE, rows / 512));
-  const int64_t ff = (int64_t)f * f;
-  double* gsum = parts + (int64_t)gs * ff;
-  TRY(ops.template gemm_nt<double>(X, ld, X, ld, f, f, rows, gs, parts, f, ff, nullptr, nullptr, stopb, blk));
-  TRY(ops.reduce_wide(parts, eff_splits(rows, gs), ff, ff, gsum, stopb, blk));
+      1, f <= 128 ? std::min<int64_t>(63 - pad, rows / 64) : std::min<int64_t>(GRAM_SPLITS_WIDE - pad, rows / 512));
+  double* gsum = parts + (int64_t)gs * fs;
+  TRY(ops.template gemm_nt<double>(X, ld, X, ld, f, f, rows, gs, parts, f, fs, nullptr, nullptr, stopb, blk, 1));
+  TRY(ops.reduce_wide(parts, eff_splits(rows, gs), fs, ff, gsum, stopb, blk));
   parts = gsum;
   // panel-blocked, one kernel per step (see k_cb_*); every step returns at
   // once for a speculative block after the stop
@@ -881,9 +887,9 @@ int cholqr2(eodabe_ctx* ctx, hipStream_t st, const WS& w, T* X, int64_t ld, int6
     }
     const bool last = pass == 1 || once;
     if (last && Zout != X) {
-      TRY(ops.update_d(Zout, ldz, X, ld, rows, f, f, Ris[pass], f));
+      TRY(ops.update_d(Zout, ldz, X, ld, rows, f, f, Ris[pass], f, 1));
     } else {
-      TRY(ops.update_d(tmp, ld, X, ld, rows, f, f, Ris[pass], f));
+      TRY(ops.update_d(tmp, ld, X, ld, rows, f, f, Ris[pass], f, 1));
       const int64_t cnt = ld * (int64_t)f;
       hipLaunchKernelGGL((k_copy2d<T, T>), dim3((unsigned)cdiv(cnt, 32), 1), dim3(32, 8), 0, st, tmp, cnt, X, cnt,
                          (int64_t)1, cnt, 0);
@@ -2572,7 +2578,7 @@ int eodabe_features(eodabe_ctx* ctx, const float* Ut, const float* core, int64_t
   if (m == 0 || r == 0) return EODABE_OK;
   if (!Ut || !core || !F) return EODABE_EINVAL;
   TRY(check_dev(ctx));
-  hipLaunchKernelGGL(k_features, dim3((unsigned)cdiv(m, 256), (unsigned)r), dim3(256), 0, ctx->stream, Ut, core, m,
+  hipLaunchKernelGGL(k_features, dim3((unsigned)cdiv(m, 256)), dim3(256), 0, ctx->stream, Ut, core, m,
                      (int)r, r_cap, F, ldf);
   LAUNCHCHK();
   return EODABE_OK;

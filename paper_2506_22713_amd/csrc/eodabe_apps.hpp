@@ -152,16 +152,49 @@ __global__ __launch_bounds__(256) void k_img_metrics(const ImgSums* __restrict__
 }
 
 // Pixel features F = U_hat D_hat (m x r, row-major, ldf): F(i, a) =
-// sum_{b <= a} U(i, b) D(b, a) with D upper triangular (grid: m / 256 x r).
+// sum_{b <= a} U(i, b) D(b, a), b ascending, with D upper triangular.  A thread
+// takes one pixel and FEAT_W features at a time (U read once per FEAT_W
+// features; the entries of D are uniform loads), and the results leave through
+// LDS as whole rows.  It is bound by reading U and writing F: 262144 x 15 in
+// 45 us with a thread per feature, which read U r / 2 times and stored single
+// floats a row apart.
+constexpr int FEAT_W = 16;
 __global__ __launch_bounds__(256) void k_features(const float* __restrict__ Ut, const float* __restrict__ core,
                                                   int64_t m, int r, int64_t rc, float* __restrict__ F,
                                                   int64_t ldf) {
-  const int a = blockIdx.y;
-  const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
-  if (i >= m || a >= r) return;
-  float acc = 0.f;
-  for (int b = 0; b <= a; ++b) acc = fmaf(Ut[(int64_t)b * m + i], core[(int64_t)b * rc + a], acc);
-  F[i * ldf + a] = acc;
+  __shared__ float buf[256][FEAT_W + 1];
+  const int64_t i0 = blockIdx.x * (int64_t)256, i = i0 + threadIdx.x < m ? i0 + threadIdx.x : m - 1;
+  const int rows = (int)(m - i0 < 256 ? m - i0 : 256);
+  for (int a0 = 0; a0 < r; a0 += FEAT_W) {
+    const int w = r - a0 < FEAT_W ? r - a0 : FEAT_W;
+    float acc[FEAT_W];
+#pragma unroll
+    for (int k = 0; k < FEAT_W; ++k) acc[k] = 0.f;
+    for (int b = 0; b < a0; ++b) {
+      const float u = Ut[(int64_t)b * m + i];
+      const float* d = core + (int64_t)b * rc + a0;
+#pragma unroll
+      for (int k = 0; k < FEAT_W; ++k) acc[k] = fmaf(u, d[k < w ? k : 0], acc[k]);
+    }
+    float u[FEAT_W];
+#pragma unroll
+    for (int q = 0; q < FEAT_W; ++q) u[q] = Ut[(int64_t)(a0 + (q < w ? q : 0)) * m + i];
+#pragma unroll
+    for (int q = 0; q < FEAT_W; ++q) {
+      if (q >= w) break;
+      const float* d = core + (int64_t)(a0 + q) * rc + a0;
+#pragma unroll
+      for (int k = q; k < FEAT_W; ++k) acc[k] = fmaf(u[q], d[k < w ? k : q], acc[k]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < FEAT_W; ++k) buf[threadIdx.x][k] = acc[k];
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < rows * w; idx += 256) {
+      const int row = idx / w, k = idx - row * w;
+      F[(i0 + row) * ldf + a0 + k] = buf[row][k];
+    }
+  }
 }
 
 constexpr int KNN_KMAX = 16;

@@ -420,7 +420,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt(
     const Tin* __restrict__ X, int64_t ldx, const Tin* __restrict__ Z, int64_t ldz,
     int64_t M, int64_t N, int64_t K, int64_t kchunk, Tacc* __restrict__ out, int64_t ldo,
     int64_t part_stride, double* __restrict__ sumsq, const int64_t* __restrict__ wlog,
-    const int32_t* __restrict__ stop_block, int block_id) {
+    const int32_t* __restrict__ stop_block, int block_id, int upper) {
   typedef Mfma<Tacc> MF;
   if (stop_block && *stop_block < block_id) return;
   if (wlog) M = wlog[block_id];
@@ -431,6 +431,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt(
   const int s = blockIdx.y;
   const int64_t kb = (int64_t)s * kchunk;
   const int64_t ke = min(K, kb + kchunk);
+  if (upper && m0 > n0 + 16 * CT - 1) return;   // a symmetric product: nothing on or above the diagonal here
   const bool do_ss = (sumsq != nullptr) && blockIdx.z == 0;
   double ss = 0.0;
   __shared__ double ss_red[4];
@@ -1565,66 +1566,84 @@ __global__ void k_reduce_cols(const T* __restrict__ parts, int nparts, int64_t s
 }
 
 // ---------------------------------------------------------------------------
-// Y (m x f) -= Q (m x w) W (w x f), or Y = Q W without subtract (Y, Q
-// column-major; W column-major ldw).  On MFMA: FP32 operands and
-// accumulation when TW is float, FP64 (f64 MFMA) when TW is double.  A
-// workgroup takes 64 rows and 64 columns of Y (wave: 16 rows x 4 column
-// tiles); W is staged in LDS 64 rows at a time and each wave issues all 16
-// Q loads of a chunk before its MFMAs.  w from wlog when given.
+// Y (m x f) = X (m x w) W (w x f) with FP64 weights and accumulation, X and Y
+// column-major of type T, W column-major (ldw; upper: upper triangular, so a
+// column block reads its leading rows alone).  FP64 MFMA bounds it: a
+// workgroup takes 128 rows and 64 columns (a wave 32 rows, so each weight read
+// from LDS feeds two MFMAs), W goes through two LDS buffers 32 rows at a time
+// and the next chunk's operands are in flight while one is multiplied.  At
+// 4096 x 1500 x 1500 the single-buffered 64-row form took 706 us, 36 % of the
+// FP64 peak with the zeros below the diagonal included.  The longest column
+// blocks are taken first.
 // ---------------------------------------------------------------------------
-template <typename T, typename TW>
-__global__ __launch_bounds__(256) void k_update_rows(
-    T* __restrict__ Y, int64_t ldy, const T* __restrict__ Q, int64_t ldq, int64_t m, int64_t w,
-    int f, const TW* __restrict__ W, int64_t ldw, int subtract,
-    const int64_t* __restrict__ wlog, const int32_t* __restrict__ stop_block, int block_id) {
-  typedef Mfma<TW> MF;
-  constexpr int LDS_W = 64 + (sizeof(TW) == 8 ? 1 : 4);
-  if (stop_block && *stop_block < block_id) return;
-  if (wlog) w = wlog[block_id];
-  if (w == 0 && subtract) return;
-  __shared__ TW Ws[64 * LDS_W];
+constexpr int ROWS_WG = 128;
+template <typename T>
+__global__ __launch_bounds__(256) void k_rows_gemm(T* __restrict__ Y, int64_t ldy, const T* __restrict__ X,
+                                                   int64_t ldx, int64_t m, int64_t w, int f,
+                                                   const double* __restrict__ W, int64_t ldw, int upper) {
+  typedef Mfma<double> MF;
+  constexpr int KC = 32, LDW = 65;
+  __shared__ double Ws[2][KC * LDW];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r = lane & 15, g = lane >> 4;
-  const int64_t row0 = (int64_t)blockIdx.x * 64 + 16 * wv;
-  const int c0 = blockIdx.y * 64;
-  const int fc = (int)min((int64_t)64, (int64_t)f - c0);
-  const int64_t arow = row0 + r;
-  const bool aok = arow < m;
-  typename MF::acc_t acc[4];
+  const int64_t row0 = (int64_t)blockIdx.x * ROWS_WG + 32 * wv;
+  const int c0 = 64 * (gridDim.y - 1 - blockIdx.y);
+  const int64_t wl = upper ? min(w, (int64_t)c0 + 64) : w;
+  const T* xp[2];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) acc[u] = MF::zero();
-  for (int64_t a0 = 0; a0 < w; a0 += 64) {
-    const int na = (int)min((int64_t)64, w - a0);
-    // this wave's Q operands for the chunk (row arow, columns a0 + 4kk + g)
-    TW qa[16];
+  for (int t = 0; t < 2; ++t) xp[t] = X + min(row0 + 16 * t + r, m - 1);
+  // loads past the edges are clamped to the last row, column or weight; the
+  // weights past wl and f are stored as zeros
+  T xn[2][KC / 4];
+  double wn[KC / 4];
+  const int wk = tid & 31, wc = tid >> 5;
+  auto load = [&](int64_t a0) {
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      const int k = 4 * kk + g;
-      qa[kk] = (aok && k < na) ? (TW)Q[(a0 + k) * ldq + arow] : (TW)0;
+    for (int q = 0; q < KC / 4; ++q) {
+      const int64_t k = min(a0 + 4 * q + g, wl - 1);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) xn[t][q] = xp[t][k * ldx];
+      wn[q] = W[(int64_t)min(c0 + wc + 8 * q, f - 1) * ldw + min(a0 + wk, wl - 1)];
+    }
+  };
+  typename MF::acc_t acc[2][4];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[t][u] = MF::zero();
+  load(0);
+  int buf = 0;
+  for (int64_t a0 = 0; a0 < wl; a0 += KC, buf ^= 1) {
+    double x[2][KC / 4];
+    double* Wb = Ws[buf];
+#pragma unroll
+    for (int q = 0; q < KC / 4; ++q) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) x[t][q] = (double)xn[t][q];
+      Wb[wk * LDW + wc + 8 * q] = a0 + wk < wl && c0 + wc + 8 * q < f ? wn[q] : 0.0;
     }
     __syncthreads();
-    for (int idx = tid; idx < 64 * 64; idx += 256) {
-      const int k = idx >> 6, c = idx & 63;
-      Ws[k * LDS_W + c] = (k < na && c < fc) ? W[(int64_t)(c0 + c) * ldw + a0 + k] : (TW)0;
-    }
-    __syncthreads();
+    if (a0 + KC < wl) load(a0 + KC);
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk)
+    for (int q = 0; q < KC / 4; ++q)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) acc[u] = MF::op(qa[kk], Ws[(4 * kk + g) * LDS_W + 16 * u + r], acc[u]);
+      for (int u = 0; u < 4; ++u) {
+        const double b = Wb[(4 * q + g) * LDW + 16 * u + r];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[t][u] = MF::op(x[t][q], b, acc[t][u]);
+      }
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int c = 16 * u + r;
-    if (c >= fc) continue;
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t row = row0 + MF::row(g, e);
-      if (row < m) {
-        T* p = Y + (int64_t)(c0 + c) * ldy + row;
-        *p = subtract ? (T)((TW)*p - acc[u][e]) : (T)acc[u][e];
+    for (int u = 0; u < 4; ++u) {
+      const int c = c0 + 16 * u + r;
+      if (c >= f) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t row = row0 + 16 * t + MF::row(g, e);
+        if (row < m) Y[(int64_t)c * ldy + row] = (T)acc[t][u][e];
       }
     }
-  }
 }
 
 
