@@ -190,10 +190,10 @@ __global__ __launch_bounds__(256) void k_features(const float* __restrict__ Ut, 
 #pragma unroll
     for (int k = 0; k < FEAT_W; ++k) buf[threadIdx.x][k] = acc[k];
     __syncthreads();
-    for (int idx = threadIdx.x; idx < rows * w; idx += 256) {
-      const int row = idx / w, k = idx - row * w;
-      F[(i0 + row) * ldf + a0 + k] = buf[row][k];
-    }
+    const int k = threadIdx.x % FEAT_W;
+    if (k < w)
+      for (int row = threadIdx.x / FEAT_W; row < rows; row += 256 / FEAT_W)
+        F[(i0 + row) * ldf + a0 + k] = buf[row][k];
   }
 }
 

@@ -2365,87 +2365,6 @@ __device__ __forceinline__ void gmm64(const double* A, int lda, const double* B,
   }
 }
 
-// C = op(A) op(B) for M, N, K <= 64 with both operands staged in LDS first
-// (every thread's loads in flight at once: one memory round trip), then
-// 16 x 16 FP64 MFMA tiles from LDS, four per wave.  Element (i,k) of op(A)
-// at TA ? A[k*lda + i] : A[i*lda + k], (k,j) of op(B) at TB ? B[j*ldb + k] :
-// B[k*ldb + j]; element (i, j) of the product goes to out(i, j, v) for
-// i < M, j < N.  sm: GMM64S_LDS doubles of LDS; the call begins and ends
-// with a barrier, so consecutive calls may share sm.
-constexpr int GMM64S_LD = 65;
-constexpr int GMM64S_LDS = 2 * 64 * GMM64S_LD;
-template <bool TA, bool TB, typename Out>
-__device__ __forceinline__ void gmm64s(const double* A, int lda, const double* B, int ldb, int M, int N, int K,
-                                       double* sm, Out out) {
-  typedef Mfma<double> MF;
-  constexpr int LD = GMM64S_LD;
-  double* As = sm;                 // As[i*LD + k] = op(A)(i, k)
-  double* Bs = sm + 64 * LD;       // Bs[k*LD + j] = op(B)(k, j)
-  const int tid = threadIdx.x;
-  __syncthreads();                 // earlier readers of sm are done
-  double va[16], vb[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int idx = tid + 256 * q;
-    const int hi = idx >> 6, lo = idx & 63;   // lo runs along contiguous memory
-    // op(A): TA -> memory (k = hi, i = lo) contiguous in i; else (i = hi, k = lo)
-    {
-      const int i = TA ? lo : hi, k = TA ? hi : lo;
-      va[q] = (i < M && k < K) ? (TA ? A[(int64_t)k * lda + i] : A[(int64_t)i * lda + k]) : 0.0;
-    }
-    // op(B): TB -> memory (j = hi, k = lo) contiguous in k; else (k = hi, j = lo)
-    {
-      const int j = TB ? hi : lo, k = TB ? lo : hi;
-      vb[q] = (k < K && j < N) ? (TB ? B[(int64_t)j * ldb + k] : B[(int64_t)k * ldb + j]) : 0.0;
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int idx = tid + 256 * q;
-    const int hi = idx >> 6, lo = idx & 63;
-    {
-      const int i = TA ? lo : hi, k = TA ? hi : lo;
-      As[i * LD + k] = va[q];
-    }
-    {
-      const int j = TB ? hi : lo, k = TB ? lo : hi;
-      Bs[k * LD + j] = vb[q];
-    }
-  }
-  __syncthreads();
-  const int wv = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
-  const int TM = (M + 15) / 16, TN = (N + 15) / 16, KS = (K + 3) / 4;
-  // wave wv: tiles wv, wv + 4, wv + 8, wv + 12 of the TM x TN grid (row-major)
-  typename MF::acc_t acc[4];
-#pragma unroll
-  for (int h = 0; h < 4; ++h) acc[h] = MF::zero();
-  for (int kk = 0; kk < KS; ++kk) {
-    const int k = 4 * kk + g;
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const int tile = wv + 4 * h;
-      if (tile < TM * TN) {
-        const int ti = tile / TN, tj = tile - ti * TN;
-        acc[h] = MF::op(As[(16 * ti + r) * LD + k], Bs[k * LD + 16 * tj + r], acc[h]);
-      }
-    }
-  }
-#pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    const int tile = wv + 4 * h;
-    if (tile < TM * TN) {
-      const int ti = tile / TN, tj = tile - ti * TN;
-      const int j = 16 * tj + r;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int i = 16 * ti + MF::row(g, e);
-        if (i < M && j < N) out(i, j, acc[h][e]);
-      }
-    }
-  }
-  __syncthreads();
-}
-
 // LDS (doubles) used by chol_inv128.
 constexpr int CHOL128_LDS = 3 * SmallCfg<64>::SIZE + 24 * 64 + 2 * 64;
 
@@ -2688,6 +2607,53 @@ __global__ __launch_bounds__(256) void k_cb_diag(const double* __restrict__ G, i
   }
 }
 
+// 64 x 64 blocks of column-major FP64 matrices on 256 threads: thread (lo, hi)
+// = (tid % 64, tid / 64) takes row lo of columns hi, hi + 4, ...  Loads past
+// the block's edge are clamped to it (no branch between loads) and stored as
+// zeros; in LDS element (i, j) is at i*BLK_LD + j.
+constexpr int BLK_LD = 65, BLK_SIZE = 64 * BLK_LD;
+__device__ __forceinline__ void blk_load(double (&v)[16], const double* p, int64_t ld, int rows, int cols) {
+  const int lo = min((int)threadIdx.x & 63, rows - 1), hi = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) v[q] = p[(int64_t)min(hi + 4 * q, cols - 1) * ld + lo];
+}
+__device__ __forceinline__ void blk_store(const double (&v)[16], double* s, int rows, int cols) {
+  const int lo = threadIdx.x & 63, hi = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) s[lo * BLK_LD + hi + 4 * q] = (lo < rows && hi + 4 * q < cols) ? v[q] : 0.0;
+}
+// R = Ri^T S for an upper triangular Ri, in place of S (both in LDS): wave w
+// the columns 16 w .. 16 w + 15, which no other wave reads.  Rows in nl and,
+// with dead, this lane's column 16 w + r become zero.
+__device__ __forceinline__ void blk_rpanel(const double* Ri, double* S, uint64_t nl, bool dead) {
+  typedef Mfma<double> MF;
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  double* col = S + 16 * (threadIdx.x >> 6) + r;
+  double b[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) b[k] = col[(4 * k + g) * BLK_LD];
+  typename MF::acc_t acc[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    acc[t] = MF::zero();
+#pragma unroll
+    for (int k = 0; k < 4 * t + 4; ++k) acc[t] = MF::op(Ri[(4 * k + g) * BLK_LD + 16 * t + r], b[k], acc[t]);
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = 16 * t + MF::row(g, e);
+      col[i * BLK_LD] = (dead || ((nl >> i) & 1ull)) ? 0.0 : acc[t][e];
+    }
+}
+
+// One step of the wide Cholesky (see above).  Workgroup 0 carries the chain of
+// diagonal blocks, so everything it needs is requested at once: R_pp^{-1}, the
+// panel's blocks and the block to update, one round trip instead of one per
+// product, and each product's operands stay in LDS or registers for the next.
+// A step with 64 x 64 products staged one after another from memory took 43 us
+// (rank 1500), of which the diagonal block's factorization is 10.
 __global__ __launch_bounds__(256) void k_cb_look(double* __restrict__ G, int ld, int f, int p,
                                                  double* __restrict__ R, double* __restrict__ Rinv,
                                                  const double* __restrict__ dg, const int32_t* __restrict__ dead,
@@ -2696,60 +2662,118 @@ __global__ __launch_bounds__(256) void k_cb_look(double* __restrict__ G, int ld,
                                                  const int32_t* __restrict__ stopb, int blk) {
   if (stopb && *stopb < blk) return;       // a speculative block after the stop
   typedef SmallCfg<64> S;
-  constexpr int LD = S::LD;
-  static_assert(S::SIZE >= 64 * LD, "a 64 x 64 block per buffer");
-  __shared__ double sm[GMM64S_LDS];
-  __shared__ double Gs[S::SIZE], Ri[S::SIZE], work[24 * 64], dgs[64];
-  const int k0 = 64 * p, pw = cb_width(f, p);
+  typedef Mfma<double> MF;
+  static_assert(S::LD == BLK_LD, "one layout for blocks and factors");
+  __shared__ double Ls[BLK_SIZE], Sq[BLK_SIZE], Sr[BLK_SIZE], Gs[S::SIZE], work[24 * 64], dgs[64];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lr = lane & 15, g = lane >> 4;
+  const int k0 = 64 * p, pw = cb_width(f, p), P = (f + 63) / 64;
+  // block pair (q, r), p < q <= r < P, enumerated row by row; pair 0 =
+  // (p+1, p+1) belongs to workgroup 0
+  int idx = blockIdx.x, q = p + 1;
+  while (idx >= P - q) {
+    idx -= P - q;
+    ++q;
+  }
+  const int r = q + idx;
+  const int cq = 64 * q, cr = 64 * r, qw = cb_width(f, q), rw = cb_width(f, r);
   const uint64_t nl = nolive[p];
-  // R_pq = R_pp^{-T} S_pq with the masked entries zeroed, into dst (column j
-  // at dst + j*LD) and, if store, into R
-  auto rblock = [&](int q, double* dst, bool store) {
-    const int c0 = 64 * q, qw = cb_width(f, q);
-    gmm64s<false, true>(Rinv + (int64_t)k0 * ld + k0, ld, G + (int64_t)c0 * ld + k0, ld, pw, qw, pw, sm,
-                        [&](int i, int j, double v) {
-                          const bool z = ((nl >> i) & 1ull) || dead[c0 + j] != 0;
-                          const double x = z ? 0.0 : v;
-                          dst[j * LD + i] = x;
-                          if (store) R[(int64_t)(c0 + j) * ld + k0 + i] = x;
-                        });
-  };
-  if (blockIdx.x != 0) {
-    // trailing block pair (q, r), p < q <= r < P, enumerated row by row;
-    // pair 0 = (p+1, p+1) belongs to workgroup 0
-    const int P = (f + 63) / 64;
-    int idx = blockIdx.x, q = p + 1;
-    while (idx >= P - q) {
-      idx -= P - q;
-      ++q;
+  const int jc = 16 * wv + lr;             // this lane's column of the wave's 16
+  const bool dq = dead[cq + min(jc, qw - 1)] != 0, dr = dead[cr + min(jc, rw - 1)] != 0;
+  uint64_t dm = 0;
+  if (blockIdx.x == 0) dm = __ballot(dead[cq + min(lane, qw - 1)] != 0 && lane < qw);
+  double vl[16], vq[16], vr[16];
+  blk_load(vl, Rinv + (int64_t)k0 * ld + k0, ld, pw, pw);
+  blk_load(vq, G + (int64_t)cq * ld + k0, ld, pw, qw);
+  if (r != q) blk_load(vr, G + (int64_t)cr * ld + k0, ld, pw, rw);
+  typename MF::acc_t acc[4];               // S_qr: rows 16 t .. of column jc
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      acc[t][e] = G[(int64_t)(cr + min(jc, rw - 1)) * ld + cq + min(16 * t + MF::row(g, e), qw - 1)];
+  blk_store(vl, Ls, pw, pw);
+  blk_store(vq, Sq, pw, qw);
+  if (r != q) blk_store(vr, Sr, pw, rw);
+  __syncthreads();
+  blk_rpanel(Ls, Sq, nl, dq);
+  if (r != q) blk_rpanel(Ls, Sr, nl, dr);
+  __syncthreads();
+  if (q == r)
+    for (int e = tid; e < pw * qw; e += 256) {
+      const int j = e / pw, i = e - j * pw;
+      R[(int64_t)(cq + j) * ld + k0 + i] = Sq[i * BLK_LD + j];
     }
-    const int r = q + idx;
-    const int cq = 64 * q, cr = 64 * r, qw = cb_width(f, q), rw = cb_width(f, r);
-    rblock(q, Gs, q == r);
-    if (r != q) rblock(r, Ri, false);
-    gmm64s<false, true>(Gs, LD, r != q ? Ri : Gs, LD, qw, rw, pw, sm,
-                        [&](int i, int j, double v) { G[(int64_t)(cr + j) * ld + cq + i] -= v; });
+  const double* Bs = r != q ? Sr : Sq;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const double b = Bs[(4 * k + g) * BLK_LD + jc];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = MF::op(-Sq[(4 * k + g) * BLK_LD + 16 * t + lr], b, acc[t]);
+  }
+  if (blockIdx.x != 0) {
+    if (jc < rw)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = 16 * t + MF::row(g, e);
+          if (i < qw) G[(int64_t)(cr + jc) * ld + cq + i] = acc[t][e];
+        }
     return;
   }
-  // workgroup 0: R_{p,p+1}, S_{p+1,p+1} -= R_{p,p+1}^T R_{p,p+1} in LDS,
-  // then the diagonal step p+1 on it (as k_cb_diag)
-  const int tid = threadIdx.x, p1 = p + 1, c1 = 64 * p1, w1 = cb_width(f, p1);
-  uint64_t dm = 0, dmo = 0, nl1 = 0;
-  for (int c = 0; c < w1; ++c) dm |= (uint64_t)(dead[c1 + c] != 0) << c;
-  rblock(p1, Ri, true);
-  stage_small<64>({G + (int64_t)c1 * ld + c1}, w1, {Gs}, LD, ld);
-  gmm64s<false, true>(Ri, LD, Ri, LD, w1, w1, pw, sm, [&](int i, int j, double v) { Gs[i * LD + j] -= v; });
+  // workgroup 0: the diagonal step p+1 on the block (as k_cb_diag)
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = 16 * t + MF::row(g, e);
+      Gs[i * BLK_LD + jc] = (i < qw && jc < qw) ? acc[t][e] : 0.0;
+    }
+  __syncthreads();
+  uint64_t dmo = 0, nl1 = 0;
   int nf = 0;
-  chol_inv<64>(Gs, Ri, work, dgs, w1, dm, first_pass, &dmo, &nf, dg + c1, &nl1);
-  for (int idx = tid; idx < w1 * w1; idx += 256) {
-    const int i = idx / w1, j = idx - i * w1;
-    R[(int64_t)(c1 + j) * ld + c1 + i] = Gs[i * LD + j];
-    Rinv[(int64_t)(c1 + j) * ld + c1 + i] = Ri[i * LD + j];
+  double* Ri = Sr;                         // not used by a pair (q, q)
+  chol_inv<64>(Gs, Ri, work, dgs, qw, dm, first_pass, &dmo, &nf, dg + cq, &nl1);
+  for (int e = tid; e < qw * qw; e += 256) {
+    const int j = e / qw, i = e - j * qw;
+    R[(int64_t)(cq + j) * ld + cq + i] = Gs[i * BLK_LD + j];
+    Rinv[(int64_t)(cq + j) * ld + cq + i] = Ri[i * BLK_LD + j];
   }
   if (tid == 0) {
-    nolive[p1] = nl1;
-    deadmask[p1] = dmo;
+    nolive[q] = nl1;
+    deadmask[q] = dmo;
     if (count_floors && nf && st) atomicAdd(&st->floored, nf);
+  }
+}
+
+// acc += sum_{m0 <= m < m1} A_m B_m for 64 x 64 blocks (column-major, ld; A_m
+// rows x cb_width(f, m), B_m cb_width(f, m) x cols, at A + m sa and B + m sb):
+// wave w the columns 16 w .., acc[t] the rows 16 t ..  The next pair of blocks
+// is in flight while one is multiplied, the sums stay in registers.
+__device__ __forceinline__ void blk_sum(Mfma<double>::acc_t (&acc)[4], const double* A, int64_t sa, const double* B,
+                                        int64_t sb, int64_t ld, int f, int rows, int cols, int m0, int m1, double* As,
+                                        double* Bs) {
+  typedef Mfma<double> MF;
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, jc = 16 * (threadIdx.x >> 6) + r;
+  double va[16], vb[16];
+  blk_load(va, A + m0 * sa, ld, rows, cb_width(f, m0));
+  blk_load(vb, B + m0 * sb, ld, cb_width(f, m0), cols);
+  for (int m = m0; m < m1; ++m) {
+    const int kw = cb_width(f, m);
+    __syncthreads();                       // earlier readers of As and Bs are done
+    blk_store(va, As, rows, kw);
+    blk_store(vb, Bs, kw, cols);
+    __syncthreads();
+    if (m + 1 < m1) {
+      blk_load(va, A + (m + 1) * sa, ld, rows, cb_width(f, m + 1));
+      blk_load(vb, B + (m + 1) * sb, ld, cb_width(f, m + 1), cols);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const double b = Bs[(4 * k + g) * BLK_LD + jc];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = MF::op(As[(16 * t + r) * BLK_LD + 4 * k + g], b, acc[t]);
+    }
   }
 }
 
@@ -2758,11 +2782,10 @@ __global__ __launch_bounds__(256) void k_cb_inv(const double* __restrict__ R, do
                                                 const uint64_t* __restrict__ deadmask, int32_t* __restrict__ dead,
                                                 const int32_t* __restrict__ stopb, int blk) {
   if (stopb && *stopb < blk) return;       // a speculative block after the stop
+  typedef Mfma<double> MF;
   if (stage == 2 && blockIdx.x == 0)
     for (int c = 64 + threadIdx.x; c < f; c += 256) dead[c] = (int32_t)((deadmask[c >> 6] >> (c & 63)) & 1ull);
-  constexpr int LD = SmallCfg<64>::LD;
-  __shared__ double Acc[64 * LD];
-  __shared__ double sm[GMM64S_LDS];
+  __shared__ double As[BLK_SIZE], Bs[BLK_SIZE];
   const int P = (f + 63) / 64;
   // this workgroup's pair (groups A = [a, a+L), C = [a+L, a+2L)) and block (i, j)
   int idx = blockIdx.x, a = 0, cw = 0;
@@ -2773,37 +2796,41 @@ __global__ __launch_bounds__(256) void k_cb_inv(const double* __restrict__ R, do
   }
   const int i = a + idx / cw, j = a + L + idx % cw;
   const int wi = cb_width(f, i), wj = cb_width(f, j), ci = 64 * i, cj = 64 * j;
-  if (stage != 1) {
-    // T_ij = sum_{a+L <= m <= j} R_im (R^{-1})_mj
-    for (int m = a + L; m <= j; ++m) {
-      const bool first = m == a + L;
-      gmm64s<true, true>(R + (int64_t)(64 * m) * ld + ci, ld, Rinv + (int64_t)cj * ld + 64 * m, ld, wi, wj,
-                         cb_width(f, m), sm,
-                         [&](int r, int c, double v) { Acc[r * LD + c] = first ? v : Acc[r * LD + c] + v; });
+  const int lane = threadIdx.x & 63, lr = lane & 15, g = lane >> 4, jc = 16 * (threadIdx.x >> 6) + lr;
+  typename MF::acc_t acc[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) acc[t] = MF::zero();
+  if (stage != 1)                          // T_ij = sum_{a+L <= m <= j} R_im (R^{-1})_mj
+    blk_sum(acc, R + ci, (int64_t)64 * ld, Rinv + (int64_t)cj * ld, 64, ld, f, wi, wj, a + L, j + 1, As, Bs);
+  else                                     // sum_{i <= k < a+L} (R^{-1})_ik T_kj, T from G
+    blk_sum(acc, Rinv + ci, (int64_t)64 * ld, G + (int64_t)cj * ld, 64, ld, f, wi, wj, i, a + L, As, Bs);
+  if (stage == 2) {
+    // L = 1, A = {i}: (R^{-1})_ii T_ij, T's rows already where the right
+    // operand wants them (row 4 e + g of a tile, column jc)
+    double va[16];
+    blk_load(va, Rinv + (int64_t)ci * ld + ci, ld, wi, wi);
+    __syncthreads();
+    blk_store(va, As, wi, wi);
+    __syncthreads();
+    typename MF::acc_t v[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      v[t] = MF::zero();
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[t] = MF::op(As[(16 * t + lr) * BLK_LD + 4 * k + g], acc[k >> 2][k & 3], v[t]);
     }
-    if (stage == 0) {
-      for (int e = threadIdx.x; e < wi * wj; e += 256) {
-        const int r = e / wj, c = e - r * wj;
-        G[(int64_t)(cj + c) * ld + ci + r] = Acc[r * LD + c];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = v[t];
+  }
+  double* out = stage == 0 ? G : Rinv;
+  if (jc < wj)
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = 16 * t + MF::row(g, e);
+        if (row < wi) out[(int64_t)(cj + jc) * ld + ci + row] = stage == 0 ? acc[t][e] : -acc[t][e];
       }
-      return;
-    }
-    // stage 2 (L = 1, A = {i}): (R^{-1})_ij = -(R^{-1})_ii T_ij, T still in LDS
-    gmm64s<true, false>(Rinv + (int64_t)ci * ld + ci, ld, Acc, LD, wi, wj, wi, sm,
-                        [&](int r, int c, double v) { Rinv[(int64_t)(cj + c) * ld + ci + r] = -v; });
-    return;
-  }
-  // (R^{-1})_ij = -sum_{i <= k < a+L} (R^{-1})_ik T_kj, T from G
-  for (int k = i; k < a + L; ++k) {
-    const bool first = k == i;
-    gmm64s<true, true>(Rinv + (int64_t)(64 * k) * ld + ci, ld, G + (int64_t)cj * ld + 64 * k, ld, wi, wj,
-                       cb_width(f, k), sm,
-                       [&](int r, int c, double v) { Acc[r * LD + c] = first ? v : Acc[r * LD + c] + v; });
-  }
-  for (int e = threadIdx.x; e < wi * wj; e += 256) {
-    const int r = e / wj, c = e - r * wj;
-    Rinv[(int64_t)(cj + c) * ld + ci + r] = -Acc[r * LD + c];
-  }
 }
 
 // The panel-blocked Cholesky with inverse (the k_cb_* steps) for two
