@@ -68,17 +68,27 @@ static_assert(TL_FOLD + TL_FOLD_N <= TILE_SQR, "basis carve inside the arena");
 
 // ---------------------------------------------------------------------------
 // Omega_j^T for the tile: rows j < f of column col0 + j, zero rows f..fpad-1.
+// Wave w fills rows w, w+4, ...; a lane makes four entries (one Philox block)
+// and stores them at once (ldk is a multiple of 4).  Bound by the chain of one
+// Philox block and two Box-Muller pairs, so two quads are in flight per lane.
 // ---------------------------------------------------------------------------
-__device__ void tile_omega(float* Om, int64_t ldk, int64_t n, int64_t col0, int f, int fpad,
-                           uint32_t k0, uint32_t k1) {
-  const int64_t nq = ldk / 4;
-  for (int64_t idx = threadIdx.x; idx < (int64_t)fpad * nq; idx += 256) {
-    const int j = (int)(idx / nq);
-    const int64_t q = idx - (int64_t)j * nq;
-    float z[4] = {0.f, 0.f, 0.f, 0.f};
-    if (j < f && 4 * q < n) omega4(k0, k1, q, col0 + j, z);
+__device__ __noinline__ void tile_omega(float* Om, int ldk, int n, int64_t col0, int f, int fpad, uint32_t k0,
+                                        uint32_t k1) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nq = ldk / 4;
+  auto quad = [&](int j, int q) {
+    float z[4];
+    omega4(k0, k1, q, col0 + j, z);
+    V4<float> o;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) Om[(int64_t)j * ldk + 4 * q + e] = (j < f && 4 * q + e < n) ? z[e] : 0.f;
+    for (int e = 0; e < 4; ++e) o.v[e] = (j < f && 4 * q + e < n) ? z[e] : 0.f;
+    return o;
+  };
+  for (int j = wv; j < fpad; j += 8) {             // fpad is a multiple of 16: j + 4 < fpad too
+    for (int q = lane; q < nq; q += 64) {
+      const V4<float> a = quad(j, q), b = quad(j + 4, q);
+      st4(Om + (int64_t)j * ldk + 4 * q, a);
+      st4(Om + (int64_t)(j + 4) * ldk + 4 * q, b);
+    }
   }
 }
 
@@ -471,84 +481,140 @@ __device__ __forceinline__ void tile_xty(const float* X, int64_t ldx, int wx, co
 
 // ---------------------------------------------------------------------------
 // Z (column-major, ldz, columns zoff .. zoff+ncols-1) = X (m x f, ldx) W
-// (f x ncols FP64, LDS or global, element (i,j) at i*ldw + j), f <= 4 KSM,
-// on f64 MFMA; each wave computes 16 whole rows at a time, so Z may alias X.
+// (f x ncols FP64 in LDS, element (i,j) at i*ldw + j), f <= 4 KSM, on f64
+// MFMA.  X lies in the slot: ldx = TILE_MAX rows can be read from every
+// column, whatever m.  One workgroup has the CU to itself, so what bounds
+// this is the number of memory instructions a wave waits for, not their
+// bytes: a wave takes 64 rows and a lane four consecutive ones, one 16-byte
+// load per column of X (row 4 r + v is row r of the v-th of four MFMA tiles,
+// which share every operand of W) and one 16-byte store per output.  All
+// loads of a panel come before its stores, so Z may alias X.  With the update
+// below split the same way, 1024 tiles of 64..1024 rows at ranks 5..80:
+// projections 150 -> 41 us a tile, applies about 220 -> 100 (16 rows a wave
+// and 4-byte guarded loads before), the batch 6.9 -> 4.65 ms.
 // ---------------------------------------------------------------------------
-template <int KSM = 16>
-__device__ __forceinline__ void tile_apply(const float* X, int64_t ldx, int64_t m, int f, const double* W,
-                                           int ldw, float* Z, int64_t ldz, int64_t zoff, int ncols) {
+typedef __attribute__((address_space(3))) const double* lds_cptr;
+template <int KSM>
+__device__ __noinline__ void tile_apply_t(const float* X, int64_t ldx, int m, int f, lds_cptr W, int ldw, float* Z,
+                                          int64_t ldz, int ncols) {
   typedef Mfma<double> MF;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
-  const int TT = (ncols + 15) / 16, KS = (f + 3) / 4;
-  for (int64_t row0 = 16 * (int64_t)wv; row0 < m; row0 += 64) {
-    const int64_t arow = row0 + r;
-    double a[KSM];
+  const int TT = (ncols + 15) / 16;
+  const bool vec = ((uintptr_t)Z % 16 == 0) && (ldz % 4 == 0);
+  for (int row0 = 64 * wv; row0 < m; row0 += 256) {
+    V4<float> a[KSM];
 #pragma unroll
-    for (int kk = 0; kk < KSM; ++kk) {
-      const int k = 4 * kk + g;
-      a[kk] = (kk < KS && k < f && arow < m) ? (double)X[(int64_t)k * ldx + arow] : 0.0;
-    }
+    for (int kk = 0; kk < KSM; ++kk) a[kk] = ld4(X + (int64_t)min(4 * kk + g, f - 1) * ldx + row0 + 4 * r);
+    loads_first();
     for (int u = 0; u < TT; ++u) {
-      MF::acc_t z = MF::zero();
-      const int col = 16 * u + r;
+      const int col = 16 * u + r, cw = min(col, ncols - 1);
+      MF::acc_t z[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) z[v] = MF::zero();
 #pragma unroll
       for (int kk = 0; kk < KSM; ++kk) {
-        if (kk < KS) {
-          const int k = 4 * kk + g;
-          const double b = (k < f && col < ncols) ? W[k * ldw + col] : 0.0;
-          z = MF::op(a[kk], b, z);
-        }
+        const int k = 4 * kk + g;
+        const double w = W[min(k, f - 1) * ldw + cw], b = k < f ? w : 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) z[v] = MF::op((double)a[kk].v[v], b, z[v]);
       }
       if (col < ncols) {
+        float* zc = Z + (int64_t)col * ldz;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int64_t row = row0 + MF::row(g, e);
-          if (row < m) Z[(zoff + col) * ldz + row] = (float)z[e];
+          const int row = row0 + 4 * MF::row(g, e);
+          if (vec && row + 3 < m) {
+            st4(zc + row, V4<float>{{(float)z[0][e], (float)z[1][e], (float)z[2][e], (float)z[3][e]}});
+          } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (row + v < m) zc[row + v] = (float)z[v][e];
+          }
         }
       }
     }
   }
   __syncthreads();
 }
+__device__ __forceinline__ void tile_apply(const float* X, int64_t ldx, int64_t m, int f, const double* W, int ldw,
+                                           float* Z, int64_t ldz, int64_t zoff, int ncols) {
+  lds_cptr Wl = (lds_cptr)W;
+  float* Zo = Z + zoff * ldz;
+  if (f <= 16) tile_apply_t<4>(X, ldx, (int)m, f, Wl, ldw, Zo, ldz, ncols);
+  else if (f <= 32) tile_apply_t<8>(X, ldx, (int)m, f, Wl, ldw, Zo, ldz, ncols);
+  else if (f <= 64) tile_apply_t<16>(X, ldx, (int)m, f, Wl, ldw, Zo, ldz, ncols);
+  else tile_apply_t<32>(X, ldx, (int)m, f, Wl, ldw, Zo, ldz, ncols);
+}
 
 // ---------------------------------------------------------------------------
 // Y (m x f) -= Q (m x w) W (w x f, FP64 in LDS, element (i,j) at i*ldw + j),
-// in FP32 on MFMA (the projection step of block Gram-Schmidt), f <= 64.
+// in FP32 on MFMA (the projection step of block Gram-Schmidt), f <= 16 TT.
+// Rows split as in tile_apply (Q and Y lie in the slot too); the columns of
+// Q come 16 at a time, one chunk ahead of its products.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void tile_update(float* Yb, int64_t ldy, const float* Q, int64_t ldq, int64_t m,
-                                            int w, int f, const double* W, int ldw) {
+template <int TT>
+__device__ __noinline__ void tile_update_t(float* Yb, int64_t ldy, const float* Q, int64_t ldq, int m, int w, int f,
+                                           lds_cptr W, int ldw) {
   typedef Mfma<float> MF;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
-  const int TT = (f + 15) / 16;
-  for (int64_t row0 = 16 * (int64_t)wv; row0 < m; row0 += 64) {
-    const int64_t arow = row0 + r;
-    MF::acc_t z[4];
+  for (int row0 = 64 * wv; row0 < m; row0 += 256) {
+    MF::acc_t z[4][TT];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) z[u] = MF::zero();
-    for (int k0 = 0; k0 < w; k0 += 4) {
-      const int k = k0 + g;
-      const float a = (k < w && arow < m) ? Q[(int64_t)k * ldq + arow] : 0.f;
+    for (int v = 0; v < 4; ++v)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (u < TT) {
-          const int col = 16 * u + r;
-          const float b = (k < w && col < f) ? (float)W[k * ldw + col] : 0.f;
-          z[u] = MF::op(a, b, z[u]);
+      for (int u = 0; u < TT; ++u) z[v][u] = MF::zero();
+    V4<float> a[4], an[4];
+    auto load = [&](V4<float>(&q)[4], int k0) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) q[s] = ld4(Q + (int64_t)min(k0 + 4 * s + g, w - 1) * ldq + row0 + 4 * r);
+    };
+    load(a, 0);
+    for (int k0 = 0; k0 < w; k0 += 16) {
+      load(an, k0 + 16);                           // past the last chunk: its last column again
+      loads_first();
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int k = k0 + 4 * s + g;
+#pragma unroll
+        for (int u = 0; u < TT; ++u) {
+          const float wk = (float)W[min(k, w - 1) * ldw + min(16 * u + r, f - 1)], b = k < w ? wk : 0.f;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) z[v][u] = MF::op(a[s].v[v], b, z[v][u]);
         }
       }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) a[s] = an[s];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < TT; ++u) {
       const int col = 16 * u + r;
-      if (u < TT && col < f) {
-        const int64_t row = row0 + 4 * g;
+      if (col < f) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (row + e < m) Yb[(int64_t)col * ldy + row + e] -= z[u][e];
+        for (int e = 0; e < 4; ++e) {
+          const int row = row0 + 4 * MF::row(g, e);
+          float* py = Yb + (int64_t)col * ldy + row;
+          if (row + 3 < m) {
+            V4<float> y = ld4(py);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) y.v[v] -= z[v][u][e];
+            st4(py, y);
+          } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (row + v < m) py[v] -= z[v][u][e];
+          }
+        }
       }
     }
   }
   __syncthreads();
+}
+__device__ __forceinline__ void tile_update(float* Yb, int64_t ldy, const float* Q, int64_t ldq, int64_t m, int w,
+                                            int f, const double* W, int ldw) {
+  lds_cptr Wl = (lds_cptr)W;
+  if (f <= 16) tile_update_t<1>(Yb, ldy, Q, ldq, (int)m, w, f, Wl, ldw);
+  else if (f <= 32) tile_update_t<2>(Yb, ldy, Q, ldq, (int)m, w, f, Wl, ldw);
+  else tile_update_t<4>(Yb, ldy, Q, ldq, (int)m, w, f, Wl, ldw);
 }
 
 // Cholesky with inverse of G (LDS, row-major ld F+1) for the smallest
@@ -662,7 +728,7 @@ __device__ __attribute__((noinline)) void tile_apply_big(const float* X, int64_t
     lds[i * 129 + j] = Wg[(int64_t)i * TileSlot::LB + j];
   }
   __syncthreads();
-  tile_apply<32>(X, ldx, m, f, lds, 129, Z, ldz, 0, ncols);
+  tile_apply(X, ldx, m, f, lds, 129, Z, ldz, 0, ncols);
 }
 
 // QR of M^T (M = R2 R1, or R2 when R1 is null; f x f, 64 < f <= 128):
@@ -712,7 +778,7 @@ __device__ void tile_factor(const TileDesc& td, float* slot, double* sdbl, doubl
     const int f = (int)((n - col0) < b ? (n - col0) : b);
     const int fpad = ((f + 15) / 16) * 16;
     ++blocks;
-    tile_omega(Om, ldk, n, col0, f, fpad, k0, k1);
+    tile_omega(Om, (int)ldk, (int)n, col0, f, fpad, k0, k1);
     __syncthreads();
     double* ss = (col0 == 0) ? &scal[0] : nullptr;
     // Y = A_o Omega_j (A_o the oriented tile, m x n)
