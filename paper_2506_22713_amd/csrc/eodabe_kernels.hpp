@@ -2449,13 +2449,39 @@ __device__ int chol_inv128(const double* G, int ldg, int f, double* R, double* R
   return nf1 + nf2;
 }
 
+// chol_tame after chol_inv128's first pass over G: R^{-1} row-major, ld (lds:
+// 4 doubles).
+__device__ __forceinline__ bool chol128_tame(const double* G, int ld, const double* Ri, int f, double* lds) {
+  double s = 0.0;
+  for (int i0 = threadIdx.x >> 6; i0 < f; i0 += 32) {       // 8 rows of this wave's at a time
+    double d[8], a[8], b[8];
+    const int j = threadIdx.x & 63;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int i = min(i0 + 4 * q, f - 1);
+      d[q] = G[(int64_t)i * ld + i];
+      a[q] = Ri[(int64_t)i * ld + j];
+      b[q] = Ri[(int64_t)i * ld + min(j + 64, f - 1)];
+    }
+    loads_first();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int i = i0 + 4 * q;
+      if (i < f && i <= j) s = fma(d[q] * a[q], a[q], s);
+      if (i < f && i <= j + 64 && j + 64 < f) s = fma(d[q] * b[q], b[q], s);
+    }
+  }
+  return chol_tame_sum(s, f, lds);
+}
+
 // ---------------------------------------------------------------------------
 // QR of M^T (M = R2 R1, or M = R2 when R1 is null; f x f, 64 < f <= 128) by
 // CholeskyQR2 in FP64 on one workgroup, with the matrices in global memory:
 // G = M M^T = Rh1^T Rh1, Z1 = M^T Rh1^{-1}, Z1^T Z1 = Rh2^T Rh2, Qh =
 // Z1 Rh2^{-1}, Rh = Rh2 Rh1 (first Cholesky floored, the second kills what
-// stays non-positive).  R1, R2: element (i,j) at j*ldi + i (CMI) or
-// i*ldi + j.  Qh and Rh go out through put_q(i, j, v) and put_r(i, j, v).
+// stays non-positive; the second pass only where chol_tame asks for it, the
+// data being FP32).  R1, R2: element (i,j) at j*ldi + i (CMI) or i*ldi + j.
+// Qh and Rh go out through put_q(i, j, v) and put_r(i, j, v).
 // scr: 7 buffers of 128 x 128 doubles.  lds: CHOL128_LDS doubles.  Returns
 // the number of floored pivots.
 // ---------------------------------------------------------------------------
@@ -2484,6 +2510,12 @@ __device__ int small_qr_mid(double* lds, const double* R1g, const double* R2g, i
   __syncthreads();
   uint64_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
   int nf = chol_inv128(G, LB, f, H1, H1i, lds, 0ull, 0ull, 1, &a0, &a1);
+  if (nf == 0 && (a0 | a1) == 0ull && chol128_tame(G, LB, H1i, f, lds)) {     // Qh = Z1, Rh = Rh1
+    gmm64<true, false>(M, LB, H1i, LB, f, f, f, put_q);
+    for (int idx = threadIdx.x; idx < f * f; idx += 256) put_r(idx / f, idx % f, H1[idx / f * LB + idx % f]);
+    __syncthreads();
+    return 0;
+  }
   gmm64<true, false>(M, LB, H1i, LB, f, f, f, [&](int i, int j, double v) { Z1[i * LB + j] = v; });
   __syncthreads();
   gmm64<true, false>(Z1, LB, Z1, LB, f, f, f, [&](int i, int j, double v) { G[i * LB + j] = v; });

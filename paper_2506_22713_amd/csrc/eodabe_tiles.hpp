@@ -629,10 +629,29 @@ __device__ __noinline__ void tile_chol(double* Gs, double* Ri, double* work, dou
   else chol_inv<64>(Gs, Ri, work, dgs, f, dmask_in, first_pass, dmask_out, nfl);
 }
 
+// Store the leading f x f block of an LDS row-major matrix (ld) to global
+// (element (i,j) at j*f + i).
+__device__ void tile_store_small(const double* in, int ld, int f, double* Mg) {
+  for (int idx = threadIdx.x; idx < f * f; idx += 256) {
+    const int j = idx / f, i = idx - j * f;
+    Mg[idx] = in[i * ld + j];
+  }
+  __syncthreads();
+}
+
+// chol_tame after tile_chol's first pass of f columns (red: 4 doubles of LDS)
+__device__ __noinline__ bool tile_tame(const double* Ri, const double* dgs, int f, double* red) {
+  const int F = chol_width(f);
+  if (F == 16) return chol_tame<16>(Ri, dgs, f, red);
+  if (F == 32) return chol_tame<32>(Ri, dgs, f, red);
+  return chol_tame<64>(Ri, dgs, f, red);
+}
+
 // ---------------------------------------------------------------------------
 // QR of M^T (M = R2 R1, or R2 when R1 is null; f x f FP64 in global memory,
 // element (i,j) at j*f + i) by CholeskyQR2 in FP64 on the LDS arena (as the
-// closing QR of the single-matrix path).  Qh -> Qout, Rh -> Dout (FP64,
+// closing QR of the single-matrix path; the second pass where chol_tame asks
+// for it).  Qh -> Qout, Rh -> Dout (FP64,
 // both element (i,j) at j*f + i).
 // ---------------------------------------------------------------------------
 template <int F>
@@ -664,6 +683,14 @@ __device__ void tile_small_qr(double* lds, const double* R1g, const double* R2g,
   uint64_t dm1, dm2;
   int nf1, nf2;
   chol_inv<F>(B1, B2, work, dgs, f, 0ull, 1, &dm1, &nf1);
+  if (dm1 == 0ull && nf1 == 0 && chol_tame<F>(B2, dgs, f, work)) {
+    lds_gemm<F, true, false>(B0, B2, [&](int i, int jj, double v) {
+      if (i < f && jj < f) Qout[(int64_t)jj * f + i] = v;
+    });
+    tile_store_small(B1, LD, f, Dout);
+    *nfloor = 0;
+    return;
+  }
   lds_gemm<F, true, false>(B0, B2, [&](int i, int jj, double v) { B3[i * LD + jj] = v; });
   __syncthreads();
   lds_gemm<F, true, false>(B3, B3, [&](int i, int jj, double v) { B0[i * LD + jj] = v; });
@@ -693,16 +720,6 @@ __device__ void tile_load_small(const double* Mg, int f, double* out, int ld) {
   }
   __syncthreads();
 }
-// Store the leading f x f block of an LDS row-major matrix (ld) to global
-// (element (i,j) at j*f + i).
-__device__ void tile_store_small(const double* in, int ld, int f, double* Mg) {
-  for (int idx = threadIdx.x; idx < f * f; idx += 256) {
-    const int j = idx / f, i = idx - j * f;
-    Mg[idx] = in[i * ld + j];
-  }
-  __syncthreads();
-}
-
 // ---------------------------------------------------------------------------
 // Ranks 65..128: FP64 matrices row-major with leading dimension LB in the
 // slot (L2-resident); the LDS arena stages the right-hand factors.
@@ -729,6 +746,13 @@ __device__ __attribute__((noinline)) void tile_apply_big(const float* X, int64_t
   }
   __syncthreads();
   tile_apply(X, ldx, m, f, lds, 129, Z, ldz, 0, ncols);
+}
+
+// chol_inv128 on row-major matrices of leading dimension LB.
+__device__ __attribute__((noinline)) int tile_chol128(const double* G, int f, double* R, double* Rinv, double* lds,
+                                                      uint64_t dm0, uint64_t dm1, int first_pass, uint64_t* o0,
+                                                      uint64_t* o1) {
+  return chol_inv128(G, TileSlot::LB, f, R, Rinv, lds, dm0, dm1, first_pass, o0, o1);
 }
 
 // QR of M^T (M = R2 R1, or R2 when R1 is null; f x f, 64 < f <= 128):
@@ -865,15 +889,20 @@ __device__ void tile_factor(const TileDesc& td, float* slot, double* sdbl, doubl
       tile_xty(Ct, LD, ri, Ct, LD, ri, n, Gs, LDG, fold);
       tile_chol(Gs, Ri, work, dgs, ri, 0ull, 1, &dm1, &nf);
       tile_store_small(Gs, LDG, ri, sdbl + TileSlot::R1);
-      tile_apply(Ct, LD, n, ri, Ri, LDG, Ct, LD, 0, ri);
-      tile_xty(Ct, LD, ri, Ct, LD, ri, n, Gs, LDG, fold);
-      tile_chol(Gs, Ri, work, dgs, ri, dm1, 0, &dm2, &nf);
-      tile_store_small(Gs, LDG, ri, sdbl + TileSlot::R2);
-      tile_apply(Ct, LD, n, ri, Ri, LDG, Vdst, ldv, 0, ri);
+      const bool tame = dm1 == 0ull && nf == 0 && tile_tame(Ri, dgs, ri, work);
+      if (tame) {                                   // one pass: V = C^T R1^{-1}, R2 = I
+        tile_apply(Ct, LD, n, ri, Ri, LDG, Vdst, ldv, 0, ri);
+      } else {
+        tile_apply(Ct, LD, n, ri, Ri, LDG, Ct, LD, 0, ri);
+        tile_xty(Ct, LD, ri, Ct, LD, ri, n, Gs, LDG, fold);
+        tile_chol(Gs, Ri, work, dgs, ri, dm1, 0, &dm2, &nf);
+        tile_store_small(Gs, LDG, ri, sdbl + TileSlot::R2);
+        tile_apply(Ct, LD, n, ri, Ri, LDG, Vdst, ldv, 0, ri);
+      }
       // a11: (R2 R1)^T = Qh Rh on the arena
       int nfq = 0;
-      tile_small_qr_any(lds, sdbl + TileSlot::R1, sdbl + TileSlot::R2, ri, sdbl + TileSlot::QH,
-                        sdbl + TileSlot::DH, &nfq);
+      tile_small_qr_any(lds, tame ? nullptr : sdbl + TileSlot::R1, sdbl + (tame ? TileSlot::R1 : TileSlot::R2), ri,
+                        sdbl + TileSlot::QH, sdbl + TileSlot::DH, &nfq);
       // U_hat = Q Qh (m x r)
       const int LDW = chol_width(ri) + 1;
       tile_load_small(sdbl + TileSlot::QH, ri, Gs, LDW);
@@ -915,12 +944,17 @@ __device__ void tile_factor(const TileDesc& td, float* slot, double* sdbl, doubl
       double* scr = dd + 9 * B2;                    // 7 buffers
       uint64_t d10 = 0, d11 = 0, d20 = 0, d21 = 0;
       tile_gram_big(Ct, LD, ri, n, Gg, fold);
-      chol_inv128(Gg, LB, ri, R1g, R1i, lds, 0ull, 0ull, 1, &d10, &d11);
-      tile_apply_big(Ct, LD, n, ri, R1i, lds, Ct, LD, ri);
-      tile_gram_big(Ct, LD, ri, n, Gg, fold);
-      chol_inv128(Gg, LB, ri, R2g, R2i, lds, d10, d11, 0, &d20, &d21);
-      tile_apply_big(Ct, LD, n, ri, R2i, lds, Vdst, ldv, ri);
-      tile_small_qr_big(lds, R1g, R2g, ri, Qh, Rh, scr);
+      const int nf1 = tile_chol128(Gg, ri, R1g, R1i, lds, 0ull, 0ull, 1, &d10, &d11);
+      if (nf1 == 0 && (d10 | d11) == 0ull && chol128_tame(Gg, LB, R1i, ri, lds)) {
+        tile_apply_big(Ct, LD, n, ri, R1i, lds, Vdst, ldv, ri);
+        tile_small_qr_big(lds, nullptr, R1g, ri, Qh, Rh, scr);
+      } else {
+        tile_apply_big(Ct, LD, n, ri, R1i, lds, Ct, LD, ri);
+        tile_gram_big(Ct, LD, ri, n, Gg, fold);
+        tile_chol128(Gg, ri, R2g, R2i, lds, d10, d11, 0, &d20, &d21);
+        tile_apply_big(Ct, LD, n, ri, R2i, lds, Vdst, ldv, ri);
+        tile_small_qr_big(lds, R1g, R2g, ri, Qh, Rh, scr);
+      }
       const double* Rc = Rh;
       if (!tr) {
         tile_apply_big(Q, LD, m, ri, Qh, lds, Ut, td.h, ri);                   // U (h x r)
