@@ -1534,6 +1534,7 @@ struct BatchWS {
   TileDesc* descs;
   TileResult* res;
   uint32_t* queue;
+  float* omt;           // Omega^T shared by the tiles (TILE_QW x TILE_MAX)
   char* slots;
   void* fws;            // workspace of the regular path (tiles above the in-kernel rank cap)
   size_t fws_bytes;
@@ -1545,6 +1546,7 @@ BatchWS batch_carve(void* base, eodabe_ctx* ctx, int ntiles) {
   b.descs = c.take<TileDesc>(std::max(ntiles, 1));
   b.res = c.take<TileResult>(std::max(ntiles, 1));
   b.queue = c.take<uint32_t>(64);
+  b.omt = c.take<float>((int64_t)TILE_QW * TILE_MAX);
   b.slots = c.take<char>((int64_t)tile_slots(ctx) * TileSlot::BYTES);
   eodabe_opts o = ctx->o;
   o.a_dtype = EODABE_F32;
@@ -1567,7 +1569,7 @@ int tile_block(const eodabe_ctx* ctx, int64_t h, int64_t w) {
   return std::max(1, std::min(b, TILE_BMAX));
 }
 
-// Enqueue the batch on the private stream (descriptor copy, queue reset,
+// Enqueue the batch on the private stream (descriptor copy, test matrix and queue reset,
 // persistent kernel, result copy), captured once into a hipGraph per key and
 // replayed afterwards; the host copies read the pinned staging buffer when
 // they execute, so new descriptors need no new capture.
@@ -1579,9 +1581,9 @@ int batch_launch(eodabe_ctx* ctx, const BatchWS& b, int ntiles, int grid, float*
   const uint32_t k0 = (uint32_t)(ctx->o.seed & 0xffffffffu), k1 = (uint32_t)(ctx->o.seed >> 32);
   auto enqueue = [&]() -> int {
     HIPCHK(hipMemcpyAsync(b.descs, hd, (size_t)ntiles * sizeof(TileDesc), hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_zero<uint32_t>, dim3(1), dim3(64), 0, st, b.queue, (int64_t)64);
+    hipLaunchKernelGGL(k_tile_begin, dim3(TILE_QW), dim3(256), 0, st, b.omt, b.queue, k0, k1);
     hipLaunchKernelGGL(k_tiles, dim3(grid), dim3(256), 0, st, b.descs, ntiles, b.queue, b.slots, pool,
-                       b.res, tol, k0, k1);
+                       b.res, tol, (const float*)b.omt);
     LAUNCHCHK();
     HIPCHK(hipMemcpyAsync(hr, b.res, (size_t)ntiles * sizeof(TileResult), hipMemcpyDeviceToHost, st));
     return 0;

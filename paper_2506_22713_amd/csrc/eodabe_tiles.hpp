@@ -16,6 +16,11 @@ constexpr int TILE_RMAX = 128;                 // rank finished inside the kerne
 constexpr int TILE_BMAX = 64;                  // largest block width
 constexpr int TILE_QW = TILE_RMAX + TILE_BMAX; // basis columns held (rank + one block)
 
+// LDS operands of the routines kept out of line: a plain pointer would make
+// every access a flat one.
+typedef __attribute__((address_space(3))) double* lds_ptr;
+typedef __attribute__((address_space(3))) const double* lds_cptr;
+
 enum TileStatus : int32_t { TS_OK = 0, TS_RANK = 1, TS_NONFINITE = 2, TS_CAPACITY = 3 };
 
 struct TileDesc {
@@ -37,8 +42,7 @@ struct TileResult {
 // Scratch of one workgroup (floats unless marked).
 struct TileSlot {
   static constexpr int64_t LD = TILE_MAX;                // leading dimension of tall buffers
-  static constexpr int64_t OM = 0;                       // Omega^T rows, TILE_BMAX x LD
-  static constexpr int64_t Y = OM + TILE_BMAX * LD;      // block, LD x TILE_BMAX
+  static constexpr int64_t Y = 0;                        // block, LD x TILE_BMAX
   static constexpr int64_t Q = Y + LD * TILE_BMAX;       // basis, LD x TILE_QW
   static constexpr int64_t CT = Q + LD * TILE_QW;        // C^T, LD x TILE_RMAX
   static constexpr int64_t VP = CT + LD * TILE_RMAX;     // V' of a wide tile, LD x TILE_RMAX
@@ -67,29 +71,21 @@ static_assert(CHOL128_LDS <= TILE_SQR && 128 * 129 <= TILE_SQR, "wide-rank closi
 static_assert(TL_FOLD + TL_FOLD_N <= TILE_SQR, "basis carve inside the arena");
 
 // ---------------------------------------------------------------------------
-// Omega_j^T for the tile: rows j < f of column col0 + j, zero rows f..fpad-1.
-// Wave w fills rows w, w+4, ...; a lane makes four entries (one Philox block)
-// and stores them at once (ldk is a multiple of 4).  Bound by the chain of one
-// Philox block and two Box-Muller pairs, so two quads are in flight per lane.
+// First launch of a batch: Omega^T (row c, TILE_MAX entries, is column c of
+// the test matrix: a pure function of seed, row and column, so the tiles of a
+// batch share it), and the reset of the work queue.  A block of a tile starts
+// at a column <= TILE_RMAX and has at most TILE_BMAX columns: TILE_QW columns
+// reach every one.  Made by each tile for itself it took 42 of a tile's 730 us
+// (the Box-Muller pairs are evaluated in FP64).  Grid: TILE_QW x 256 threads.
 // ---------------------------------------------------------------------------
-__device__ __noinline__ void tile_omega(float* Om, int ldk, int n, int64_t col0, int f, int fpad, uint32_t k0,
-                                        uint32_t k1) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nq = ldk / 4;
-  auto quad = [&](int j, int q) {
-    float z[4];
-    omega4(k0, k1, q, col0 + j, z);
-    V4<float> o;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o.v[e] = (j < f && 4 * q + e < n) ? z[e] : 0.f;
-    return o;
-  };
-  for (int j = wv; j < fpad; j += 8) {             // fpad is a multiple of 16: j + 4 < fpad too
-    for (int q = lane; q < nq; q += 64) {
-      const V4<float> a = quad(j, q), b = quad(j + 4, q);
-      st4(Om + (int64_t)j * ldk + 4 * q, a);
-      st4(Om + (int64_t)(j + 4) * ldk + 4 * q, b);
-    }
-  }
+__global__ __launch_bounds__(256) void k_tile_begin(float* __restrict__ omt, uint32_t* __restrict__ queue,
+                                                    uint32_t k0, uint32_t k1) {
+  static_assert(TILE_MAX == 4 * 256, "one quad per thread");
+  const int c = blockIdx.x, q = threadIdx.x;
+  if (c == 0 && q < 64) queue[q] = 0u;
+  V4<float> o;
+  omega4(k0, k1, q, c, o.v);
+  st4(omt + (int64_t)c * TILE_MAX + 4 * q, o);
 }
 
 // ---------------------------------------------------------------------------
@@ -388,15 +384,16 @@ __device__ __forceinline__ void tile_colprod(const float* A, int64_t lda, int64_
 // m x wx and Y m x wy column-major (ldx, ldy multiples of 4, 16-byte aligned
 // columns; columns beyond wx / wy read as zero), wx, wy <= 64.  Waves split
 // the rows (16-row steps, interleaved) and accumulate every 16 x 16 tile of
-// the product at once; the partial tiles are folded in wave order through
-// red (16 * 256 doubles, disjoint from out).  TX, TY: tile counts of X and
+// the product at once; the partial tiles are folded through red (16 * 256
+// doubles, disjoint from out): up to 4 tiles all waves at once, up to 8 by
+// pairs, more in wave order.  TX, TY: tile counts of X and
 // Y; full steps load without branches (clamped columns zeroed by a select).
 // ---------------------------------------------------------------------------
 template <int TX, int TY>
 __device__ __noinline__ void tile_xty_t(const float* X, int64_t ldx, int wx, const float* Yb, int64_t ldy,
-                                        int wy, int64_t m, double* out, int ldo, double* red) {
+                                        int wy, int64_t m, double* out, int ldo, lds_ptr red) {
   typedef Mfma<double> MF;
-  constexpr int PF = 2;
+  constexpr int PF = TX + TY <= 4 ? 4 : 2;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
   MF::acc_t acc[TX][TY];
 #pragma unroll
@@ -487,32 +484,36 @@ __device__ __noinline__ void tile_xty_t(const float* X, int64_t ldx, int wx, con
       step(xt, yt);
     }
   }
-  // fold the waves in order
-  for (int w = 0; w < 4; ++w) {
-    if (wv == w) {
+  constexpr int NT = TX * TY * 256, S = TX * TY <= 4 ? 4 : (TX * TY <= 8 ? 2 : 1);   // waves per round
+#pragma unroll
+  for (int w = 0; w < 4; w += S) {
+    if (S == 4 || wv / S == w / S) {
 #pragma unroll
       for (int t = 0; t < TX; ++t)
 #pragma unroll
         for (int u = 0; u < TY; ++u)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            double* q = &red[((t * TY + u) * 4 + e) * 64 + lane];
+            lds_ptr q = red + (wv % S) * NT + ((t * TY + u) * 4 + e) * 64 + lane;
             *q = (w == 0) ? acc[t][u][e] : *q + acc[t][u][e];
           }
     }
     __syncthreads();
   }
-  for (int idx = threadIdx.x; idx < TX * TY * 256; idx += 256) {
-    const int l = idx & 63, e = (idx >> 6) & 3, tu = idx >> 8;
-    const int t = tu / TY, u = tu - t * TY;
-    const int i = 16 * t + MF::row(l >> 4, e), j = 16 * u + (l & 15);
-    if (i < wx && j < wy) out[i * ldo + j] = red[idx];
+#pragma unroll
+  for (int tu = 0; tu < TX * TY; ++tu) {
+    const int t = tu / TY, u = tu % TY, idx = tu * 256 + threadIdx.x, e = threadIdx.x >> 6;
+    const int i = 16 * t + MF::row(lane >> 4, e), j = 16 * u + (lane & 15);
+    double v = red[idx];
+#pragma unroll
+    for (int w = 1; w < S; ++w) v += red[idx + w * NT];
+    if (i < wx && j < wy) out[i * ldo + j] = v;
   }
   __syncthreads();
 }
 template <int TX>
 __device__ __forceinline__ void tile_xty_y(const float* X, int64_t ldx, int wx, const float* Yb, int64_t ldy,
-                                           int wy, int64_t m, double* out, int ldo, double* red) {
+                                           int wy, int64_t m, double* out, int ldo, lds_ptr red) {
   const int ty = (wy + 15) / 16;
   if (ty <= 1) tile_xty_t<TX, 1>(X, ldx, wx, Yb, ldy, wy, m, out, ldo, red);
   else if (ty == 2) tile_xty_t<TX, 2>(X, ldx, wx, Yb, ldy, wy, m, out, ldo, red);
@@ -520,7 +521,8 @@ __device__ __forceinline__ void tile_xty_y(const float* X, int64_t ldx, int wx, 
   else tile_xty_t<TX, 4>(X, ldx, wx, Yb, ldy, wy, m, out, ldo, red);
 }
 __device__ __forceinline__ void tile_xty(const float* X, int64_t ldx, int wx, const float* Yb, int64_t ldy,
-                                         int wy, int64_t m, double* out, int ldo, double* red) {
+                                         int wy, int64_t m, double* out, int ldo, double* red_) {
+  lds_ptr red = (lds_ptr)red_;
   const int tx = (wx + 15) / 16;
   if (tx <= 1) tile_xty_y<1>(X, ldx, wx, Yb, ldy, wy, m, out, ldo, red);
   else if (tx == 2) tile_xty_y<2>(X, ldx, wx, Yb, ldy, wy, m, out, ldo, red);
@@ -542,7 +544,6 @@ __device__ __forceinline__ void tile_xty(const float* X, int64_t ldx, int wx, co
 // projections 150 -> 41 us a tile, applies about 220 -> 100 (16 rows a wave
 // and 4-byte guarded loads before), the batch 6.9 -> 4.65 ms.
 // ---------------------------------------------------------------------------
-typedef __attribute__((address_space(3))) const double* lds_cptr;
 template <int KSM>
 __device__ __noinline__ void tile_apply_t(const float* X, int64_t ldx, int m, int f, lds_cptr W, int ldw, float* Z,
                                           int64_t ldz, int ncols) {
@@ -822,8 +823,8 @@ __device__ __attribute__((noinline)) void tile_small_qr_big(double* lds, const d
 // of a tall tile with the roles of the routines exchanged; the core is
 // then re-triangularised.
 // ---------------------------------------------------------------------------
-__device__ void tile_factor(const TileDesc& td, float* slot, double* sdbl, double* lds, float* out_pool,
-                            TileResult* res, double tol, uint32_t k0, uint32_t k1) {
+__device__ void tile_factor(const TileDesc& td, const float* omt, float* slot, double* sdbl, double* lds, float* out_pool,
+                            TileResult* res, double tol) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   constexpr int64_t LD = TileSlot::LD;
   const bool tr = td.h < td.w;
@@ -838,10 +839,9 @@ __device__ void tile_factor(const TileDesc& td, float* slot, double* sdbl, doubl
   double* fold = lds + TL_FOLD;                      // wave fold buffer of the reductions
   double* scal = lds + TILE_SQR;                     // [0] ||A||^2, [1..64] R1 diagonal
   __shared__ int s_keep, s_stop;
-  float* Om = slot + TileSlot::OM;
   float* Yb = slot + TileSlot::Y;
   float* Q = slot + TileSlot::Q;
-  const int64_t ldk = ((n + 3) / 4) * 4;
+  const int64_t ldk = TILE_MAX;                      // rows of Omega^T
   const int b = td.b;
   int64_t wcols = 0;
   int blocks = 0;
@@ -849,10 +849,8 @@ __device__ void tile_factor(const TileDesc& td, float* slot, double* sdbl, doubl
   double eps = 0.0;
   for (int64_t col0 = 0; col0 < n; col0 += b) {
     const int f = (int)((n - col0) < b ? (n - col0) : b);
-    const int fpad = ((f + 15) / 16) * 16;
     ++blocks;
-    tile_omega(Om, (int)ldk, (int)n, col0, f, fpad, k0, k1);
-    __syncthreads();
+    const float* Om = omt + col0 * ldk;
     double* ss = (col0 == 0) ? &scal[0] : nullptr;
     // Y = A_o Omega_j (A_o the oriented tile, m x n)
     if (tr && al) tile_colprod<true>(td.A, td.lda, n, m, Om, ldk, f, Yb, LD, ss, fold);
@@ -1038,7 +1036,7 @@ __device__ void tile_factor(const TileDesc& td, float* slot, double* sdbl, doubl
 __global__ __launch_bounds__(256) void k_tiles(const TileDesc* __restrict__ descs, int ntiles,
                                                uint32_t* __restrict__ queue, char* __restrict__ scratch,
                                                float* __restrict__ out_pool, TileResult* __restrict__ res,
-                                               double tol, uint32_t k0, uint32_t k1) {
+                                               double tol, const float* __restrict__ omt) {
   __shared__ __align__(16) double lds[TILE_LDS];
   __shared__ int s_t;
   float* slot = reinterpret_cast<float*>(scratch + (int64_t)blockIdx.x * TileSlot::BYTES);
@@ -1049,7 +1047,7 @@ __global__ __launch_bounds__(256) void k_tiles(const TileDesc* __restrict__ desc
     const int t = s_t;
     __syncthreads();
     if (t >= ntiles) break;
-    tile_factor(descs[t], slot, sdbl, lds, out_pool, res, tol, k0, k1);
+    tile_factor(descs[t], omt, slot, sdbl, lds, out_pool, res, tol);
   }
 }
 
