@@ -2874,6 +2874,10 @@ __global__ __launch_bounds__(256) void k_cb_inv(const double* __restrict__ R, do
 // -R11^{-1} (R12 R22^{-1}).  The same R and R^{-1} as the separate launches
 // up to rounding order; G (column-major, ld) is not modified.  Outputs as
 // k_cb_*: R, R^{-1} column-major (ld), per-column dead flags.
+// Bound by one chain of two factorizations on one CU: the operands come in one
+// round trip, wave w carries columns 16 w .. of the products between the
+// factorizations in registers (triangular factors skip their zero half), and
+// stores run along the columns.
 __global__ __launch_bounds__(256) void k_chol2p(const double* __restrict__ G, int ld, int f,
                                                 double* __restrict__ R, double* __restrict__ Rinv,
                                                 int32_t* __restrict__ dead, int first_pass, int fresh, State* st,
@@ -2881,94 +2885,115 @@ __global__ __launch_bounds__(256) void k_chol2p(const double* __restrict__ G, in
                                                 int32_t* __restrict__ one_pass, double* __restrict__ R2one) {
   if (stopb && *stopb < blk) return;       // a speculative block after the stop, or a second pass not needed
   typedef SmallCfg<64> S;
+  typedef Mfma<double> MF;
   constexpr int LD = S::LD;
+  static_assert(LD == BLK_LD, "one layout for blocks and factors");
   __shared__ double A[S::SIZE], B[S::SIZE], C[S::SIZE], D[S::SIZE], work[24 * 64], dgs[64], dg0[64], dg1[64];
-  const int tid = threadIdx.x, w1 = f - 64;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lr = lane & 15, g = lane >> 4;
+  const int w1 = f - 64, jc = 16 * wv + lr;  // jc: this lane's column of the wave's 16
+  int d0 = 0, d1 = 0;
+  if (!fresh) {
+    d0 = dead[lane];
+    d1 = dead[64 + min(lane, w1 - 1)];
+  }
+  double va[16], vc[16], vg;
+  blk_load(va, G, ld, 64, 64);
+  blk_load(vc, G + (int64_t)64 * ld, ld, 64, w1);
+  vg = G[(int64_t)(64 + min(lane, w1 - 1)) * (ld + 1)];
+  typename MF::acc_t acc[4];               // G22: rows 16 t .. of column jc
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      acc[t][e] = G[(int64_t)(64 + min(jc, w1 - 1)) * ld + 64 + min(16 * t + MF::row(g, e), w1 - 1)];
+  loads_first();
+  const uint64_t dm0 = __ballot(d0 != 0), dm1 = __ballot(d1 != 0 && lane < w1);
+  blk_store(va, A, 64, 64);
+  blk_store(vc, C, 64, w1);
+  if (wv == 0) dg1[lane] = lane < w1 ? vg : 0.0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q)
+    if (lane == wv + 4 * q) dg0[lane] = va[q];
   // lower-left blocks of R and R^{-1}
   for (int idx = tid; idx < w1 * 64; idx += 256) {
-    const int i = 64 + idx / 64, j = idx % 64;
+    const int j = idx / w1, i = 64 + idx - j * w1;
     R[(int64_t)j * ld + i] = 0.0;
     Rinv[(int64_t)j * ld + i] = 0.0;
-  }
-  uint64_t dm0 = 0, dm1 = 0;
-  if (!fresh) {
-    for (int c = 0; c < 64; ++c) dm0 |= (uint64_t)(dead[c] != 0) << c;
-    for (int c = 0; c < w1; ++c) dm1 |= (uint64_t)(dead[64 + c] != 0) << c;
-  }
-  // G11 -> A, G12 -> C, G22 -> D (row-major, zero padded); each thread's
-  // loads in flight before its stores
-  {
-    constexpr int NQ = 64 * 64 / 256;
-    double va[NQ], vc[NQ], vd[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int idx = tid + 256 * q, j = idx / 64, i = idx % 64;      // element (i, j)
-      va[q] = G[(int64_t)j * ld + i];
-      vc[q] = j < w1 ? G[(int64_t)(64 + j) * ld + i] : 0.0;
-      vd[q] = (i < w1 && j < w1) ? G[(int64_t)(64 + j) * ld + 64 + i] : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int idx = tid + 256 * q, j = idx / 64, i = idx % 64;
-      A[i * LD + j] = va[q];
-      C[i * LD + j] = vc[q];
-      D[i * LD + j] = vd[q];
-      if (i == j) {
-        dg0[i] = va[q];
-        dg1[i] = vd[q];
-      }
-    }
   }
   __syncthreads();
   uint64_t dmo0 = 0, nl0 = 0, dmo1 = 0, nl1 = 0;
   int nf0 = 0, nf1 = 0;
   chol_inv<64>(A, B, work, dgs, 64, dm0, first_pass, &dmo0, &nf0, nullptr, &nl0);
-  for (int idx = tid; idx < 64 * 64; idx += 256) {
-    const int i = idx / 64, j = idx % 64;
-    R[(int64_t)j * ld + i] = A[i * LD + j];
-    Rinv[(int64_t)j * ld + i] = B[i * LD + j];
+  // R12 = R11^{-T} G12, masked, in place
+  blk_rpanel(B, C, nl0, (dm1 >> jc) & 1ull);
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int j = wv + 4 * q;
+    R[(int64_t)j * ld + lane] = A[lane * LD + j];
+    Rinv[(int64_t)j * ld + lane] = B[lane * LD + j];
   }
-  __syncthreads();
-  // R12 = R11^{-T} G12, masked, into A (and R)
-  lds_gemm<64, true, false>(B, C, [&](int i, int j, double v) {
-    const bool z = j >= w1 || ((nl0 >> i) & 1ull) || ((dm1 >> j) & 1ull);
-    A[i * LD + j] = z ? 0.0 : v;
-    if (j < w1) R[(int64_t)(64 + j) * ld + i] = z ? 0.0 : v;
-  });
   __syncthreads();
   // S22 = G22 - R12^T R12
-  lds_gemm<64, true, false>(A, A, [&](int i, int j, double v) {
-    if (i < w1 && j < w1) D[i * LD + j] -= v;
-  });
-  __syncthreads();
-  chol_inv<64>(D, C, work, dgs, w1, dm1, first_pass, &dmo1, &nf1, dg1, &nl1);
-  for (int idx = tid; idx < w1 * w1; idx += 256) {
-    const int i = idx / w1, j = idx % w1;
-    R[(int64_t)(64 + j) * ld + 64 + i] = D[i * LD + j];
-    Rinv[(int64_t)(64 + j) * ld + 64 + i] = C[i * LD + j];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const double b = C[(4 * k + g) * LD + jc];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = MF::op(-C[(4 * k + g) * LD + 16 * t + lr], b, acc[t]);
   }
-  __syncthreads();
-  // T = R12 R22^{-1} into D, then (R^{-1})12 = -R11^{-1} T
-  lds_gemm<64, false, false>(A, C, [&](int i, int j, double v) { D[i * LD + j] = v; });
-  __syncthreads();
-  double ts = 0.0;                         // this thread's part of |D R^{-1}|_F^2
-  lds_gemm<64, false, false>(B, D, [&](int i, int j, double v) {
-    if (j < w1) {
-      Rinv[(int64_t)(64 + j) * ld + i] = -v;
-      ts = fma(dg0[i] * v, v, ts);
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = 16 * t + MF::row(g, e);
+      D[i * LD + jc] = (i < w1 && jc < w1) ? acc[t][e] : 0.0;
     }
-  });
+  for (int j = wv; j < w1; j += 4) R[(int64_t)(64 + j) * ld + lane] = C[lane * LD + j];
+  __syncthreads();
+  chol_inv<64>(D, A, work, dgs, w1, dm1, first_pass, &dmo1, &nf1, dg1, &nl1);
+  // T = R12 R22^{-1}, then (R^{-1})12 = -R11^{-1} T: T's rows are already where
+  // the right operand wants them (row 4 e + g of a tile, column jc)
+#pragma unroll
+  for (int t = 0; t < 4; ++t) acc[t] = MF::zero();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    if (k < 4 * wv + 4) {
+      const double b = A[(4 * k + g) * LD + jc];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = MF::op(C[(16 * t + lr) * LD + 4 * k + g], b, acc[t]);
+    }
+  }
+  double ts = 0.0;                         // this thread's part of |D R^{-1}|_F^2
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    typename MF::acc_t v = MF::zero();
+#pragma unroll
+    for (int k = 4 * t; k < 16; ++k) v = MF::op(B[(16 * t + lr) * LD + 4 * k + g], acc[k >> 2][k & 3], v);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = 16 * t + MF::row(g, e);
+      if (jc < w1) {
+        Rinv[(int64_t)(64 + jc) * ld + i] = -v[e];
+        ts = fma(dg0[i] * v[e], v[e], ts);
+      }
+    }
+  }
+  for (int j = wv; j < w1; j += 4)
+    if (lane < w1) {
+      R[(int64_t)(64 + j) * ld + 64 + lane] = D[lane * LD + j];
+      Rinv[(int64_t)(64 + j) * ld + 64 + lane] = A[lane * LD + j];
+    }
   if (one_pass) {
-    for (int idx = tid; idx < 64 * 64; idx += 256) {
-      const int i = idx / 64, j = idx % 64;
-      ts = fma(dg0[i] * B[i * LD + j], B[i * LD + j], ts);
-      ts = fma(dg1[i] * C[i * LD + j], C[i * LD + j], ts);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int j = wv + 4 * q;
+      const double x = B[lane * LD + j], y = A[lane * LD + j];
+      ts = fma(dg0[lane] * x, x, ts);
+      if (lane < w1 && j < w1) ts = fma(dg1[lane] * y, y, ts);
     }
     const bool tame = chol_tame_sum(ts, f, work);
     one_pass_out(tame && (nl0 | nl1) == 0ull && (dm0 | dm1) == 0ull, one_pass, R2one, f);
   }
-  for (int c = tid; c < f; c += 256)
-    dead[c] = (int32_t)(c < 64 ? ((dmo0 >> c) & 1ull) : ((dmo1 >> (c - 64)) & 1ull));
+  if (tid < f) dead[tid] = (int32_t)(tid < 64 ? ((dmo0 >> tid) & 1ull) : ((dmo1 >> (tid - 64)) & 1ull));
   if (tid == 0 && count_floors && (nf0 + nf1) && st) atomicAdd(&st->floored, nf0 + nf1);
 }
 
