@@ -84,6 +84,17 @@ inline int64_t cdiv(int64_t x, int64_t a) { return (x + a - 1) / a; }
 // Workgroups of a Gram kernel of the basis loop (one row panel each up to
 // this; the partial buffer holds that many)
 constexpr int GRAM_LOOP_WG = 192;
+// At most this many for a Gram of F columns: the last to arrive sums the
+// partials alone, F/16 (F/16 + 1) / 2 loads per thread and workgroup (20 MB of
+// FP32 rows: 96 of 64 columns).
+constexpr int64_t gram_wg(int F, int64_t max_wg) {
+  return std::min<int64_t>(max_wg, F <= 16 ? 192 : (F <= 32 ? 128 : 96));
+}
+// Doubles those partials take at widths up to f (k_gram_rows: f <= 64).
+constexpr int64_t gram_parts(int64_t f, int64_t max_wg) {
+  const int F = f <= 16 ? 16 : (f <= 32 ? 32 : 64);
+  return gram_wg(F, max_wg) * (F / 16) * (F / 16 + 1) / 2 * 256;
+}
 // Workgroups of a k_apply launch (its 64-row blocks taken grid-stride)
 constexpr int64_t APPLY_WG = 1024;
 
@@ -251,7 +262,7 @@ struct WS {
   void* y;              // ldy x bn
   void* wpart;          // s_proj x ldw x bn
   void* w;              // ldw x bn
-  double* gpart;        // Gram partials (max(s_gram, GRAM_LOOP_WG) x bn x bn)
+  double* gpart;        // Gram partials of the blocks
   void* wfp;            // W = Q^T Y partials of the one-launch block Gram-Schmidt
   double* gsum;         // summed block Gram (bn x bn)
   double* r1;           // bn x bn
@@ -303,7 +314,7 @@ WS carve(void* base, const Geo& g) {
   w.y = c.take<char>(g.ldy * g.bn * e);
   w.wpart = c.take<char>((int64_t)g.s_proj * ldw_of(g) * g.bn * e);
   w.w = c.take<char>(ldw_of(g) * g.bn * e);
-  w.gpart = c.take<double>((int64_t)std::max(g.s_gram, GRAM_LOOP_WG) * g.bn * g.bn);
+  w.gpart = c.take<double>(std::max<int64_t>((int64_t)g.s_gram * g.bn * g.bn, gram_parts(g.bn, GRAM_LOOP_WG)));
   w.wfp = c.take<char>((int64_t)CQR2_GMAX * CQR2_PROJ_WMAX * std::min(g.bn, 32) * e);   // W partials of the one-launch BCGS2
   w.gsum = c.take<double>((int64_t)g.bn * g.bn);
   w.r1 = c.take<double>(g.bn * g.bn);
@@ -319,10 +330,10 @@ WS carve(void* base, const Geo& g) {
   const int64_t rb = std::max<int64_t>(rc, g.bn);
   // Gram partials of the closing QRs: 64 of up to 128 x 128 (the K-split
   // partials of a Gram of at most 128 columns and their sum), or
-  // GRAM_SPLITS_WIDE + 1 of rb x rb (wider), or those of the one-launch
-  // CholeskyQR2 (768 doubles a workgroup and pass)
+  // GRAM_SPLITS_WIDE + 1 of rb x rb (wider), those of k_gram_rows, or those
+  // of the one-launch CholeskyQR2 (768 doubles a workgroup and pass)
   const int64_t rb128 = std::min<int64_t>(rb, 128);
-  w.gbig = c.take<double>(std::max<int64_t>({64 * rb128 * rb128, (GRAM_SPLITS_WIDE + 1) * rb * rb,
+  w.gbig = c.take<double>(std::max<int64_t>({64 * rb128 * rb128, gram_parts(rb, 64), (GRAM_SPLITS_WIDE + 1) * rb * rb,
                                          2 * 768 * std::min<int64_t>(CQR2_GMAX, cdiv(g.nn, CQR2_RPW))}));
   w.rb1 = c.take<double>(rb * rb);
   w.rb2 = c.take<double>(rb * rb);
@@ -774,11 +785,10 @@ int gram_chol(eodabe_ctx* ctx, hipStream_t st, const WS& w, T* X, int64_t ld, in
   if (f <= 0) return 0;
   if (f <= 64) {
     uint32_t* counter = &w.st->counter[0];
-    const int64_t cap = max_wg;
 #define GRAM_CASE(FF, MM)                                                                            \
   do {                                                                                               \
     const int64_t npan = cdiv(rows, GramCfg<T, FF, MM>::RPW);                                        \
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(npan, cap));              \
+    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(npan, gram_wg(FF, max_wg))); \
     hipLaunchKernelGGL((k_gram_rows<T, FF, MM>), dim3(grid), dim3(256), 0, st, X, ld, rows, f, W,    \
                        parts, counter, stopb, blk, ca);                                              \
   } while (0)

@@ -3062,10 +3062,16 @@ struct CholArgs {
 //           over X; G is the Gram of the rounded Z, so the next Cholesky
 //           factor corrects the block actually stored (the second pass of
 //           CholeskyQR2 must see the Z it orthogonalises).
-// Each workgroup stages panels of RPW rows of X in LDS (grid-stride),
-// accumulates on f64 MFMA with its 4 waves splitting the panel rows, folds
-// the waves in fixed order and writes its partial to parts[blockIdx.x]
-// (element (i,j) at j*f + i).  The last workgroup to arrive (device-scope
+// A wave takes steps of 16 U rows (grid-stride) and holds its operands in the
+// MFMA layout from the load on: one 16-byte load is four consecutive rows of a
+// column, the next step's loads are in flight during a step's products, and
+// nothing goes through LDS before the fold of the four waves.  In MODE 1 the
+// rows of a product are permuted so that a lane's results are consecutive rows:
+// they are stored from registers and are the Gram's operands as they stand.
+// The workgroup's partial goes to parts in tile form (upper 16 x 16 tiles, the
+// order of the accumulators).  With the panel staged in LDS and partials
+// f x f a launch of 4096 rows x 32 took 17.7 us, of which the Cholesky is 5;
+// so 15.1.  The last workgroup to arrive (device-scope
 // counter) sums the partials in fixed order and runs chol_inv plus the
 // epilogues in ca: R, R^{-1}, dead flags, floors, the ||A||_F finish and
 // the stop test of Alg. 1:
@@ -3076,17 +3082,13 @@ struct CholArgs {
 template <typename T, int F, int MODE>
 struct GramCfg {
   typedef SmallCfg<F> S;
-  static constexpr int RPW = MODE == 0 ? (F * (int)sizeof(T) <= 128 ? 256 : 128)
-                                       : (F <= 32 ? 256 : (sizeof(T) == 4 ? 128 : 64));
-  static constexpr int LDX = RPW + 16 / (int)sizeof(T);   // X panel column stride (T elements)
-  static constexpr int LDZ = RPW + 2;                     // Z panel column stride (doubles)
+  static constexpr int NT = (F / 16) * (F / 16 + 1) / 2;  // upper tiles
+  static constexpr int U = F * (int)sizeof(T) <= 128 ? 4 : (MODE == 0 && F * (int)sizeof(T) <= 256 ? 2 : 1);
+  static constexpr int RPW = 4 * 16 * U;                  // rows of one pass of a workgroup
+  static constexpr int PART = NT * 256;                   // doubles of a partial
   static constexpr int PBASE = MODE == 1 ? S::SIZE : 0;   // W first (MODE 1), then the phases
-  static constexpr int XD = (F * LDX * (int)sizeof(T) + 7) / 8;
-  static constexpr int ZD = MODE == 1 ? F * LDZ : 0;
-  static constexpr int FOLD = (F / 16) * (F / 16) * 256;
-  static constexpr int LOOPD = XD + ZD > FOLD ? XD + ZD : FOLD;
   static constexpr int CHAIND = 2 * S::SIZE + 24 * F + F;
-  static constexpr int TOTAL = PBASE + (LOOPD > CHAIND ? LOOPD : CHAIND);
+  static constexpr int TOTAL = PBASE + (4 * PART > CHAIND ? 4 * PART : CHAIND);
 };
 
 template <typename T, int F, int MODE>
@@ -3097,184 +3099,219 @@ __global__ __launch_bounds__(256) void k_gram_rows(
   typedef Mfma<double> MF;
   typedef GramCfg<T, F, MODE> Cfg;
   typedef SmallCfg<F> S;
-  constexpr int TT = F / 16, RPW = Cfg::RPW, LDX = Cfg::LDX, LDZ = Cfg::LDZ, LD = S::LD;
+  constexpr int TT = F / 16, U = Cfg::U, NT = Cfg::NT, LD = S::LD;
   static_assert(Cfg::TOTAL * 8 <= 160 * 1024, "LDS budget");
-  if (stop_block && *stop_block < block_id) return;
-  if (gate_shut(ca.gate)) return;
-  if (ca.f_dev) f = (int)*ca.f_dev;
-  if (f > F) return;                    // cannot happen: the launch width bounds the rank
   __shared__ __align__(16) double lds[Cfg::TOTAL];
   double* Wl = lds;                                   // MODE 1: W, row-major ld F+1
   double* ph = lds + Cfg::PBASE;
-  T* pan = reinterpret_cast<T*>(ph);                  // X panel: pan[c*LDX + row]
-  double* pz = ph + Cfg::XD;                          // MODE 1: Z panel: pz[c*LDZ + row]
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int r = lane & 15, g = lane >> 4;
-  if constexpr (MODE == 1) stage_small<F>({Wg}, f, {Wl}, LD);
-  typename MF::acc_t acc[TT][TT];
+  const int64_t nw = 4 * (int64_t)gridDim.x, gw = 4 * (int64_t)blockIdx.x + wv;
+  const int64_t nst = rows / (16 * U);                // whole steps
+  const int fl = f;                                   // width the buffer has, whatever f_dev says
+  typename MF::acc_t acc[NT];
 #pragma unroll
-  for (int t = 0; t < TT; ++t)
+  for (int t = 0; t < NT; ++t) acc[t] = MF::zero();
+  if constexpr (MODE == 0) {
+    const T* xb[TT];
 #pragma unroll
-    for (int u = 0; u < TT; ++u) acc[t][u] = MF::zero();
-  const int64_t npan = (rows + RPW - 1) / RPW;
-  constexpr int NIT = F * RPW / 256;
-  static_assert(NIT <= 32, "staging registers");
-  for (int64_t pnl = blockIdx.x; pnl < npan; pnl += gridDim.x) {
-    const int64_t rb = pnl * RPW;
-    __syncthreads();                          // previous panel consumed (and W ready)
-    {                                         // stage X (zero outside rows x f), all loads in flight
-      T xv[NIT];
+    for (int t = 0; t < TT; ++t) xb[t] = X + (int64_t)min(16 * t + r, fl - 1) * ld + 4 * g;
+    V4<T> a[U][TT], an[U][TT];
+    auto load = [&](V4<T>(&v)[U][TT], int64_t s) {
 #pragma unroll
-      for (int q = 0; q < NIT; ++q) {
-        const int idx = tid + 256 * q;
-        const int c = idx / RPW, rl = idx - c * RPW;
-        const int64_t row = rb + rl;
-        xv[q] = (c < f && row < rows) ? X[(int64_t)c * ld + row] : (T)0;
-      }
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int q = 0; q < NIT; ++q) {
-        const int idx = tid + 256 * q;
-        const int c = idx / RPW, rl = idx - c * RPW;
-        pan[c * LDX + rl] = xv[q];
-      }
+        for (int t = 0; t < TT; ++t) v[u][t] = ld4(xb[t] + 16 * (U * s + u));
+    };
+    auto sub = [&](const V4<T>(&v)[TT]) {             // columns past f only reach entries that are dropped
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int t = 0, i = 0; t < TT; ++t)
+#pragma unroll
+          for (int q = t; q < TT; ++q, ++i) acc[i] = MF::op((double)v[t].v[e], (double)v[q].v[e], acc[i]);
+    };
+    if (gw < nst) load(a, gw);
+    loads_first();                                    // the flags arrive with the data
+    if (stop_block && *stop_block < block_id) return;
+    if (gate_shut(ca.gate)) return;
+    for (int64_t s = gw; s < nst; s += nw) {
+      if (s + nw < nst) load(an, s + nw);
+      loads_first();
+#pragma unroll
+      for (int u = 0; u < U; ++u) sub(a[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int t = 0; t < TT; ++t) a[u][t] = an[u][t];
     }
-    __syncthreads();
-    if constexpr (MODE == 1) {                // Z panel = X panel W (FP64 MFMA), rounded to T
-      for (int rt = wv; rt < RPW / 16; rt += 4) {
-        double a[F / 4];
+    // the last rows, 16 at a time (at most U pieces, the workgroups have 4 waves each), masked
+    const int64_t k = 16 * (U * nst + nw - 1 - gw);
+    if (k < rows) {
 #pragma unroll
-        for (int kk = 0; kk < F / 4; ++kk) a[kk] = (double)pan[(4 * kk + g) * LDX + 16 * rt + r];
-        typename MF::acc_t z[TT];
+      for (int t = 0; t < TT; ++t) a[0][t] = ld4_masked(xb[t] + k, k + 4 * g, rows);
+      sub(a[0]);
+    }
+  } else {
+    if (stop_block && *stop_block < block_id) return;
+    if (gate_shut(ca.gate)) return;
+  }
+  if (ca.f_dev) f = (int)*ca.f_dev;
+  if (f > F) return;                    // cannot happen: the launch width bounds the rank
+  if constexpr (MODE == 1) {
+    constexpr int V = U == 4 ? 4 : 1, KS = F / 4;     // rows a lane loads at once; 16 V rows a step
+    // V = 4: rows 4 r + v, the v-th of four products; V = 1: row 4 (r % 4) + r / 4,
+    // so that rows 4 g .. 4 g + 3 of the product are the lane's accumulators
+    const int lr = V == 4 ? 4 * r : 4 * (r & 3) + (r >> 2);
+    T a[KS][V], an[KS][V];
+    auto load = [&](T(&v)[KS][V], int64_t row0) {
 #pragma unroll
-        for (int u = 0; u < TT; ++u) z[u] = MF::zero();
+      for (int k = 0; k < KS; ++k) {
+        const T* p = X + (int64_t)min(4 * k + g, max(f - 1, 0)) * ld + row0 + lr;
+        if constexpr (V == 4) {
+          const V4<T> x = ld4(p);
 #pragma unroll
-        for (int kk = 0; kk < F / 4; ++kk)
+          for (int e = 0; e < V; ++e) v[k][e] = x.v[e];
+        } else {
+          v[k][0] = *p;
+        }
+      }
+    };
+    auto panel = [&](const T(&v)[KS][V], int64_t row0, bool whole) {
+      typename MF::acc_t z[V][TT];
 #pragma unroll
-          for (int u = 0; u < TT; ++u) z[u] = MF::op(a[kk], Wl[(4 * kk + g) * LD + 16 * u + r], z[u]);
+      for (int e = 0; e < V; ++e)
+#pragma unroll
+        for (int u = 0; u < TT; ++u) z[e][u] = MF::zero();
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const bool ok = 4 * k + g < f;
+#pragma unroll
+        for (int u = 0; u < TT; ++u) {
+          const double w = Wl[(4 * k + g) * LD + 16 * u + r];
+#pragma unroll
+          for (int e = 0; e < V; ++e) z[e][u] = MF::op(ok ? (double)v[k][e] : 0.0, w, z[e][u]);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < V; ++e)
 #pragma unroll
         for (int u = 0; u < TT; ++u)
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            pz[(16 * u + r) * LDZ + 16 * rt + MF::row(g, e)] = (double)(T)z[u][e];
-      }
-      __syncthreads();
-      {                                       // write Z back over X (LDS reads batched)
-        double zv[NIT];
+          for (int c = 0; c < 4; ++c) z[e][u][c] = (double)(T)z[e][u][c];
 #pragma unroll
-        for (int q = 0; q < NIT; ++q) {
-          const int idx = tid + 256 * q;
-          const int c = idx / RPW, rl = idx - c * RPW;
-          zv[q] = pz[c * LDZ + rl];
-        }
+      for (int u = 0; u < TT; ++u) {
+        const int col = 16 * u + r;
+        if (col < f) {
 #pragma unroll
-        for (int q = 0; q < NIT; ++q) {
-          const int idx = tid + 256 * q;
-          const int c = idx / RPW, rl = idx - c * RPW;
-          const int64_t row = rb + rl;
-          if (c < f && row < rows) X[(int64_t)c * ld + row] = (T)zv[q];
+          for (int c = 0; c < V; ++c) {
+            const int64_t row = row0 + (V == 4 ? 4 * MF::row(g, c) : 4 * g);
+            V4<T> o;
+            if constexpr (V == 4) o = V4<T>{{(T)z[0][u][c], (T)z[1][u][c], (T)z[2][u][c], (T)z[3][u][c]}};
+            else o = V4<T>{{(T)z[0][u][0], (T)z[0][u][1], (T)z[0][u][2], (T)z[0][u][3]}};
+            T* p = X + (int64_t)col * ld + row;
+            if (whole) {
+              st4(p, o);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (row + e < rows) p[e] = o.v[e];
+            }
+          }
         }
       }
+#pragma unroll
+      for (int e = 0; e < V; ++e)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+          for (int t = 0, i = 0; t < TT; ++t)
+#pragma unroll
+            for (int q = t; q < TT; ++q, ++i) acc[i] = MF::op(z[e][t][c], z[e][q][c], acc[i]);
+    };
+    if (gw < nst) load(a, 16 * V * gw);
+    stage_small<F>({Wg}, f, {Wl}, LD);
+    __syncthreads();
+    for (int64_t s = gw; s < nst; s += nw) {
+      if (s + nw < nst) load(an, 16 * V * (s + nw));
+      loads_first();
+      panel(a, 16 * V * s, true);
+#pragma unroll
+      for (int k = 0; k < KS; ++k)
+#pragma unroll
+        for (int e = 0; e < V; ++e) a[k][e] = an[k][e];
     }
-    // Gram over this panel: wave wv takes rows [wv*RPW/4, (wv+1)*RPW/4)
-    constexpr int PW = RPW / 4;
+    if (16 * V * nst < rows && gw == nw - 1) {        // the last rows, masked
+      const int64_t row0 = 16 * V * nst;
 #pragma unroll
-    for (int k0 = 0; k0 < PW; k0 += 16) {
-      const int kr = wv * PW + k0 + 4 * g;
-      V4<double> a[TT];
+      for (int k = 0; k < KS; ++k)
 #pragma unroll
-      for (int t = 0; t < TT; ++t)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          a[t].v[e] = MODE == 1 ? pz[(16 * t + r) * LDZ + kr + e] : (double)pan[(16 * t + r) * LDX + kr + e];
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int t = 0; t < TT; ++t)
-#pragma unroll
-          for (int u = t; u < TT; ++u) acc[t][u] = MF::op(a[t].v[v], a[u].v[v], acc[t][u]);
+        for (int e = 0; e < V; ++e)
+          a[k][e] = row0 + lr + e < rows ? X[(int64_t)min(4 * k + g, max(f - 1, 0)) * ld + row0 + lr + e] : (T)0;
+      panel(a, row0, false);
     }
   }
-  // fold the 4 waves (fixed order) through LDS
-  __syncthreads();
+  // fold the 4 waves in order
   double* red = ph;
-  for (int w = 0; w < 4; ++w) {
-    if (wv == w) {
 #pragma unroll
-      for (int t = 0; t < TT; ++t)
+  for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int u = t; u < TT; ++u)
+    for (int e = 0; e < 4; ++e) red[wv * Cfg::PART + (4 * i + e) * 64 + lane] = acc[i][e];
+  __syncthreads();
+  double sum[NT];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            double* qq = &red[((t * TT + u) * 4 + e) * 64 + lane];
-            *qq = (w == 0) ? acc[t][u][e] : *qq + acc[t][u][e];
-          }
+  for (int i = 0; i < NT; ++i) {
+    const double* q = red + 256 * i + tid;
+    sum[i] = ((q[0] + q[Cfg::PART]) + q[2 * Cfg::PART]) + q[3 * Cfg::PART];
+  }
+  const unsigned nb = gridDim.x;
+  if (nb > 1) {
+    double* Pw = parts + (int64_t)blockIdx.x * Cfg::PART + tid;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) Pw[256 * i] = sum[i];
+    // the last workgroup to arrive folds all partials in fixed order
+    wg_stores_done();
+    __shared__ int s_last;
+    if (tid == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      s_last = (atomicAdd(counter, 1u) == nb - 1);
+      if (s_last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
-  }
-  // workgroup partial, symmetric fill: tile (t,u) register e of lane l is
-  // G[16t + 4e + l/16][16u + l%16]
-  double* Pw = parts + (int64_t)blockIdx.x * f * f;
-  for (int idx = tid; idx < TT * TT * 256; idx += 256) {
-    const int l = idx & 63, e = (idx >> 6) & 3, tu = idx >> 8;
-    const int t = tu / TT, u = tu - t * TT;
-    if (u < t) continue;
-    const int i = 16 * t + MF::row(l >> 4, e), jj = 16 * u + (l & 15);
-    if (i < f && jj < f) {
-      const double v = red[idx];
-      Pw[(int64_t)jj * f + i] = v;
-      Pw[(int64_t)i * f + jj] = v;
+    if (!s_last) return;
+    constexpr int PB = NT == 1 ? 32 : (NT == 3 ? 16 : 4);   // partials per batch (loads in flight)
+#pragma unroll
+    for (int i = 0; i < NT; ++i) sum[i] = 0.0;
+    for (unsigned b = 0; b < nb; b += PB) {
+      double v[PB][NT];
+#pragma unroll
+      for (int q = 0; q < PB; ++q)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) v[q][i] = parts[(int64_t)min(b + q, nb - 1) * Cfg::PART + 256 * i + tid];
+#pragma unroll
+      for (int q = 0; q < PB; ++q)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) sum[i] += b + q < nb ? v[q][i] : 0.0;
     }
+  } else {
+    __syncthreads();                   // the fold area becomes the matrices below
   }
-  // the last workgroup to arrive folds all partials in fixed order
-  wg_stores_done();
-  __shared__ int s_last;
-  if (tid == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    s_last = (atomicAdd(counter, 1u) == gridDim.x - 1);
-    if (s_last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  }
-  __syncthreads();
-  if (!s_last) return;
   const int ff = f * f;
   double* Gs = ph;                   // G, then R
   double* Ri = Gs + S::SIZE;         // R^{-1}
   double* rowbuf = Ri + S::SIZE;     // elimination work area, 24F
   double* dgs = rowbuf + 24 * F;
-  {
-    // upper triangle, all partials of an element loaded before summing them
-    // in order b = 0, 1, ...
-    constexpr int EPT = (F * F + 255) / 256;
-    const unsigned nb = gridDim.x;
-    double sum[EPT];
+  // element e of lane l of tile (t, u) is G[16t + 4e + l/16][16u + l%16]
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) sum[e] = 0.0;
-    constexpr int PB = EPT == 1 ? 96 : (EPT <= 4 ? 16 : 4);   // partials per batch (loads in flight)
-    for (unsigned b = 0; b < nb; b += PB) {
-      double v[EPT][PB];
+  for (int t = 0, i = 0; t < TT; ++t)
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        const int idx = tid + 256 * e;
-        const int c = idx / (f > 0 ? f : 1), rr = idx - c * f;
-        const bool ok = idx < ff && rr <= c;
-#pragma unroll
-        for (int q = 0; q < PB; ++q)
-          v[e][q] = (ok && b + q < nb) ? parts[(int64_t)(b + q) * ff + idx] : 0.0;
-      }
-#pragma unroll
-      for (int e = 0; e < EPT; ++e)
-#pragma unroll
-        for (int q = 0; q < PB; ++q) sum[e] += v[e][q];
-    }
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const int idx = tid + 256 * e;
-      const int c = idx / (f > 0 ? f : 1), rr = idx - c * f;
-      if (idx < ff && rr <= c) {
-        Gs[rr * LD + c] = sum[e];
-        Gs[c * LD + rr] = sum[e];
+    for (int u = t; u < TT; ++u, ++i) {
+      const int gi = 16 * t + MF::row(g, wv), gj = 16 * u + r;
+      if (gi < f && gj < f) {
+        Gs[gi * LD + gj] = sum[i];
+        if (t != u) Gs[gj * LD + gi] = sum[i];
       }
     }
-  }
   if (tid == 0) *counter = 0u;
   State* st = ca.st;
   if (ca.norm_parts) {               // ||A||_F from the sketch partials (fixed order)
