@@ -135,6 +135,20 @@ __device__ __forceinline__ void wg_stores_done() {
   __syncthreads();
 }
 
+// The same hand-over without the write-back and the invalidate: the values
+// themselves are stored and loaded as relaxed device-scope atomics, which pass
+// the caches of one XCD by, so once a wave's stores are done (wg_stores_done)
+// an arrival on a device-scope counter may follow.  For what is written and
+// read once, such as partial sums: the caches keep the rest of the working
+// set.  Partial Grams handed over so: 4096 x 4096 at rank 28 141 -> 139 us,
+// 262144 x 200 at rank 15 263 -> 255, three image channels 465 -> 458.
+__device__ __forceinline__ void co_store(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double co_load(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ bool gate_shut(const Gate& g) {
   if (!g.st) return false;
   const int32_t stop = g.st->stop_block, nonfinite = g.st->nonfinite;   // all three in one round trip
@@ -3268,15 +3282,11 @@ __global__ __launch_bounds__(256) void k_gram_rows(
   if (nb > 1) {
     double* Pw = parts + (int64_t)blockIdx.x * Cfg::PART + tid;
 #pragma unroll
-    for (int i = 0; i < NT; ++i) Pw[256 * i] = sum[i];
+    for (int i = 0; i < NT; ++i) co_store(Pw + 256 * i, sum[i]);
     // the last workgroup to arrive folds all partials in fixed order
     wg_stores_done();
     __shared__ int s_last;
-    if (tid == 0) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      s_last = (atomicAdd(counter, 1u) == nb - 1);
-      if (s_last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    }
+    if (tid == 0) s_last = (atomicAdd(counter, 1u) == nb - 1);
     __syncthreads();
     if (!s_last) return;
     constexpr int PB = NT == 1 ? 32 : (NT == 3 ? 16 : 4);   // partials per batch (loads in flight)
@@ -3287,7 +3297,7 @@ __global__ __launch_bounds__(256) void k_gram_rows(
 #pragma unroll
       for (int q = 0; q < PB; ++q)
 #pragma unroll
-        for (int i = 0; i < NT; ++i) v[q][i] = parts[(int64_t)min(b + q, nb - 1) * Cfg::PART + 256 * i + tid];
+        for (int i = 0; i < NT; ++i) v[q][i] = co_load(parts + (int64_t)min(b + q, nb - 1) * Cfg::PART + 256 * i + tid);
 #pragma unroll
       for (int q = 0; q < PB; ++q)
 #pragma unroll
@@ -3406,9 +3416,9 @@ __global__ __launch_bounds__(256) void k_gram_rows(
 // that all their workgroups are resident at once (at most CQR2_GMAX
 // workgroups of 256 threads on a device of 256 CUs).  The workgroup's
 // global stores are handed over as wg_stores_done describes (thread 0 takes
-// the release), thread 0 arrives on the counter, waits for `target`
-// arrivals and takes the acquire before the barrier that lets its waves
-// read what the others wrote.  The wait is bounded by the 100 MHz wall
+// the release; FENCE off: they are co_store's, read by co_load), thread 0
+// arrives on the counter, waits for `target` arrivals and takes the acquire
+// before the barrier that lets its waves read what the others wrote.  The wait is bounded by the 100 MHz wall
 // clock: past CQR2_WAIT_TICKS (about 1.3 s; a resident grid arrives within
 // microseconds) the workgroup sets st->sync_fail and goes on, so every wave
 // still ends; the call then reports EODABE_ESYNC and its outputs are void.
@@ -3424,11 +3434,12 @@ constexpr int CQR2_RPW = 256;
 constexpr int CQR2_PROJ_WMAX = 128;
 constexpr uint64_t CQR2_WAIT_TICKS = 1ull << 27;
 
+template <bool FENCE>
 __device__ __forceinline__ void grid_barrier(uint32_t* ctr, uint32_t target, State* st,
                                              uint64_t wait_ticks = CQR2_WAIT_TICKS) {
   wg_stores_done();
   if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (FENCE) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     atomicAdd(ctr, 1u);
     const uint64_t t0 = wall_clock64();
     while (atomicAdd(ctr, 0u) < target) {        // a read-modify-write: the device-coherent value
@@ -3438,7 +3449,7 @@ __device__ __forceinline__ void grid_barrier(uint32_t* ctr, uint32_t target, Sta
         break;
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (FENCE) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
   __syncthreads();
 }
@@ -3737,7 +3748,7 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
             if (am < wb && cn < f) myWP[am * F + cn] = (T)acc[e];
           }
         }
-        grid_barrier(a.counter, (++bars) * G + a.wait_extra, st, wticks);
+        grid_barrier<true>(a.counter, (++bars) * G + a.wait_extra, st, wticks);
         // (2) W = sum of the G partials in order g = 0, 1, ... (every
         //     workgroup the same), four consecutive columns per load; a
         //     thread takes its groups of four one after another, sixteen
@@ -3844,8 +3855,8 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
     if (!one) {
       double* pp = a.parts + (int64_t)pass * G * (NT * 256);
 #pragma unroll
-      for (int q = 0; q < NT; ++q) pp[((int64_t)blockIdx.x * NT + q) * 256 + tid] = sum[q];
-      grid_barrier(a.counter, (++bars) * G + a.wait_extra, st, wticks);
+      for (int q = 0; q < NT; ++q) co_store(pp + ((int64_t)blockIdx.x * NT + q) * 256 + tid, sum[q]);
+      grid_barrier<false>(a.counter, (++bars) * G + a.wait_extra, st, wticks);
       // all partials, order b = 0, 1, ...
       constexpr int PB = 16;
 #pragma unroll
@@ -3856,7 +3867,7 @@ __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
         for (int q = 0; q < NT; ++q)
 #pragma unroll
           for (int k = 0; k < PB; ++k)           // clamped: the loads stay unconditional
-            v[q][k] = pp[((int64_t)min(b + k, G - 1) * NT + q) * 256 + tid];
+            v[q][k] = co_load(pp + ((int64_t)min(b + k, G - 1) * NT + q) * 256 + tid);
 #pragma unroll
         for (int q = 0; q < NT; ++q)
 #pragma unroll
