@@ -67,6 +67,10 @@ struct eodabe_ctx {
   struct { const void* ws; const void* pool; int ntiles, grid; double tol; uint64_t seed; } tile_key{};
   int tile_b[4] = {0, 0, 0, 0};   // block width per tile-size bucket (0: opts.block)
   int tile_graphs = 1;            // capture the launch in a hipGraph
+  // further channels of an image: contexts like this one on streams of their own
+  eodabe_ctx* chan[IMG_MAX_CH - 1] = {};
+  hipEvent_t chan_ev = nullptr;
+  bool had_image = false;         // set by the first image of several channels
   // learned warm start (eodabe_set_predictor): device parameters of the MLP
   void* scratch = nullptr;        // this device's copy of the static scratch array
   bool cplx_pairs = false;        // set by eodabe_factor_complex around its realified call
@@ -936,10 +940,20 @@ int copy2d(eodabe_ctx* ctx, hipStream_t st, const T* src, int64_t lds, T* dst, i
 // (gated) closing steps, 2 if those steps also write the control block to
 // the context's host copy (no copy needed), 0 if not, < 0 on error.  *spec_ran tells whether
 // such closing steps ran to completion for the chunk that ended the loop.
+// A factorization in two calls with the same arguments: the first returns once
+// the first chunk of blocks (and its speculative closing) is on the stream, the
+// second goes on from there.  Not with the learned warm start.
+struct Split {
+  bool resume = false;     // the second call
+  int64_t j = 0;           // blocks on the stream, after_chunk's answer
+  int spec = 0;
+};
+
 template <typename T, typename Hook>
 int run_basis(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const T* Ae, double tol,
-              int64_t* rank, int* blocks, double* norm_a, Hook&& after_chunk, bool* spec_ran) {
+              int64_t* rank, int* blocks, double* norm_a, Hook&& after_chunk, bool* spec_ran, Split* split) {
   *spec_ran = false;
+  bool resumed = split && split->resume;   // the first chunk is already on the stream
   Ops<T> ops{ctx, st};
   const uint32_t k0 = (uint32_t)(ctx->o.seed & 0xffffffffu), k1 = (uint32_t)(ctx->o.seed >> 32);
   const int nwlog = (int)(g.nblk + 2);
@@ -948,7 +962,7 @@ int run_basis(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const 
   // that is the first launch (ungated), else it is a launch of its own.
   StateInit init{w.st, tol, w.wlog, nwlog, w.dead, (int64_t)(g.nblk + 1) * BN_MAX, w.accv, (int)(g.nblk + 1),
                  g.lp, g.paired ? 1 : 0};
-  if (!(g.sk_rows && !learned && g.nn > 0)) {
+  if (!resumed && !(g.sk_rows && !learned && g.nn > 0)) {
     hipLaunchKernelGGL(k_init_state, dim3(64), dim3(256), 0, st, init.st, init.tol, init.wlog, init.nwlog,
                        init.dead, init.ndead, init.acc, init.nacc, init.lp_mode, init.paired);
     LAUNCHCHK();
@@ -976,7 +990,9 @@ int run_basis(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const 
   int64_t pre_j0 = 0, pre_j1 = 0;       // blocks whose sketch sits in y_w
   while (!finished) {
     int64_t jend = std::min<int64_t>(g.nblk, j + per_sync);
-    if (!probed) {
+    if (resumed) {
+      j = jend = split->j;
+    } else if (!probed) {
       jend = std::min<int64_t>(g.nblk, cdiv(64, g.b));
     } else if (learned && j * g.b < pred_end) {
       // one wide sketch for the next blocks up to the predicted width
@@ -1190,11 +1206,17 @@ int run_basis(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const 
         return EODABE_EINVAL;          // blocks are at most BN_MAX = 128 wide
       }
     }
-    const int spec = after_chunk(j);
+    const int spec = resumed ? split->spec : after_chunk(j);
     if (spec < 0) return spec;
     // host check of the stop flag (one small D2H copy per chunk, unless the
     // closing kernel wrote the control block to host memory itself: spec 2)
-    if (spec != 2) HIPCHK(hipMemcpyAsync(ctx->host_state, w.st, sizeof(State), hipMemcpyDeviceToHost, st));
+    if (spec != 2 && !resumed) HIPCHK(hipMemcpyAsync(ctx->host_state, w.st, sizeof(State), hipMemcpyDeviceToHost, st));
+    if (split && !resumed && !split->resume) {
+      split->j = j;
+      split->spec = spec;
+      return 0;
+    }
+    resumed = false;
     HIPCHK(hipStreamSynchronize(st));
     const State& hs = *ctx->host_state;
     if (hs.sync_fail) return EODABE_ESYNC;
@@ -2032,6 +2054,12 @@ void eodabe_destroy(eodabe_ctx* ctx) {
   if (ctx->tile_ev) (void)hipEventDestroy(ctx->tile_ev);
   if (ctx->tile_stream) (void)hipStreamDestroy(ctx->tile_stream);
   if (ctx->tile_host) (void)hipHostFree(ctx->tile_host);
+  for (eodabe_ctx* c : ctx->chan) {
+    if (!c) continue;
+    if (c->stream) (void)hipStreamDestroy(c->stream);
+    eodabe_destroy(c);
+  }
+  if (ctx->chan_ev) (void)hipEventDestroy(ctx->chan_ev);
   delete ctx;
 }
 
@@ -2066,7 +2094,7 @@ size_t eodabe_workspace_size(const eodabe_ctx* ctx, int64_t m, int64_t n, int64_
 static int factor_impl(eodabe_ctx* ctx, const void* A, int64_t m, int64_t n, int64_t lda, double tol,
                        void* ws, size_t ws_bytes, void* Ut, void* core, void* Vt, int64_t r_cap,
                        eodabe_info* info, void* Qbasis, double* diagT, int64_t diag_cap,
-                       bool basis_only) {
+                       bool basis_only, Split* split = nullptr) {
   TRY(check_ctx(ctx));
   if (!info) return EODABE_EINVAL;
   std::memset(info, 0, sizeof(*info));
@@ -2111,7 +2139,8 @@ static int factor_impl(eodabe_ctx* ctx, const void* A, int64_t m, int64_t n, int
     typedef decltype(tag) T;
     const T* Ae = (const T*)A;
     if (g.packed) {
-      TRY(copy2d<T>(ctx, st, (const T*)A, lda, (T*)w.apack, g.lda_eff, g.mm, g.nn, g.transposed ? 1 : 0));
+      if (!split || !split->resume)
+        TRY(copy2d<T>(ctx, st, (const T*)A, lda, (T*)w.apack, g.lda_eff, g.mm, g.nn, g.transposed ? 1 : 0));
       Ae = (const T*)w.apack;
     }
     // With a small enough basis the closing steps are enqueued right behind
@@ -2129,7 +2158,8 @@ static int factor_impl(eodabe_ctx* ctx, const void* A, int64_t m, int64_t n, int
       return sent ? 2 : 1;
     };
     bool spec_ran = false;
-    TRY(run_basis<T>(ctx, st, g, w, Ae, tol, &rank, &blocks, &norm_a, after_chunk, &spec_ran));
+    TRY(run_basis<T>(ctx, st, g, w, Ae, tol, &rank, &blocks, &norm_a, after_chunk, &spec_ran, split));
+    if (split && !split->resume) return 0;
     info->rank = rank;
     info->blocks = blocks;
     info->norm_a = norm_a;
@@ -2473,9 +2503,16 @@ int eodabe_sketch(eodabe_ctx* ctx, const void* A, int64_t m, int64_t n, int64_t 
 // Applications: colour-image compression and hyperspectral classification.
 // ---------------------------------------------------------------------------
 namespace {
+// Images overlap their channels up to this workspace per channel: below it a
+// channel's chain of small launches leaves most of the GPU idle (1024 x 768:
+// 150 us a channel, 129 MB), above it memory for every channel at once would
+// take what a single large image may need.
+constexpr size_t IMG_OVERLAP_WS = (size_t)512 << 20;
+
 struct ImgPlan {
   int64_t rc, per, nparts;
-  size_t fws, total;
+  size_t fws, total;         // fws: of one channel
+  int slots;                 // channels factored at once
   size_t off_b, off_parts, off_metrics;
 };
 bool img_plan(eodabe_ctx* ctx, int channels, int64_t h, int64_t w, ImgPlan& p) {
@@ -2484,9 +2521,11 @@ bool img_plan(eodabe_ctx* ctx, int channels, int64_t h, int64_t w, ImgPlan& p) {
   p.per = p.rc * (h + p.rc + w);
   p.fws = eodabe_workspace_size(ctx, h, w, p.rc);
   if (p.fws == 0) return false;
+  p.fws = (size_t)rup((int64_t)p.fws, 256);
+  p.slots = p.fws <= IMG_OVERLAP_WS ? channels : 1;
   p.nparts = (int64_t)channels * cdiv(h, 64) * cdiv(w, 64);
   Carver c(nullptr);
-  c.take<char>((int64_t)p.fws);
+  c.take<char>((int64_t)p.fws * p.slots);
   c.take<char>(1);
   p.off_b = (size_t)rup((int64_t)c.off, 256);
   c.take<float>((int64_t)channels * p.rc * w);
@@ -2498,6 +2537,40 @@ bool img_plan(eodabe_ctx* ctx, int channels, int64_t h, int64_t w, ImgPlan& p) {
   return true;
 }
 }  // namespace
+
+// The contexts of an image's channels 1 .. channels-1, kept with ctx: its
+// options (read anew on every call) on a stream of their own.
+static int img_channels(eodabe_ctx* ctx, int channels) {
+  if (!ctx->chan_ev) HIPCHK(hipEventCreateWithFlags(&ctx->chan_ev, hipEventDisableTiming));
+  for (int i = 0; i < channels - 1; ++i) {
+    eodabe_ctx*& c = ctx->chan[i];
+    if (!c) {
+      eodabe_ctx* n = new (std::nothrow) eodabe_ctx();
+      if (!n) return EODABE_EHIP;
+      n->host_only = false;
+      if (hipStreamCreateWithFlags(&n->stream, hipStreamNonBlocking) != hipSuccess) {
+        delete n;
+        return EODABE_EHIP;
+      }
+      if (hipHostMalloc((void**)&n->host_state, sizeof(State), hipHostMallocDefault) != hipSuccess) {
+        (void)hipStreamDestroy(n->stream);
+        delete n;
+        return EODABE_EHIP;
+      }
+      if (hipHostGetDevicePointer((void**)&n->host_state_dev, n->host_state, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        n->host_state_dev = nullptr;
+      }
+      c = n;
+    }
+    c->o = ctx->o;
+    c->device = ctx->device;
+    c->cu_count = ctx->cu_count;
+    c->barrier_fail = ctx->barrier_fail;
+    c->last_hip = 0;
+  }
+  return 0;
+}
 
 size_t eodabe_image_workspace_size(eodabe_ctx* ctx, int channels, int64_t h, int64_t w) {
   if (!ctx) return 0;
@@ -2522,18 +2595,56 @@ int eodabe_compress_image(eodabe_ctx* ctx, const float* img, int channels, int64
   float* Bbuf = (float*)(base + p.off_b);
   ImgSums* parts = (ImgSums*)(base + p.off_parts);
   ImgMetrics* met = (ImgMetrics*)(base + p.off_metrics);
-  // 1. each channel through EOD-ABE, one single-matrix factorization after
-  //    the other (the channels as tiles of one persistent launch occupy only
-  //    as many CUs as there are channels: 1.20 ms for a 1024^2 RGB image
-  //    against about 0.3 ms this way)
+  // 1. each channel through EOD-ABE as a single matrix (the channels as tiles
+  //    of one persistent launch occupy only as many CUs as there are channels:
+  //    1.20 ms for a 1024^2 RGB image).  With a workspace for each, all first
+  //    chunks go out on a stream per channel before the first is waited for:
+  //    most images stop there, and their launches overlap.  Timing and the
+  //    learned warm start read a context's own state, one channel at a time.
   int64_t ranks[IMG_MAX_CH] = {0, 0, 0, 0};
-  for (int c = 0; c < channels; ++c) {
+  //    Setting the streams up costs more than one image gains (0.39 ms; 0.54 ms
+  //    one after the other, 0.46 once warm, 0.31 overlapped, 3 x 1024 x 768), so
+  //    a context does it from its second image on.
+  const bool overlap =
+      p.slots == channels && channels > 1 && ctx->had_image && !ctx->prof_on && !ctx->pred_params;
+  ctx->had_image = ctx->had_image || channels > 1;
+  if (overlap) TRY(img_channels(ctx, channels));
+  eodabe_info fi[IMG_MAX_CH] = {};
+  Split split[IMG_MAX_CH] = {};
+  auto channel = [&](int c, Split* sp) -> int {
     float* Ut = factors + (int64_t)c * p.per;
-    eodabe_info fi{};
-    const int e = eodabe_factor(ctx, img + (int64_t)c * h * w, h, w, w, tol, ws, p.fws, Ut, Ut + p.rc * h,
-                                Ut + p.rc * (h + p.rc), p.rc, &fi);
-    if (e < 0) return e;
-    ranks[c] = fi.rank;
+    eodabe_ctx* cc = overlap && c > 0 ? ctx->chan[c - 1] : ctx;
+    const int e = factor_impl(cc, img + (int64_t)c * h * w, h, w, w, tol, base + (overlap ? c * p.fws : 0), p.fws, Ut,
+                              Ut + p.rc * h, Ut + p.rc * (h + p.rc), p.rc, &fi[c], nullptr, nullptr, 0, false, sp);
+    if (cc != ctx && cc->last_hip) ctx->last_hip = cc->last_hip;
+    return e;
+  };
+  int err = 0;
+  if (overlap) {
+    HIPCHK(hipEventRecord(ctx->chan_ev, ctx->stream));     // the image is ready on the caller's stream
+    for (int c = 0; c < channels && err >= 0; ++c) {
+      if (c > 0) {
+        const hipError_t he = hipStreamWaitEvent(ctx->chan[c - 1]->stream, ctx->chan_ev, 0);
+        if (he != hipSuccess) {
+          ctx->last_hip = (int)he;
+          err = EODABE_EHIP;
+          break;
+        }
+      }
+      err = channel(c, &split[c]);
+      split[c].resume = true;
+    }
+  }
+  for (int c = 0; c < channels && err >= 0; ++c) {
+    err = channel(c, overlap ? &split[c] : nullptr);
+    ranks[c] = fi[c].rank;
+  }
+  if (err < 0) {                       // nothing may still use the caller's buffers
+    if (overlap) {
+      (void)hipStreamSynchronize(ctx->stream);
+      for (int c = 1; c < channels; ++c) (void)hipStreamSynchronize(ctx->chan[c - 1]->stream);
+    }
+    return err;
   }
   // 2. reconstruction U_hat (D_hat V_hat^T) with the criteria fused in
   ImgJob job{};

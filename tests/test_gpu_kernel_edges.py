@@ -110,3 +110,28 @@ def test_tile_widths(b):
         U, D, Vt, rk, _ = bt.result(t)
         assert rk == r, (h, w, r, rk)
         check_factors(tiles[t], U, D, Vt, r, b, 8, 1e-4)
+
+
+@pytest.mark.parametrize("channels,h,w,tol", [(2, 300, 200, 1e-3), (3, 200, 300, 1e-3), (4, 333, 257, 1e-4),
+                                              (3, 90, 400, 1e-4)])
+def test_image_channels_overlap(channels, h, w, tol):
+    # a context's first image goes channel by channel, later ones overlap the
+    # channels: the same factors bit for bit, also where a channel's rank needs
+    # several chunks of blocks, differs between channels or is zero
+    say(f"image {channels}x{h}x{w} tol {tol}")
+    rng = np.random.default_rng(h)
+    img = np.stack([W.lowrank_haar(c, m=h, n=w, r=(70, 5, 33, 1)[c], noise_std=0.0, decades=1.0) * 40 + c
+                    for c in range(channels)]).astype(np.float32)
+    imgs = [img, img + rng.standard_normal(img.shape).astype(np.float32) * 1e-3, np.zeros_like(img)]
+    imgs[1][channels - 1] = 0.0
+    ctx = E.Context(block=16, seed=3)
+    first = E.compress_image(torch.from_numpy(img).cuda(), tol, ctx)
+    for k, x in enumerate(imgs):
+        d = torch.from_numpy(x).cuda()
+        out = E.compress_image(d, tol, ctx)
+        ref = first if k == 0 else E.compress_image(d, tol, E.Context(block=16, seed=3))
+        assert list(out.info.rank[:channels]) == list(ref.info.rank[:channels])
+        for a, b in zip(out.factors, ref.factors):
+            for u, v in zip(a, b):
+                assert torch.equal(u, v)
+        assert torch.equal(out.recon, ref.recon)
