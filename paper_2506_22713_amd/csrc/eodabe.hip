@@ -1161,8 +1161,8 @@ int run_basis(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, const 
         if (j > 0) {
           TRY(ops.template gemm_nt<T>(q, g.ldy, y, g.ldy, wmax, f, g.mm, g.s_proj, (T*)w.wpart, ldw,
                                       ldw * g.bn, nullptr, w.wlog, stopb, blk));
-          hipLaunchKernelGGL((k_reduce_cols<T>), dim3(256), dim3(256), 0, st, (const T*)w.wpart,
-                             eff_splits(g.mm, g.s_proj), ldw * g.bn, wmax, (int64_t)f, ldw, wbuf, w.wlog,
+          hipLaunchKernelGGL((k_reduce_cols<T>), dim3((unsigned)cdiv(std::max<int64_t>(wmax, 1), 256), (unsigned)f), dim3(256),
+                             0, st, (const T*)w.wpart, eff_splits(g.mm, g.s_proj), ldw * g.bn, wmax, ldw, wbuf, w.wlog,
                              stopb, blk);
           LAUNCHCHK();
           TRY(ops.update(y, g.ldy, q, g.ldy, g.mm, wmax, f, wbuf, ldw, 1, w.wlog, stopb, blk));
