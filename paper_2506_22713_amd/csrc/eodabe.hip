@@ -267,6 +267,7 @@ struct WS {
   void* wpart;          // s_proj x ldw x bn
   void* w;              // ldw x bn
   double* gpart;        // Gram partials of the blocks
+  int64_t gpart_n;
   void* wfp;            // W = Q^T Y partials of the one-launch block Gram-Schmidt
   double* gsum;         // summed block Gram (bn x bn)
   double* r1;           // bn x bn
@@ -280,6 +281,8 @@ struct WS {
   void* cpart;          // s_core x r_cap x ldk
   void* ybig;           // ldy x r_cap   (power iteration / U_hat scratch)
   double* gbig;         // Gram partials of the closing QRs
+  double* gclose;       // those of at most 64 columns
+  int64_t gclose_n;
   double* rb1;          // r_cap x r_cap
   double* rb2;
   double* rb3;
@@ -318,7 +321,8 @@ WS carve(void* base, const Geo& g) {
   w.y = c.take<char>(g.ldy * g.bn * e);
   w.wpart = c.take<char>((int64_t)g.s_proj * ldw_of(g) * g.bn * e);
   w.w = c.take<char>(ldw_of(g) * g.bn * e);
-  w.gpart = c.take<double>(std::max<int64_t>((int64_t)g.s_gram * g.bn * g.bn, gram_parts(g.bn, GRAM_LOOP_WG)));
+  w.gpart_n = std::max<int64_t>((int64_t)g.s_gram * g.bn * g.bn, gram_parts(g.bn, GRAM_LOOP_WG));
+  w.gpart = c.take<double>(w.gpart_n);
   w.wfp = c.take<char>((int64_t)CQR2_GMAX * CQR2_PROJ_WMAX * std::min(g.bn, 32) * e);   // W partials of the one-launch BCGS2
   w.gsum = c.take<double>((int64_t)g.bn * g.bn);
   w.r1 = c.take<double>(g.bn * g.bn);
@@ -334,11 +338,15 @@ WS carve(void* base, const Geo& g) {
   const int64_t rb = std::max<int64_t>(rc, g.bn);
   // Gram partials of the closing QRs: 64 of up to 128 x 128 (the K-split
   // partials of a Gram of at most 128 columns and their sum), or
-  // GRAM_SPLITS_WIDE + 1 of rb x rb (wider), those of k_gram_rows, or those
-  // of the one-launch CholeskyQR2 (768 doubles a workgroup and pass)
+  // GRAM_SPLITS_WIDE + 1 of rb x rb (wider).  Up to 64 columns (k_gram_rows,
+  // the one-launch CholeskyQR2 with 768 doubles a workgroup and pass) the
+  // larger of this and the basis loop's buffer, which is free by then.
   const int64_t rb128 = std::min<int64_t>(rb, 128);
-  w.gbig = c.take<double>(std::max<int64_t>({64 * rb128 * rb128, gram_parts(rb, 64), (GRAM_SPLITS_WIDE + 1) * rb * rb,
-                                         2 * 768 * std::min<int64_t>(CQR2_GMAX, cdiv(g.nn, CQR2_RPW))}));
+  const int64_t gbig_n = std::max<int64_t>(64 * rb128 * rb128, (GRAM_SPLITS_WIDE + 1) * rb * rb);
+  w.gbig = c.take<double>(gbig_n);
+  w.gclose = gbig_n >= w.gpart_n ? w.gbig : w.gpart;
+  w.gclose_n = std::max(gbig_n, w.gpart_n);
+  static_assert(gram_parts(16, GRAM_LOOP_WG) >= 2 * 768 * CQR2_GMAX, "room for the one-launch CholeskyQR2");
   w.rb1 = c.take<double>(rb * rb);
   w.rb2 = c.take<double>(rb * rb);
   w.rb3 = c.take<double>(rb * rb);
@@ -789,10 +797,14 @@ int gram_chol(eodabe_ctx* ctx, hipStream_t st, const WS& w, T* X, int64_t ld, in
   if (f <= 0) return 0;
   if (f <= 64) {
     uint32_t* counter = &w.st->counter[0];
+    const bool loop = parts == w.gpart;
+    if (!loop) parts = w.gclose;
+    const int64_t room = loop ? w.gpart_n : w.gclose_n;
 #define GRAM_CASE(FF, MM)                                                                            \
   do {                                                                                               \
     const int64_t npan = cdiv(rows, GramCfg<T, FF, MM>::RPW);                                        \
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(npan, gram_wg(FF, max_wg))); \
+    const int64_t most = std::min<int64_t>(gram_wg(FF, max_wg), room / GramCfg<T, FF, MM>::PART);    \
+    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(npan, most));             \
     hipLaunchKernelGGL((k_gram_rows<T, FF, MM>), dim3(grid), dim3(256), 0, st, X, ld, rows, f, W,    \
                        parts, counter, stopb, blk, ca);                                              \
   } while (0)
@@ -1383,7 +1395,7 @@ int close_small(eodabe_ctx* ctx, hipStream_t st, const Geo& g, const WS& w, cons
     a.rows = g.nn;
     a.f = (int)r;
     a.f_dev = r_dev;
-    a.parts = w.gbig;
+    a.parts = w.gclose;
     a.counter = &w.st->counter[2];
     a.gate = gate;
     a.st = w.st;
