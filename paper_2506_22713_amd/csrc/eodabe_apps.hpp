@@ -154,46 +154,50 @@ __global__ __launch_bounds__(256) void k_img_metrics(const ImgSums* __restrict__
 // Pixel features F = U_hat D_hat (m x r, row-major, ldf): F(i, a) =
 // sum_{b <= a} U(i, b) D(b, a), b ascending, with D upper triangular.  A thread
 // takes one pixel and FEAT_W features at a time (U read once per FEAT_W
-// features; the entries of D are uniform loads), and the results leave through
-// LDS as whole rows.  It is bound by reading U and writing F: 262144 x 15 in
-// 45 us with a thread per feature, which read U r / 2 times and stored single
-// floats a row apart.
+// features, a FEAT_W x FEAT_W tile of D from LDS, requested with U's column
+// chunk), and the results leave through LDS as whole rows.  It is bound by
+// reading U and writing F: 262144 x 15 in 45 us with a thread per feature,
+// which read U r / 2 times and stored single floats a row apart, 22 us with
+// D's entries as uniform loads, 11 us so.
 constexpr int FEAT_W = 16;
 __global__ __launch_bounds__(256) void k_features(const float* __restrict__ Ut, const float* __restrict__ core,
                                                   int64_t m, int r, int64_t rc, float* __restrict__ F,
                                                   int64_t ldf) {
+  static_assert(FEAT_W * FEAT_W == 256, "one entry of D per thread");
   __shared__ float buf[256][FEAT_W + 1];
-  const int64_t i0 = blockIdx.x * (int64_t)256, i = i0 + threadIdx.x < m ? i0 + threadIdx.x : m - 1;
+  __shared__ __align__(16) float ds[FEAT_W * FEAT_W];
+  const int tid = threadIdx.x, dk = tid % FEAT_W, dq = tid / FEAT_W;
+  const int64_t i0 = blockIdx.x * (int64_t)256, i = i0 + tid < m ? i0 + tid : m - 1;
   const int rows = (int)(m - i0 < 256 ? m - i0 : 256);
   for (int a0 = 0; a0 < r; a0 += FEAT_W) {
-    const int w = r - a0 < FEAT_W ? r - a0 : FEAT_W;
     float acc[FEAT_W];
 #pragma unroll
     for (int k = 0; k < FEAT_W; ++k) acc[k] = 0.f;
-    for (int b = 0; b < a0; ++b) {
-      const float u = Ut[(int64_t)b * m + i];
-      const float* d = core + (int64_t)b * rc + a0;
+    for (int b0 = 0; b0 <= a0; b0 += FEAT_W) {       // entries past r are read at r - 1 and not stored
+      float u[FEAT_W];
 #pragma unroll
-      for (int k = 0; k < FEAT_W; ++k) acc[k] = fmaf(u, d[k < w ? k : 0], acc[k]);
+      for (int q = 0; q < FEAT_W; ++q) u[q] = Ut[(int64_t)min(b0 + q, r - 1) * m + i];
+      const float d = core[(int64_t)min(b0 + dq, r - 1) * rc + min(a0 + dk, r - 1)];
+      __syncthreads();
+      ds[tid] = d;
+      __syncthreads();
+      if (b0 < a0) {
+#pragma unroll
+        for (int q = 0; q < FEAT_W; ++q)
+#pragma unroll
+          for (int k = 0; k < FEAT_W; ++k) acc[k] = fmaf(u[q], ds[q * FEAT_W + k], acc[k]);
+      } else {                                       // D is upper triangular
+#pragma unroll
+        for (int q = 0; q < FEAT_W; ++q)
+#pragma unroll
+          for (int k = q; k < FEAT_W; ++k) acc[k] = fmaf(u[q], ds[q * FEAT_W + k], acc[k]);
+      }
     }
-    float u[FEAT_W];
 #pragma unroll
-    for (int q = 0; q < FEAT_W; ++q) u[q] = Ut[(int64_t)(a0 + (q < w ? q : 0)) * m + i];
-#pragma unroll
-    for (int q = 0; q < FEAT_W; ++q) {
-      if (q >= w) break;
-      const float* d = core + (int64_t)(a0 + q) * rc + a0;
-#pragma unroll
-      for (int k = q; k < FEAT_W; ++k) acc[k] = fmaf(u[q], d[k < w ? k : q], acc[k]);
-    }
+    for (int k = 0; k < FEAT_W; ++k) buf[tid][k] = acc[k];
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < FEAT_W; ++k) buf[threadIdx.x][k] = acc[k];
-    __syncthreads();
-    const int k = threadIdx.x % FEAT_W;
-    if (k < w)
-      for (int row = threadIdx.x / FEAT_W; row < rows; row += 256 / FEAT_W)
-        F[(i0 + row) * ldf + a0 + k] = buf[row][k];
+    if (a0 + dk < r)
+      for (int row = dq; row < rows; row += 256 / FEAT_W) F[(i0 + row) * ldf + a0 + dk] = buf[row][dk];
   }
 }
 

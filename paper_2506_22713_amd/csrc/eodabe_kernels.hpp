@@ -3294,7 +3294,7 @@ __global__ __launch_bounds__(256) void k_gram_rows(
     if (tid == 0) s_last = (atomicAdd(counter, 1u) == nb - 1);
     __syncthreads();
     if (!s_last) return;
-    constexpr int PB = NT == 1 ? 32 : (NT == 3 ? 16 : 4);   // partials per batch (loads in flight)
+    constexpr int PB = NT == 1 ? 96 : (NT == 3 ? 32 : 8);   // partials per batch (loads in flight)
 #pragma unroll
     for (int i = 0; i < NT; ++i) sum[i] = 0.0;
     for (unsigned b = 0; b < nb; b += PB) {
@@ -3559,14 +3559,16 @@ struct Cqr2Cfg {
 // before each pass the panel is projected against the basis (block
 // Gram-Schmidt, BCGS2 over the two passes): W = Qb^T Y from per-workgroup
 // partials summed in a fixed order after a barrier, then Y -= Qb W in place.
-// close_qr (the closing of Alg. 2): after pass 1 every workgroup also runs
-// the QR of R^T = (R2 R1)^T on its own LDS (the steps of k_small_qr) and
-// forms its rows of U = Uq Qh.
-// The arithmetic is that of the kernels it replaces (k_gram_rows modes 0
-// and 1, k_apply, k_small_qr; for PROJ the K-split projection and update up
-// to the grouping of the partial sums): the same fold order and MFMA
-// sequences.  Workgroup 0 alone writes R1, R2, their inverses, the dead
-// flags, the floors and the state.
+// close_qr (the closing of Alg. 2): every workgroup then also runs the QR of
+// R^T = (R2 R1)^T on its own LDS (the steps of k_small_qr) and forms its rows
+// of U = Uq Qh; FP32 data takes the second pass of either QR only where
+// chol_tame asks for it.
+// Workgroup 0 alone writes the closing's small outputs, the dead flags, the
+// floors and the state.
+// Bound by latency: the launch with the panel's round trip, a barrier and the
+// fold of the partials per pass, 16 pivots of the Cholesky per 1 us.  At 4096
+// rows x 28 columns 36 us (loop block) and 36 (closing; 54 with four passes of
+// the 8-pivot Cholesky and three copies of it in the code).
 // ---------------------------------------------------------------------------
 template <typename T, int F, bool PROJ>
 __global__ __launch_bounds__(256) void k_cqr2(Cqr2Args a) {
