@@ -70,7 +70,7 @@ struct eodabe_ctx {
   // further channels of an image: contexts like this one on streams of their own
   eodabe_ctx* chan[IMG_MAX_CH - 1] = {};
   hipEvent_t chan_ev = nullptr;
-  bool had_image = false;         // set by the first image of several channels
+  int images = 0;                 // images of several channels so far (counted up to IMG_OVERLAP_AFTER)
   // learned warm start (eodabe_set_predictor): device parameters of the MLP
   void* scratch = nullptr;        // this device's copy of the static scratch array
   bool cplx_pairs = false;        // set by eodabe_factor_complex around its realified call
@@ -2520,6 +2520,11 @@ namespace {
 // 150 us a channel, 129 MB), above it memory for every channel at once would
 // take what a single large image may need.
 constexpr size_t IMG_OVERLAP_WS = (size_t)512 << 20;
+// A context sets the streams up after this many images: a process's first
+// streams beside its own cost 6 ms (the runtime's queues), an overlapped image
+// gains 0.2 ms (3 x 1024 x 1024: 0.48 ms one channel after the other, 0.28),
+// so a context that sees fewer images is better off without.
+constexpr int IMG_OVERLAP_AFTER = 32;
 
 struct ImgPlan {
   int64_t rc, per, nparts;
@@ -2614,12 +2619,9 @@ int eodabe_compress_image(eodabe_ctx* ctx, const float* img, int channels, int64
   //    most images stop there, and their launches overlap.  Timing and the
   //    learned warm start read a context's own state, one channel at a time.
   int64_t ranks[IMG_MAX_CH] = {0, 0, 0, 0};
-  //    Setting the streams up costs more than one image gains (0.39 ms; 0.54 ms
-  //    one after the other, 0.46 once warm, 0.31 overlapped, 3 x 1024 x 768), so
-  //    a context does it from its second image on.
-  const bool overlap =
-      p.slots == channels && channels > 1 && ctx->had_image && !ctx->prof_on && !ctx->pred_params;
-  ctx->had_image = ctx->had_image || channels > 1;
+  const bool overlap = p.slots == channels && channels > 1 && ctx->images >= IMG_OVERLAP_AFTER && !ctx->prof_on &&
+                       !ctx->pred_params;
+  if (channels > 1 && ctx->images < IMG_OVERLAP_AFTER) ++ctx->images;
   if (overlap) TRY(img_channels(ctx, channels));
   eodabe_info fi[IMG_MAX_CH] = {};
   Split split[IMG_MAX_CH] = {};
