@@ -2704,7 +2704,7 @@ __device__ __forceinline__ void blk_rpanel(const double* Ri, double* S, uint64_t
 // panel's blocks and the block to update, one round trip instead of one per
 // product, and each product's operands stay in LDS or registers for the next.
 // A step with 64 x 64 products staged one after another from memory took 43 us
-// (rank 1500), of which the diagonal block's factorization is 10.
+// (rank 1500), of which the diagonal block's factorization is 10; so 20.6.
 __global__ __launch_bounds__(256) void k_cb_look(double* __restrict__ G, int ld, int f, int p,
                                                  double* __restrict__ R, double* __restrict__ Rinv,
                                                  const double* __restrict__ dg, const int32_t* __restrict__ dead,
@@ -2729,9 +2729,7 @@ __global__ __launch_bounds__(256) void k_cb_look(double* __restrict__ G, int ld,
   const int cq = 64 * q, cr = 64 * r, qw = cb_width(f, q), rw = cb_width(f, r);
   const uint64_t nl = nolive[p];
   const int jc = 16 * wv + lr;             // this lane's column of the wave's 16
-  const bool dq = dead[cq + min(jc, qw - 1)] != 0, dr = dead[cr + min(jc, rw - 1)] != 0;
-  uint64_t dm = 0;
-  if (blockIdx.x == 0) dm = __ballot(dead[cq + min(lane, qw - 1)] != 0 && lane < qw);
+  const int32_t dqi = dead[cq + min(jc, qw - 1)], dri = dead[cr + min(jc, rw - 1)], dmi = dead[cq + min(lane, qw - 1)];
   double vl[16], vq[16], vr[16];
   blk_load(vl, Rinv + (int64_t)k0 * ld + k0, ld, pw, pw);
   blk_load(vq, G + (int64_t)cq * ld + k0, ld, pw, qw);
@@ -2742,6 +2740,9 @@ __global__ __launch_bounds__(256) void k_cb_look(double* __restrict__ G, int ld,
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       acc[t][e] = G[(int64_t)(cr + min(jc, rw - 1)) * ld + cq + min(16 * t + MF::row(g, e), qw - 1)];
+  loads_first();
+  const bool dq = dqi != 0, dr = dri != 0;
+  const uint64_t dm = __ballot(dmi != 0 && lane < qw);
   blk_store(vl, Ls, pw, pw);
   blk_store(vq, Sq, pw, qw);
   if (r != q) blk_store(vr, Sr, pw, rw);
@@ -2749,11 +2750,8 @@ __global__ __launch_bounds__(256) void k_cb_look(double* __restrict__ G, int ld,
   blk_rpanel(Ls, Sq, nl, dq);
   if (r != q) blk_rpanel(Ls, Sr, nl, dr);
   __syncthreads();
-  if (q == r)
-    for (int e = tid; e < pw * qw; e += 256) {
-      const int j = e / pw, i = e - j * pw;
-      R[(int64_t)(cq + j) * ld + k0 + i] = Sq[i * BLK_LD + j];
-    }
+  if (q == r && lane < pw)
+    for (int j = wv; j < qw; j += 4) R[(int64_t)(cq + j) * ld + k0 + lane] = Sq[lane * BLK_LD + j];
   const double* Bs = r != q ? Sr : Sq;
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
@@ -2785,11 +2783,11 @@ __global__ __launch_bounds__(256) void k_cb_look(double* __restrict__ G, int ld,
   int nf = 0;
   double* Ri = Sr;                         // not used by a pair (q, q)
   chol_inv<64>(Gs, Ri, work, dgs, qw, dm, first_pass, &dmo, &nf, dg + cq, &nl1);
-  for (int e = tid; e < qw * qw; e += 256) {
-    const int j = e / qw, i = e - j * qw;
-    R[(int64_t)(cq + j) * ld + cq + i] = Gs[i * BLK_LD + j];
-    Rinv[(int64_t)(cq + j) * ld + cq + i] = Ri[i * BLK_LD + j];
-  }
+  if (lane < qw)
+    for (int j = wv; j < qw; j += 4) {
+      R[(int64_t)(cq + j) * ld + cq + lane] = Gs[lane * BLK_LD + j];
+      Rinv[(int64_t)(cq + j) * ld + cq + lane] = Ri[lane * BLK_LD + j];
+    }
   if (tid == 0) {
     nolive[q] = nl1;
     deadmask[q] = dmo;
@@ -3090,7 +3088,7 @@ struct CholArgs {
 // The workgroup's partial goes to parts in tile form (upper 16 x 16 tiles, the
 // order of the accumulators).  With the panel staged in LDS and partials
 // f x f a launch of 4096 rows x 32 took 17.7 us, of which the Cholesky is 5;
-// so 15.1.  The last workgroup to arrive (device-scope
+// so 14.5.  The last workgroup to arrive (device-scope
 // counter) sums the partials in fixed order and runs chol_inv plus the
 // epilogues in ca: R, R^{-1}, dead flags, floors, the ||A||_F finish and
 // the stop test of Alg. 1:
@@ -3294,20 +3292,29 @@ __global__ __launch_bounds__(256) void k_gram_rows(
     if (tid == 0) s_last = (atomicAdd(counter, 1u) == nb - 1);
     __syncthreads();
     if (!s_last) return;
-    constexpr int PB = NT == 1 ? 96 : (NT == 3 ? 32 : 8);   // partials per batch (loads in flight)
+    // in batches of loads in flight: small ones where they cover the launch
+    // (loads past the last partial repeat it: 16 partials of 32 columns in
+    // batches of 32 took 1.7 us more), else up to 96
 #pragma unroll
     for (int i = 0; i < NT; ++i) sum[i] = 0.0;
-    for (unsigned b = 0; b < nb; b += PB) {
-      double v[PB][NT];
+    auto fold = [&](auto pb) {
+      constexpr int PB = decltype(pb)::value;
+      for (unsigned b = 0; b < nb; b += PB) {
+        double v[PB][NT];
 #pragma unroll
-      for (int q = 0; q < PB; ++q)
+        for (int q = 0; q < PB; ++q)
 #pragma unroll
-        for (int i = 0; i < NT; ++i) v[q][i] = co_load(parts + (int64_t)min(b + q, nb - 1) * Cfg::PART + 256 * i + tid);
+          for (int i = 0; i < NT; ++i)
+            v[q][i] = co_load(parts + (int64_t)min(b + q, nb - 1) * Cfg::PART + 256 * i + tid);
 #pragma unroll
-      for (int q = 0; q < PB; ++q)
+        for (int q = 0; q < PB; ++q)
 #pragma unroll
-        for (int i = 0; i < NT; ++i) sum[i] += b + q < nb ? v[q][i] : 0.0;
-    }
+          for (int i = 0; i < NT; ++i) sum[i] += b + q < nb ? v[q][i] : 0.0;
+      }
+    };
+    constexpr int SMALL = NT == 10 ? 4 : 16, LARGE = NT == 1 ? 96 : (NT == 3 ? 32 : 8);
+    if (nb <= 16) fold(std::integral_constant<int, SMALL>{});
+    else fold(std::integral_constant<int, LARGE>{});
   } else {
     __syncthreads();                   // the fold area becomes the matrices below
   }
