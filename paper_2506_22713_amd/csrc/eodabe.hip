@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "../../include/eodabe.h"
+#include "eodabe_sizes.hpp"
 #include "eodabe_kernels.hpp"
 #include "eodabe_tiles.hpp"
 #include "eodabe_mlp.hpp"
@@ -85,20 +86,6 @@ constexpr int BN_MAX = 128;
 
 inline int64_t rup(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 inline int64_t cdiv(int64_t x, int64_t a) { return (x + a - 1) / a; }
-// Workgroups of a Gram kernel of the basis loop (one row panel each up to
-// this; the partial buffer holds that many)
-constexpr int GRAM_LOOP_WG = 192;
-// At most this many for a Gram of F columns: the last to arrive sums the
-// partials alone, F/16 (F/16 + 1) / 2 loads per thread and workgroup (20 MB of
-// FP32 rows: 96 of 64 columns).
-constexpr int64_t gram_wg(int F, int64_t max_wg) {
-  return std::min<int64_t>(max_wg, F <= 16 ? 192 : (F <= 32 ? 128 : 96));
-}
-// Doubles those partials take at widths up to f (k_gram_rows: f <= 64).
-constexpr int64_t gram_parts(int64_t f, int64_t max_wg) {
-  const int F = f <= 16 ? 16 : (f <= 32 ? 32 : 64);
-  return gram_wg(F, max_wg) * (F / 16) * (F / 16 + 1) / 2 * 256;
-}
 // Workgroups of a k_apply launch (its 64-row blocks taken grid-stride)
 constexpr int64_t APPLY_WG = 1024;
 
@@ -235,7 +222,6 @@ struct Geo {
   int64_t r_cap;        // output capacity (rank bound)
   int s_sketch;         // K-splits of the sketch
   int s_proj;           // K-splits of Q^T Y
-  int s_gram;           // K-splits of block Grams
   int s_core;           // K-splits of the r-column products (C = Q^T A etc.)
   size_t elem;
   int lp;               // low-precision sketch: 0 none, 1 FP16, 2 BF16
@@ -247,8 +233,6 @@ struct Geo {
 
 // Widest sketch of the learned warm start in one pass over A (columns).
 constexpr int WIDE_COLS = 128;
-// K-splits of the Gram of blocks wider than 64 columns (partials, then a sum).
-constexpr int GRAM_SPLITS_WIDE = 16;
 // Waves of a k_sketch_rows workgroup (the K parts of one 16-row tile).
 constexpr int SKETCH_ROWS_WAVES = 8;
 
@@ -281,6 +265,7 @@ struct WS {
   void* cpart;          // s_core x r_cap x ldk
   void* ybig;           // ldy x r_cap   (power iteration / U_hat scratch)
   double* gbig;         // Gram partials of the closing QRs
+  int64_t gbig_n;
   double* gclose;       // those of at most 64 columns
   int64_t gclose_n;
   double* rb1;          // r_cap x r_cap
@@ -321,7 +306,7 @@ WS carve(void* base, const Geo& g) {
   w.y = c.take<char>(g.ldy * g.bn * e);
   w.wpart = c.take<char>((int64_t)g.s_proj * ldw_of(g) * g.bn * e);
   w.w = c.take<char>(ldw_of(g) * g.bn * e);
-  w.gpart_n = std::max<int64_t>((int64_t)g.s_gram * g.bn * g.bn, gram_parts(g.bn, GRAM_LOOP_WG));
+  w.gpart_n = gram_loop_room(g.bn, g.mm);
   w.gpart = c.take<double>(w.gpart_n);
   w.wfp = c.take<char>((int64_t)CQR2_GMAX * CQR2_PROJ_WMAX * std::min(g.bn, 32) * e);   // W partials of the one-launch BCGS2
   w.gsum = c.take<double>((int64_t)g.bn * g.bn);
@@ -336,16 +321,13 @@ WS carve(void* base, const Geo& g) {
   w.cpart = c.take<char>((int64_t)g.s_core * rc * g.ldk * e);
   w.ybig = c.take<char>(g.ldy * rc * e);
   const int64_t rb = std::max<int64_t>(rc, g.bn);
-  // Gram partials of the closing QRs: 64 of up to 128 x 128 (the K-split
-  // partials of a Gram of at most 128 columns and their sum), or
-  // GRAM_SPLITS_WIDE + 1 of rb x rb (wider).  Up to 64 columns (k_gram_rows,
-  // the one-launch CholeskyQR2 with 768 doubles a workgroup and pass) the
-  // larger of this and the basis loop's buffer, which is free by then.
-  const int64_t rb128 = std::min<int64_t>(rb, 128);
-  const int64_t gbig_n = std::max<int64_t>(64 * rb128 * rb128, (GRAM_SPLITS_WIDE + 1) * rb * rb);
-  w.gbig = c.take<double>(gbig_n);
-  w.gclose = gbig_n >= w.gpart_n ? w.gbig : w.gpart;
-  w.gclose_n = std::max(gbig_n, w.gpart_n);
+  // Gram partials of the closing QRs.  Up to 64 columns (k_gram_rows, the
+  // one-launch CholeskyQR2 with 768 doubles a workgroup and pass) the larger
+  // of this and the basis loop's buffer, which is free by then.
+  w.gbig_n = gram_close_room(rb);
+  w.gbig = c.take<double>(w.gbig_n);
+  w.gclose = w.gbig_n >= w.gpart_n ? w.gbig : w.gpart;
+  w.gclose_n = std::max(w.gbig_n, w.gpart_n);
   static_assert(gram_parts(16, GRAM_LOOP_WG) >= 2 * 768 * CQR2_GMAX, "room for the one-launch CholeskyQR2");
   w.rb1 = c.take<double>(rb * rb);
   w.rb2 = c.take<double>(rb * rb);
@@ -410,7 +392,6 @@ bool plan(const eodabe_ctx* ctx, int64_t m, int64_t n, int64_t lda, const void* 
   // whose sketch would otherwise be split along K: no partials at all.
   g.sk_rows = use_sketch_rows(g.mm, g.s_sketch, g.bn) && !g.paired;
   g.s_proj = (int)std::max<int64_t>(1, std::min<int64_t>(64, g.mm / 256));
-  g.s_gram = (int)std::max<int64_t>(1, std::min<int64_t>(64, g.mm / 2048));
   // C = Q^T A: output r x nn is small, the reduction over mm is long.
   const int64_t rc1 = std::max<int64_t>(r_cap, 1);
   const int64_t tiles = cdiv(std::max<int64_t>(g.nn, 1), 256) * cdiv(rc1, 64);
@@ -826,17 +807,12 @@ int gram_chol(eodabe_ctx* ctx, hipStream_t st, const WS& w, T* X, int64_t ld, in
   if (ca.norm_parts)
     hipLaunchKernelGGL(k_finish_norm, dim3(1), dim3(256), 0, st, ca.norm_parts, ca.max_parts, ca.n_norm,
                        w.st);
-  // G = X^T X as K-split partials summed in fixed order: up to 63 splits of
-  // at least 64 rows for f <= 128 (the partial buffers hold 64 such
-  // matrices; more splits put more workgroups on the FP64 products),
-  // GRAM_SPLITS_WIDE of at least 512 rows above; one split less where the
-  // partials' stride is rounded up for the fold's vector loads (f odd), so
-  // that they fit the same buffer.  Blocks below the diagonal are not formed:
-  // the Cholesky reads none of them.
-  const int64_t ff = (int64_t)f * f, fs = rup(ff, 4);
-  const int pad = fs != ff ? 1 : 0;
-  const int gs = (int)std::max<int64_t>(
-      1, f <= 128 ? std::min<int64_t>(63 - pad, rows / 64) : std::min<int64_t>(GRAM_SPLITS_WIDE - pad, rows / 512));
+  // G = X^T X as K-split partials summed in fixed order (gram_split).  Blocks
+  // below the diagonal are not formed: the Cholesky reads none of them.
+  const GramSplit sp = gram_split(f, rows);
+  if (sp.need() > (parts == w.gpart ? w.gpart_n : w.gbig_n)) return EODABE_EINVAL;   // the buffers are sized for it
+  const int64_t ff = (int64_t)f * f, fs = sp.stride;
+  const int gs = sp.splits;
   double* gsum = parts + (int64_t)gs * fs;
   TRY(ops.template gemm_nt<double>(X, ld, X, ld, f, f, rows, gs, parts, f, fs, nullptr, nullptr, stopb, blk, 1));
   TRY(ops.reduce_wide(parts, eff_splits(rows, gs), fs, ff, gsum, stopb, blk));
