@@ -2136,6 +2136,12 @@ __device__ __forceinline__ void chol16(double (&D)[16], double (&M)[16], int r, 
 // LDS, take 18400 and 64400.  Rows and columns past f are padded by the
 // identity.  Arguments and rules as chol_inv_general.
 // ---------------------------------------------------------------------------
+// Words of the work area (doubles): the masks of refused pivots, one 32-bit
+// word per block, which every thread reads last, with no barrier behind; the
+// sums of the test that may follow at once (chol_tame_sum: a wave that is
+// ahead writes them while another still reads the masks); and where lanes
+// without a column store.
+constexpr int CHOL_REFUSED = 0, CHOL_RED = 4, CHOL_DUMP = 8;
 template <int F>
 __device__ __forceinline__ void chol_inv_blocked(double* Gs, double* Ri, double* work, double* dgs, int f,
                                                  int first_pass, uint64_t* nolive, const double* dg_in) {
@@ -2145,8 +2151,8 @@ __device__ __forceinline__ void chol_inv_blocked(double* Gs, double* Ri, double*
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nb = (f + 15) / 16;
-  uint32_t* refused = reinterpret_cast<uint32_t*>(work);   // per block
-  double* dump = work + 8;               // where lanes without a column store
+  uint32_t* refused = reinterpret_cast<uint32_t*>(work + CHOL_REFUSED);
+  double* dump = work + CHOL_DUMP;
   if (tid < F) dgs[tid] = tid < f ? (dg_in ? dg_in[tid] : Gs[tid * LD + tid]) : 1.0;
   if (f < 16 * nb)                       // the last block's rows and columns past f
     for (int idx = tid; idx < 16 * nb * 16; idx += 256) {
@@ -2299,7 +2305,8 @@ __device__ __forceinline__ void chol_inv(double* Gs, double* Ri, double* work, d
 // the columns does not change it); the bound 2^-27 is an eighth of an FP32
 // rounding.  FP64 data, whose own rounding that loss exceeds, and basis
 // blocks, whose stop test needs the second factor, take both passes.
-__device__ __forceinline__ bool chol_tame_sum(double s, int f, double* red) {
+__device__ __forceinline__ bool chol_tame_sum(double s, int f, double* work) {
+  double* red = work + CHOL_RED;
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
@@ -2308,9 +2315,10 @@ __device__ __forceinline__ bool chol_tame_sum(double s, int f, double* red) {
   return f * U64 * s <= 0x1p-27;
 }
 // The test for R^{-1} in LDS (row-major, ld F + 1) and the squares dg of D's
-// entries, f <= F (uniform over the 256 threads; red: 4 doubles of LDS).
+// entries, f <= F (uniform over the 256 threads; work: chol_inv's work area, or
+// 8 doubles of LDS that nothing else uses).
 template <int F>
-__device__ __forceinline__ bool chol_tame(const double* Ri, const double* dg, int f, double* red) {
+__device__ __forceinline__ bool chol_tame(const double* Ri, const double* dg, int f, double* work) {
   constexpr int LD = SmallCfg<F>::LD;
   double s = 0.0;
 #pragma unroll
@@ -2318,7 +2326,7 @@ __device__ __forceinline__ bool chol_tame(const double* Ri, const double* dg, in
     const int idx = threadIdx.x + 256 * q, i = idx / F, j = idx % F;
     if (i <= j && j < f) s = fma(dg[i] * Ri[i * LD + j], Ri[i * LD + j], s);
   }
-  return chol_tame_sum(s, f, red);
+  return chol_tame_sum(s, f, work);
 }
 // Its outcome for the launches that follow: the flag, and the identity as the
 // second factor (f x f, element (i,j) at j*f + i) when there will be no other.
@@ -2469,7 +2477,7 @@ __device__ int chol_inv128(const double* G, int ldg, int f, double* R, double* R
 }
 
 // chol_tame after chol_inv128's first pass over G: R^{-1} row-major, ld (lds:
-// 4 doubles).
+// 8 doubles).
 __device__ __forceinline__ bool chol128_tame(const double* G, int ld, const double* Ri, int f, double* lds) {
   double s = 0.0;
   for (int i0 = threadIdx.x >> 6; i0 < f; i0 += 32) {       // 8 rows of this wave's at a time

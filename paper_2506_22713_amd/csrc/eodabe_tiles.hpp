@@ -689,12 +689,12 @@ __device__ void tile_store_small(const double* in, int ld, int f, double* Mg) {
   __syncthreads();
 }
 
-// chol_tame after tile_chol's first pass of f columns (red: 4 doubles of LDS)
-__device__ __noinline__ bool tile_tame(const double* Ri, const double* dgs, int f, double* red) {
+// chol_tame after tile_chol's first pass of f columns
+__device__ __noinline__ bool tile_tame(const double* Ri, const double* dgs, int f, double* work) {
   const int F = chol_width(f);
-  if (F == 16) return chol_tame<16>(Ri, dgs, f, red);
-  if (F == 32) return chol_tame<32>(Ri, dgs, f, red);
-  return chol_tame<64>(Ri, dgs, f, red);
+  if (F == 16) return chol_tame<16>(Ri, dgs, f, work);
+  if (F == 32) return chol_tame<32>(Ri, dgs, f, work);
+  return chol_tame<64>(Ri, dgs, f, work);
 }
 
 // ---------------------------------------------------------------------------
