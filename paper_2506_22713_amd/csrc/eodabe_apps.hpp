@@ -235,8 +235,9 @@ constexpr int KNN_CMAX = 64;
 // a relative 2^-24, and K = 4 S + 4 products accumulated in FP32, the value
 // differs from the FP64 distance by less than 8 (d + 8) 2^-24 (|x'|^2 +
 // |y'|^2) (the pieces add to about half of that), plus 1e-36 for results
-// below the normal range.  Norms past 1e37, where a product may overflow,
-// make the pair pass.
+// below the normal range.  Norms past 1e37, where a product may overflow to
+// either side, make the pair pass: a candidate's becomes -infinity, and a
+// query's bound a NaN, which no comparison drops a pair against.
 constexpr int KNN_WV = 8;       // waves of a workgroup
 constexpr int KNN_QT = 2;       // 16-query tiles of a workgroup
 constexpr int KNN_NQ = 16 * KNN_QT;
@@ -421,7 +422,7 @@ __global__ __launch_bounds__(64 * KNN_WV) void k_knn_cv(const float* __restrict_
 #pragma unroll
     for (int t = 0; t < KNN_QT; ++t) {
       tq[t] = thr[16 * t + li] - nx[t] * (1.f - pad) + 1e-36f;
-      if (!(nx[t] < 1e37f)) tq[t] = INFINITY;
+      if (!(nx[t] < 1e37f)) tq[t] = __builtin_nanf("");
       if (q0 + 16 * t + li >= m) tq[t] = -INFINITY;
     }
     int qn = 0;                                       // queued pairs of this wave
