@@ -354,8 +354,17 @@ int eodabe_last_prediction(const eodabe_ctx* ctx, int64_t* d0, double* log_rank,
  * (rank_bound).  factors: device FP32 pool of channels * r_cap (h + r_cap + w)
  * elements, r_cap = min(h, w); channel c's Ut (r_cap x h), core (r_cap x
  * r_cap) and Vt (r_cap x w) start at c r_cap (h + r_cap + w), laid out as for
- * eodabe_factor.  Requires an F32 context; 1 <= channels <= 4.  Errors:
- * EINVAL, EWORKSPACE, ECAPACITY, ENONFINITE, EHIP.  Returns after the
+ * eodabe_factor.  Requires an F32 context; 1 <= channels <= 4.
+ * Workspace: eodabe_image_workspace_size returns what the context's next call
+ * can use.  That is one channel's factorization, and the channels follow one
+ * another; once the context has compressed 32 images of several channels it
+ * is one per channel, as long as a channel's is at most 512 MB, and such a
+ * call overlaps the channels on streams of its own (made then, with some
+ * pinned host memory, and kept until eodabe_destroy; they wait for the
+ * context's stream and are synchronised before the call returns).  The
+ * smaller size is accepted at any time, with the same results.  Timing
+ * (eodabe_profile) and a predictor keep to one channel at a time.  Errors:
+ * EINVAL, EWORKSPACE, ECAPACITY, ENONFINITE, EHIP, ESYNC.  Returns after the
  * stream has synchronised. */
 #define EODABE_IMAGE_MAX_CHANNELS 4
 typedef struct eodabe_image_info {

@@ -2499,8 +2499,12 @@ constexpr size_t IMG_OVERLAP_WS = (size_t)512 << 20;
 // A context sets the streams up after this many images: a process's first
 // streams beside its own cost 6 ms (the runtime's queues), an overlapped image
 // gains 0.2 ms (3 x 1024 x 1024: 0.48 ms one channel after the other, 0.28),
-// so a context that sees fewer images is better off without.
+// so a context that sees fewer images is better off without.  Timing and the
+// learned warm start read a context's own state, one channel at a time.
 constexpr int IMG_OVERLAP_AFTER = 32;
+bool img_overlaps(const eodabe_ctx* ctx, int channels) {
+  return channels > 1 && ctx->images >= IMG_OVERLAP_AFTER && !ctx->prof_on && !ctx->pred_params;
+}
 
 struct ImgPlan {
   int64_t rc, per, nparts;
@@ -2508,14 +2512,15 @@ struct ImgPlan {
   int slots;                 // channels factored at once
   size_t off_b, off_parts, off_metrics;
 };
-bool img_plan(eodabe_ctx* ctx, int channels, int64_t h, int64_t w, ImgPlan& p) {
+// overlap: with a workspace for each channel, if that stays small enough.
+bool img_plan(eodabe_ctx* ctx, int channels, int64_t h, int64_t w, bool overlap, ImgPlan& p) {
   if (channels < 1 || channels > IMG_MAX_CH || h < 1 || w < 1) return false;
   p.rc = std::min(h, w);
   p.per = p.rc * (h + p.rc + w);
   p.fws = eodabe_workspace_size(ctx, h, w, p.rc);
   if (p.fws == 0) return false;
   p.fws = (size_t)rup((int64_t)p.fws, 256);
-  p.slots = p.fws <= IMG_OVERLAP_WS ? channels : 1;
+  p.slots = overlap && p.fws <= IMG_OVERLAP_WS ? channels : 1;
   p.nparts = (int64_t)channels * cdiv(h, 64) * cdiv(w, 64);
   Carver c(nullptr);
   c.take<char>((int64_t)p.fws * p.slots);
@@ -2568,7 +2573,7 @@ static int img_channels(eodabe_ctx* ctx, int channels) {
 size_t eodabe_image_workspace_size(eodabe_ctx* ctx, int channels, int64_t h, int64_t w) {
   if (!ctx) return 0;
   ImgPlan p;
-  return img_plan(ctx, channels, h, w, p) ? p.total : 0;
+  return img_plan(ctx, channels, h, w, img_overlaps(ctx, channels), p) ? p.total : 0;
 }
 
 int eodabe_compress_image(eodabe_ctx* ctx, const float* img, int channels, int64_t h, int64_t w, double tol,
@@ -2580,10 +2585,15 @@ int eodabe_compress_image(eodabe_ctx* ctx, const float* img, int channels, int64
   if (!img || !factors || !recon || ctx->o.a_dtype != EODABE_F32) return EODABE_EINVAL;
   if (!(tol > 0.0) || !std::isfinite(tol)) return EODABE_EINVAL;
   ImgPlan p;
-  if (!img_plan(ctx, channels, h, w, p)) return EODABE_EINVAL;
+  if (!img_plan(ctx, channels, h, w, img_overlaps(ctx, channels), p)) return EODABE_EINVAL;
   if (factors_len < (int64_t)channels * p.per) return EODABE_EINVAL;
+  // one channel's workspace is enough at any time: then one after the other
+  if (p.slots > 1 && ws_bytes < p.total) img_plan(ctx, channels, h, w, false, p);
   if (!ws || ws_bytes < p.total) return EODABE_EWORKSPACE;
   TRY(check_dev(ctx));
+  if (channels > 1 && ctx->images < IMG_OVERLAP_AFTER) ++ctx->images;
+  const bool overlap = p.slots > 1;
+  if (overlap) TRY(img_channels(ctx, channels));
   char* base = (char*)ws;
   float* Bbuf = (float*)(base + p.off_b);
   ImgSums* parts = (ImgSums*)(base + p.off_parts);
@@ -2592,13 +2602,8 @@ int eodabe_compress_image(eodabe_ctx* ctx, const float* img, int channels, int64
   //    of one persistent launch occupy only as many CUs as there are channels:
   //    1.20 ms for a 1024^2 RGB image).  With a workspace for each, all first
   //    chunks go out on a stream per channel before the first is waited for:
-  //    most images stop there, and their launches overlap.  Timing and the
-  //    learned warm start read a context's own state, one channel at a time.
+  //    most images stop there, and their launches overlap.
   int64_t ranks[IMG_MAX_CH] = {0, 0, 0, 0};
-  const bool overlap = p.slots == channels && channels > 1 && ctx->images >= IMG_OVERLAP_AFTER && !ctx->prof_on &&
-                       !ctx->pred_params;
-  if (channels > 1 && ctx->images < IMG_OVERLAP_AFTER) ++ctx->images;
-  if (overlap) TRY(img_channels(ctx, channels));
   eodabe_info fi[IMG_MAX_CH] = {};
   Split split[IMG_MAX_CH] = {};
   auto channel = [&](int c, Split* sp) -> int {
