@@ -2537,9 +2537,14 @@ bool img_plan(eodabe_ctx* ctx, int channels, int64_t h, int64_t w, bool overlap,
 }  // namespace
 
 // The contexts of an image's channels 1 .. channels-1, kept with ctx: its
-// options (read anew on every call) on a stream of their own.
+// options (read anew on every call) on a stream of their own.  What cannot be
+// had leaves no error behind: the caller goes on without.
 static int img_channels(eodabe_ctx* ctx, int channels) {
-  if (!ctx->chan_ev) HIPCHK(hipEventCreateWithFlags(&ctx->chan_ev, hipEventDisableTiming));
+  if (!ctx->chan_ev && hipEventCreateWithFlags(&ctx->chan_ev, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->chan_ev = nullptr;
+    return EODABE_EHIP;
+  }
   for (int i = 0; i < channels - 1; ++i) {
     eodabe_ctx*& c = ctx->chan[i];
     if (!c) {
@@ -2547,10 +2552,12 @@ static int img_channels(eodabe_ctx* ctx, int channels) {
       if (!n) return EODABE_EHIP;
       n->host_only = false;
       if (hipStreamCreateWithFlags(&n->stream, hipStreamNonBlocking) != hipSuccess) {
+        (void)hipGetLastError();
         delete n;
         return EODABE_EHIP;
       }
       if (hipHostMalloc((void**)&n->host_state, sizeof(State), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
         (void)hipStreamDestroy(n->stream);
         delete n;
         return EODABE_EHIP;
@@ -2592,8 +2599,11 @@ int eodabe_compress_image(eodabe_ctx* ctx, const float* img, int channels, int64
   if (!ws || ws_bytes < p.total) return EODABE_EWORKSPACE;
   TRY(check_dev(ctx));
   if (channels > 1 && ctx->images < IMG_OVERLAP_AFTER) ++ctx->images;
+  if (p.slots > 1 && img_channels(ctx, channels) != 0) {   // no streams to be had: try again after as many images
+    ctx->images = 0;
+    img_plan(ctx, channels, h, w, false, p);
+  }
   const bool overlap = p.slots > 1;
-  if (overlap) TRY(img_channels(ctx, channels));
   char* base = (char*)ws;
   float* Bbuf = (float*)(base + p.off_b);
   ImgSums* parts = (ImgSums*)(base + p.off_parts);
