@@ -2706,8 +2706,12 @@ int eodabe_features(eodabe_ctx* ctx, const float* Ut, const float* core, int64_t
   if (m == 0 || r == 0) return EODABE_OK;
   if (!Ut || !core || !F) return EODABE_EINVAL;
   TRY(check_dev(ctx));
-  hipLaunchKernelGGL(k_features, dim3((unsigned)cdiv(m, 256)), dim3(256), 0, ctx->stream, Ut, core, m,
-                     (int)r, r_cap, F, ldf);
+  const FeatSplit fs = feat_split(m, r);
+  const dim3 grid((unsigned)cdiv(m, fs.px), (unsigned)fs.parts);
+  if (fs.px == 256)
+    hipLaunchKernelGGL((k_features<256, 1>), grid, dim3(256), 0, ctx->stream, Ut, core, m, (int)r, r_cap, F, ldf);
+  else
+    hipLaunchKernelGGL((k_features<64, 2>), grid, dim3(256), 0, ctx->stream, Ut, core, m, (int)r, r_cap, F, ldf);
   LAUNCHCHK();
   return EODABE_OK;
 }

@@ -152,53 +152,97 @@ __global__ __launch_bounds__(256) void k_img_metrics(const ImgSums* __restrict__
 }
 
 // Pixel features F = U_hat D_hat (m x r, row-major, ldf): F(i, a) =
-// sum_{b <= a} U(i, b) D(b, a), b ascending, with D upper triangular.  A thread
-// takes one pixel and FEAT_W features at a time (U read once per FEAT_W
-// features, a FEAT_W x FEAT_W tile of D from LDS, requested with U's column
-// chunk), and the results leave through LDS as whole rows.  It is bound by
-// reading U and writing F: 262144 x 15 in 45 us with a thread per feature,
-// which read U r / 2 times and stored single floats a row apart, 22 us with
-// D's entries as uniform loads, 11 us so.
+// sum_{b <= a} U(i, b) D(b, a), b ascending, with D upper triangular.  A
+// workgroup takes PX pixels and FEAT_W features at a time, a thread one pixel
+// and PX / 16 of them; U's columns come UB chunks of FEAT_W at a time, a step
+// ahead of their products, D's tiles with them through LDS, and the results
+// leave through LDS as whole rows.  With many pixels it is bound by reading U
+// and writing F, with few by the chain of steps of the last features: the rule
+// of the launch (feat_split).  Grid: pixels / PX x features' chunks (blockIdx.y
+// takes every gridDim.y-th, the longest first).
 constexpr int FEAT_W = 16;
+template <int PX, int UB>
 __global__ __launch_bounds__(256) void k_features(const float* __restrict__ Ut, const float* __restrict__ core,
                                                   int64_t m, int r, int64_t rc, float* __restrict__ F,
                                                   int64_t ldf) {
-  static_assert(FEAT_W * FEAT_W == 256, "one entry of D per thread");
-  __shared__ float buf[256][FEAT_W + 1];
-  __shared__ __align__(16) float ds[FEAT_W * FEAT_W];
+  static_assert(FEAT_W * FEAT_W == 256, "one entry of a tile of D per thread");
+  static_assert(PX % 64 == 0 && 256 % PX == 0, "whole waves per group of features");
+  constexpr int G = 256 / PX, FW = FEAT_W / G;      // groups of features, features of a thread
+  __shared__ float buf[PX][FEAT_W + 1];
+  __shared__ __align__(16) float ds[UB][FEAT_W * FEAT_W];
   const int tid = threadIdx.x, dk = tid % FEAT_W, dq = tid / FEAT_W;
-  const int64_t i0 = blockIdx.x * (int64_t)256, i = i0 + tid < m ? i0 + tid : m - 1;
-  const int rows = (int)(m - i0 < 256 ? m - i0 : 256);
-  for (int a0 = 0; a0 < r; a0 += FEAT_W) {
-    float acc[FEAT_W];
+  const int px = tid % PX, k0 = G == 1 ? 0 : tid / PX * FW;
+  const int64_t i0 = blockIdx.x * (int64_t)PX;
+  const int rows = (int)(m - i0 < PX ? m - i0 : PX), pl = min(px, rows - 1);
+  for (int c = (r - 1) / FEAT_W - (int)blockIdx.y; c >= 0; c -= gridDim.y) {
+    const int a0 = FEAT_W * c;
+    float acc[FW], u[UB][FEAT_W], un[UB][FEAT_W], d[UB], dn[UB];
+    auto load = [&](float(&v)[UB][FEAT_W], float(&e)[UB], int b0) {   // entries past r are read at r - 1 and not used
 #pragma unroll
-    for (int k = 0; k < FEAT_W; ++k) acc[k] = 0.f;
-    for (int b0 = 0; b0 <= a0; b0 += FEAT_W) {       // entries past r are read at r - 1 and not stored
-      float u[FEAT_W];
+      for (int s = 0; s < UB; ++s)
+        if (b0 + FEAT_W * s <= a0) {
 #pragma unroll
-      for (int q = 0; q < FEAT_W; ++q) u[q] = Ut[(int64_t)min(b0 + q, r - 1) * m + i];
-      const float d = core[(int64_t)min(b0 + dq, r - 1) * rc + min(a0 + dk, r - 1)];
+          for (int q = 0; q < FEAT_W; ++q) v[s][q] = (Ut + (int64_t)min(b0 + FEAT_W * s + q, r - 1) * m + i0)[pl];
+          e[s] = core[(int64_t)min(b0 + FEAT_W * s + dq, r - 1) * rc + min(a0 + dk, r - 1)];
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < FW; ++k) acc[k] = 0.f;
+    load(u, d, 0);
+    for (int b0 = 0; b0 <= a0; b0 += UB * FEAT_W) {
+      load(un, dn, b0 + UB * FEAT_W);
       __syncthreads();
-      ds[tid] = d;
+#pragma unroll
+      for (int s = 0; s < UB; ++s) ds[s][tid] = d[s];
       __syncthreads();
-      if (b0 < a0) {
 #pragma unroll
-        for (int q = 0; q < FEAT_W; ++q)
+      for (int s = 0; s < UB; ++s) {
+        if (b0 + FEAT_W * s < a0) {
 #pragma unroll
-          for (int k = 0; k < FEAT_W; ++k) acc[k] = fmaf(u[q], ds[q * FEAT_W + k], acc[k]);
-      } else {                                       // D is upper triangular
+          for (int q = 0; q < FEAT_W; ++q)
 #pragma unroll
-        for (int q = 0; q < FEAT_W; ++q)
+            for (int k = 0; k < FW; ++k) acc[k] = fmaf(u[s][q], ds[s][q * FEAT_W + k0 + k], acc[k]);
+        } else if (b0 + FEAT_W * s == a0) {          // D is upper triangular
 #pragma unroll
-          for (int k = q; k < FEAT_W; ++k) acc[k] = fmaf(u[q], ds[q * FEAT_W + k], acc[k]);
+          for (int q = 0; q < FEAT_W; ++q)
+#pragma unroll
+            for (int k = 0; k < FW; ++k) {
+              const float v = fmaf(u[s][q], ds[s][q * FEAT_W + k0 + k], acc[k]);
+              acc[k] = q <= k0 + k ? v : acc[k];
+            }
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < UB; ++s) {
+#pragma unroll
+        for (int q = 0; q < FEAT_W; ++q) u[s][q] = un[s][q];
+        d[s] = dn[s];
       }
     }
 #pragma unroll
-    for (int k = 0; k < FEAT_W; ++k) buf[tid][k] = acc[k];
+    for (int k = 0; k < FW; ++k) buf[px][k0 + k] = acc[k];
     __syncthreads();
     if (a0 + dk < r)
       for (int row = dq; row < rows; row += 256 / FEAT_W) F[(i0 + row) * ldf + a0 + dk] = buf[row][dk];
   }
+}
+// Pixels of a workgroup, and workgroups that share the features of a strip.
+// With fewer than FEAT_WG workgroups of 64 pixels and one chunk of features
+// each, every chunk is a workgroup of 64 pixels; else a workgroup has 256
+// pixels and the chunks are spread only until there are FEAT_WG (beyond,
+// re-reading U from farther away costs more than the shorter chain gains).
+// 4096 x 200: 13.7 us, all chunks of 256 pixels on one workgroup 180, a
+// thread per pixel and feature 31; 1024 x 500: 28, 1028 and 50; 262144 x 15:
+// 9, 9 and 38 (64 pixels 16); 262144 x 100: 133, 149 and 991.
+constexpr int FEAT_WG = 1024;
+struct FeatSplit {
+  int px, parts;
+};
+inline FeatSplit feat_split(int64_t m, int64_t r) {
+  const int64_t chunks = (r + FEAT_W - 1) / FEAT_W;
+  const int px = (m + 63) / 64 * chunks < FEAT_WG ? 64 : 256;
+  const int64_t strips = (m + px - 1) / px, parts = (FEAT_WG + strips - 1) / strips;
+  return FeatSplit{px, (int)(parts < chunks ? parts : chunks)};
 }
 
 constexpr int KNN_KMAX = 16;
