@@ -2738,6 +2738,8 @@ int eodabe_knn_cv(eodabe_ctx* ctx, const float* F, int64_t m, int d, int64_t ldf
   case S:                                                                                                     \
     hipLaunchKernelGGL(k_knn_cv<S>, dim3((unsigned)cdiv(m, KNN_NQ)), dim3(64 * KNN_WV), 0, st, F, m, d, ldf, \
                        labels, fold, k, nclass, pred, conf);                                                  \
+    hipLaunchKernelGGL(k_knn_rest<S>, dim3((unsigned)cdiv(m, KNN_NQ)), dim3(64 * KNN_WV), 0, st, F, m, d, ldf, \
+                       labels, fold, k, nclass, pred, conf);                                                  \
     break
   switch ((d + 3) / 4) {
     KNN_CASE(1);

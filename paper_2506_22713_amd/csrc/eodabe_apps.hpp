@@ -273,7 +273,7 @@ constexpr int KNN_CMAX = 64;
 //     list per query, from which the k smallest pairs are taken.  The lists'
 //     order varies between runs, the selection does not.
 // A query whose list overflows (more than KNN_CAP pairs within the bound:
-// duplicated points) is answered by scanning all pairs in FP64.
+// duplicated or quantised points) is left to k_knn_rest.
 //
 // Rounding bound: with x', y' the features less a common centre, each off by
 // a relative 2^-24, and K = 4 S + 4 products accumulated in FP32, the value
@@ -286,6 +286,7 @@ constexpr int KNN_WV = 8;       // waves of a workgroup
 constexpr int KNN_QT = 2;       // 16-query tiles of a workgroup
 constexpr int KNN_NQ = 16 * KNN_QT;
 constexpr int KNN_CAP = 96;     // pairs kept per query
+constexpr int32_t KNN_REST = -1;   // in pred between the two launches: not answered yet
 
 __device__ __forceinline__ double knn_dist(const float* __restrict__ F, int64_t ldf, int d, int64_t i, int64_t j) {
   const float* x = F + i * ldf;
@@ -299,6 +300,29 @@ __device__ __forceinline__ double knn_dist(const float* __restrict__ F, int64_t 
     }
   }
   return dd;
+}
+
+// Class of query i from its nearest points (0x7fffffff: none), counted.
+__device__ __forceinline__ void knn_vote(const int* sel, int k, const int32_t* __restrict__ label, int nclass, int64_t i,
+                                         int32_t* __restrict__ pred, unsigned long long* __restrict__ conf) {
+  int bl[KNN_KMAX];
+#pragma unroll
+  for (int s = 0; s < KNN_KMAX; ++s) bl[s] = (s < k && sel[s] != 0x7fffffff) ? label[sel[s]] : -1;
+  int best = KNN_CMAX, bestc = -1;
+#pragma unroll
+  for (int s = 0; s < KNN_KMAX; ++s) {
+    if (s >= k || bl[s] < 0) continue;
+    int n = 0;
+#pragma unroll
+    for (int t = 0; t < KNN_KMAX; ++t) n += (t < k && bl[t] == bl[s]) ? 1 : 0;
+    if (n > bestc || (n == bestc && bl[s] < best)) {
+      bestc = n;
+      best = bl[s];
+    }
+  }
+  if (bestc < 0) best = 0;   // no candidate in other folds
+  pred[i] = best;
+  atomicAdd(&conf[(int64_t)best * nclass + label[i]], 1ull);
 }
 
 template <int S>
@@ -321,8 +345,6 @@ __global__ __launch_bounds__(64 * KNN_WV) void k_knn_cv(const float* __restrict_
   __shared__ unsigned char queq[KNN_WV][128];
   __shared__ float thr[KNN_NQ];
   __shared__ int cnt[KNN_NQ], sel[KNN_NQ][KNN_KMAX];
-  __shared__ double wd[KNN_WV];
-  __shared__ int wj[KNN_WV];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, g = lane >> 4;
   const int64_t q0 = blockIdx.x * (int64_t)KNN_NQ;
   const int64_t ntile = (m + 15) / 16;
@@ -518,7 +540,7 @@ __global__ __launch_bounds__(64 * KNN_WV) void k_knn_cv(const float* __restrict_
             if (!__any(h)) continue;
             const int64_t j = tile * 16 + MF::row(g, e);
             h = h && j < m && q0 + 16 * t + li < m;
-            h = h && fold[j] != qf[t];
+            h = h && fold[j] != qf[t] && cnt[16 * t + li] <= KNN_CAP;   // past that, k_knn_rest answers it
             const unsigned long long mk = __ballot(h);
             if (h) {
               const int at = qn + __popcll(mk & ((1ull << lane) - 1));
@@ -576,68 +598,110 @@ __global__ __launch_bounds__(64 * KNN_WV) void k_knn_cv(const float* __restrict_
     }
   }
   __syncthreads();
-  // overflowed lists: the successive minima over all pairs
-  for (int q = 0; q < KNN_NQ; ++q) {
-    if (cnt[q] <= KNN_CAP) continue;
-    const int64_t i = q0 + q;
-    const int fi = fold[i];
-    double ld = -1.0;
-    int lj = -1;
-    for (int s = 0; s < k; ++s) {
-      double bd = INFINITY;
-      int bj = 0x7fffffff;
-      for (int64_t j = tid; j < m; j += 64 * KNN_WV) {
-        if (fold[j] == fi) continue;
-        const double dd = knn_dist(F, ldf, d, i, j);
-        if ((dd > ld || (dd == ld && j > lj)) && dd < bd) {
-          bd = dd;
-          bj = (int)j;
-        }
-      }
-      for (int o = 1; o < 64; o <<= 1) {
-        const double od = __shfl_xor(bd, o);
-        const int oj = __shfl_xor(bj, o);
-        if (od < bd || (od == bd && oj < bj)) {
-          bd = od;
-          bj = oj;
-        }
-      }
-      __syncthreads();
-      if (lane == 0) {
-        wd[wv] = bd;
-        wj[wv] = bj;
-      }
-      __syncthreads();
-      for (int w = 0; w < KNN_WV; ++w)
-        if (wd[w] < bd || (wd[w] == bd && wj[w] < bj)) {
-          bd = wd[w];
-          bj = wj[w];
-        }
-      if (tid == 0) sel[q][s] = bj;
-      ld = bd;
-      lj = bj;
-    }
-  }
-  __syncthreads();
   if (tid >= KNN_NQ || q0 + tid >= m) return;
-  int bl[KNN_KMAX];
+  if (cnt[tid] > KNN_CAP) pred[q0 + tid] = KNN_REST;
+  else knn_vote(sel[tid], k, label, nclass, q0 + tid, pred, conf);
+}
+
+// The queries that k_knn_cv left (pred = KNN_REST), by the definition: the
+// FP64 distances to all points, which go through LDS KNN_RT rows at a time for
+// all queries of the workgroup (the same 32 as there), 16 threads a query, or
+// 64 where at most 8 are left; a thread keeps the k nearest of its points in
+// registers, and the heads of the threads' lists are merged k times.  Bound by
+// the FP64 sums.  21025 x 15 points of which half are the same take 2.6 / 2.7 /
+// 2.9 ms at k = 1 / 5 / 16, all the same 2.7 / 2.8 / 2.9.  One query of the
+// workgroup after the other, all points scanned k times with rows read from
+// memory in lane-strided pieces, took 9.4 / 34 / 99 and 22 / 70 / 192, and one
+// query per thread over all pairs 20.
+constexpr int KNN_RT = 256;
+template <int S>
+__global__ __launch_bounds__(64 * KNN_WV) void k_knn_rest(const float* __restrict__ F, int64_t m, int d, int64_t ldf,
+                                                          const int32_t* __restrict__ label,
+                                                          const int32_t* __restrict__ fold, int k, int nclass,
+                                                          int32_t* __restrict__ pred,
+                                                          unsigned long long* __restrict__ conf) {
+  constexpr int NF = 4 * S, P = NF + 1;               // features of a row in LDS (zeros past d), then its fold
+  __shared__ float row[KNN_RT * P];
+  __shared__ int left[KNN_NQ], sel[KNN_NQ][KNN_KMAX];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int64_t q0 = blockIdx.x * (int64_t)KNN_NQ;
+  const int64_t ql = q0 + (lane & (KNN_NQ - 1));
+  const unsigned mask = (unsigned)__ballot(lane < KNN_NQ && ql < m && pred[ql < m ? ql : m - 1] == KNN_REST);
+  if (mask == 0u) return;                             // the same in every wave
+  if (tid < KNN_NQ && ((mask >> tid) & 1u)) left[__popc(mask & ((1u << tid) - 1u))] = tid;
+  __syncthreads();
+  const int n = __popc(mask), tpq = n <= KNN_WV ? 64 : 16;
+  const int slot = tid / tpq, sub = tid % tpq;
+  const bool mine = slot < n;
+  const int64_t i = q0 + left[mine ? slot : 0];
+  const int fi = fold[i];
+  double x[NF], bd[KNN_KMAX], worst = INFINITY;
+  int bj[KNN_KMAX];
 #pragma unroll
-  for (int s = 0; s < KNN_KMAX; ++s) bl[s] = (s < k && sel[tid][s] != 0x7fffffff) ? label[sel[tid][s]] : -1;
-  int best = KNN_CMAX, bestc = -1;
+  for (int a = 0; a < NF; ++a) x[a] = a < d ? (double)F[i * ldf + (a < d ? a : 0)] : 0.0;
 #pragma unroll
   for (int s = 0; s < KNN_KMAX; ++s) {
-    if (s >= k || bl[s] < 0) continue;
-    int n = 0;
+    bd[s] = INFINITY;
+    bj[s] = 0x7fffffff;
+  }
+  for (int64_t j0 = 0; j0 < m; j0 += KNN_RT) {
+    const int nr = (int)(m - j0 < KNN_RT ? m - j0 : KNN_RT);
+    __syncthreads();
+    for (int e = tid; e < nr * NF; e += 64 * KNN_WV) {
+      const int t = e / NF, a = e % NF;
+      row[t * P + a] = a < d ? F[(j0 + t) * ldf + a] : 0.f;
+    }
+    for (int t = tid; t < nr; t += 64 * KNN_WV) row[t * P + NF] = __int_as_float(fold[j0 + t]);
+    __syncthreads();
+    if (!mine) continue;
+    for (int t = sub; t < nr; t += tpq) {             // ascending: an equal distance later is no nearer
+      const float* y = row + t * P;
+      double dd = 0.0;
+      {
+#pragma clang fp contract(off)
 #pragma unroll
-    for (int t = 0; t < KNN_KMAX; ++t) n += (t < k && bl[t] == bl[s]) ? 1 : 0;
-    if (n > bestc || (n == bestc && bl[s] < best)) {
-      bestc = n;
-      best = bl[s];
+        for (int a = 0; a < NF; ++a) {
+          const double u = (double)y[a] - x[a];
+          dd = dd + u * u;
+        }
+      }
+      if (__float_as_int(y[NF]) == fi || !(dd < worst)) continue;
+      double v = dd;
+      int vj = (int)j0 + t;
+      bool in = false;
+#pragma unroll
+      for (int s = 0; s < KNN_KMAX; ++s) {            // in front of the first that is farther, the others one back
+        in = in || v < bd[s];
+        const double ov = bd[s];
+        const int oj = bj[s];
+        bd[s] = in ? v : ov;
+        bj[s] = in ? vj : oj;
+        v = in ? ov : v;
+        vj = in ? oj : vj;
+        if (s == k - 1) worst = bd[s];
+      }
     }
   }
-  if (bestc < 0) best = 0;   // no candidate in other folds
-  pred[q0 + tid] = best;
-  atomicAdd(&conf[(int64_t)best * nclass + label[q0 + tid]], 1ull);
+  for (int s = 0; s < k; ++s) {
+    double hd = bd[0];
+    int hj = bj[0];
+    for (int o = 1; o < tpq; o <<= 1) {
+      const double od = __shfl_xor(hd, o);
+      const int oj = __shfl_xor(hj, o);
+      if (od < hd || (od == hd && oj < hj)) {
+        hd = od;
+        hj = oj;
+      }
+    }
+    if (mine && sub == 0) sel[slot][s] = hj;
+    const bool take = bj[0] == hj;
+#pragma unroll
+    for (int e = 0; e < KNN_KMAX; ++e) {
+      bd[e] = take ? (e + 1 < KNN_KMAX ? bd[e + 1 < KNN_KMAX ? e + 1 : e] : INFINITY) : bd[e];
+      bj[e] = take ? (e + 1 < KNN_KMAX ? bj[e + 1 < KNN_KMAX ? e + 1 : e] : 0x7fffffff) : bj[e];
+    }
+  }
+  if (mine && sub == 0) knn_vote(sel[slot], k, label, nclass, i, pred, conf);
 }
 
 }  // namespace eodabe
