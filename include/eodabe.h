@@ -135,8 +135,11 @@ size_t eodabe_workspace_size(const eodabe_ctx* ctx, int64_t m, int64_t n, int64_
  *          in its leading r x r block.
  *   Vt     output, r_cap x n row-major: row a holds column a of V_hat.
  *   info   host pointer; rank, blocks, ||A||_F, eps.
- * Rows r..r_cap-1 of the outputs are left unspecified.  For m < n the
- * factorization of A^T is computed and transposed back (the core is
+ * Rows r..r_cap-1 of the outputs are left unspecified.  The QRs of Alg. 2 and
+ * of its power iterations are CholeskyQR in FP64: two passes for F64 data; for
+ * F32 data one where the loss of orthogonality it leaves is estimated well
+ * below an FP32 rounding, else two (the basis blocks of Alg. 1 always two).  For m < n
+ * the factorization of A^T is computed and transposed back (the core is
  * re-triangularised by one more QR).  Errors: EINVAL, EWORKSPACE,
  * ECAPACITY (rank > r_cap; info->rank holds the rank found so far),
  * ENONFINITE, EHIP.  Warning: WTOL_FLOOR. */
