@@ -333,7 +333,6 @@ __global__ __launch_bounds__(64 * KNN_WV) void k_knn_cv(const float* __restrict_
                                                         unsigned long long* __restrict__ conf) {
   typedef Mfma<float> MF;
   constexpr int NB = KNN_WV * 16;                     // candidate classes of pass 1
-  constexpr int64_t ROWS = 16 * KNN_WV;               // candidates per step of the workgroup
   __shared__ union {
     float bmin[NB][KNN_NQ + 1];
     struct {

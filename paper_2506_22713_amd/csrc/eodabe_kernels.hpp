@@ -2418,17 +2418,14 @@ constexpr int CHOL128_LDS = 3 * SmallCfg<64>::SIZE + 24 * 64 + 2 * 64;
 //         elimination);
 //   R22 = chol(G22 - R12^T R12), its floor rule referred to G22's diagonal;
 //   R^{-1} = [R11^{-1}, -R11^{-1} R12 R22^{-1}; 0, R22^{-1}].
-// G (read only, symmetric), R, Rinv: global FP64, leading dimension ldg;
-// R and Rinv row-major (element (i,j) at i*ldg + j), or column-major (at
-// j*ldg + i) with CM.  lds: CHOL128_LDS doubles.  dm_in / dm_out: dead
-// masks of columns 0-63 and 64-127.  Returns the number of floored pivots
-// (uniform).
+// G (read only, symmetric), R, Rinv: global FP64, row-major (element (i,j) at
+// i*ldg + j).  lds: CHOL128_LDS doubles.  dm_in / dm_out: dead masks of columns
+// 0-63 and 64-127.  Returns the number of floored pivots (uniform).
 // ---------------------------------------------------------------------------
-template <bool CM = false>
 __device__ int chol_inv128(const double* G, int ldg, int f, double* R, double* Rinv, double* lds,
                            uint64_t dm_in0, uint64_t dm_in1, int first_pass, uint64_t* dm_out0,
                            uint64_t* dm_out1) {
-  auto at = [&](int i, int j) -> int64_t { return CM ? (int64_t)j * ldg + i : (int64_t)i * ldg + j; };
+  auto at = [&](int i, int j) -> int64_t { return (int64_t)i * ldg + j; };
   typedef SmallCfg<64> S;
   constexpr int LD = S::LD;
   double* Gs = lds;                        // block being factored -> its R
@@ -2481,7 +2478,7 @@ __device__ int chol_inv128(const double* G, int ldg, int f, double* R, double* R
   }
   __syncthreads();
   // R^{-1}_12 = -(R11^{-1} R12) R22^{-1}
-  gmm64<CM, false>(Rinv, ldg, T, LD, 64, n2, 64, [&](int i, int j, double v) { Gs[i * LD + j] = v; });
+  gmm64<false, false>(Rinv, ldg, T, LD, 64, n2, 64, [&](int i, int j, double v) { Gs[i * LD + j] = v; });
   __syncthreads();
   gmm64<false, false>(Gs, LD, Ri, LD, 64, n2, n2, [&](int i, int j, double v) { Rinv[at(i, 64 + j)] = -v; });
   __syncthreads();
@@ -2519,12 +2516,12 @@ __device__ __forceinline__ bool chol128_tame(const double* G, int ld, const doub
 // G = M M^T = Rh1^T Rh1, Z1 = M^T Rh1^{-1}, Z1^T Z1 = Rh2^T Rh2, Qh =
 // Z1 Rh2^{-1}, Rh = Rh2 Rh1 (first Cholesky floored, the second kills what
 // stays non-positive; the second pass only where chol_tame asks for it, the
-// data being FP32).  R1, R2: element (i,j) at j*ldi + i (CMI) or i*ldi + j.
+// data being FP32).  R1, R2: element (i,j) at i*ldi + j.
 // Qh and Rh go out through put_q(i, j, v) and put_r(i, j, v).
 // scr: 7 buffers of 128 x 128 doubles.  lds: CHOL128_LDS doubles.  Returns
 // the number of floored pivots.
 // ---------------------------------------------------------------------------
-template <bool CMI, typename PutQ, typename PutR>
+template <typename PutQ, typename PutR>
 __device__ int small_qr_mid(double* lds, const double* R1g, const double* R2g, int f, int ldi, double* scr,
                             PutQ put_q, PutR put_r) {
   constexpr int LB = 128;
@@ -2537,11 +2534,11 @@ __device__ int small_qr_mid(double* lds, const double* R1g, const double* R2g, i
   double* H2 = scr + 5 * B2;
   double* H2i = scr + 6 * B2;
   if (R1g) {
-    gmm64<CMI, CMI>(R2g, ldi, R1g, ldi, f, f, f, [&](int i, int j, double v) { M[i * LB + j] = v; });
+    gmm64<false, false>(R2g, ldi, R1g, ldi, f, f, f, [&](int i, int j, double v) { M[i * LB + j] = v; });
   } else {
     for (int idx = threadIdx.x; idx < f * f; idx += 256) {
       const int i = idx / f, j = idx - i * f;
-      M[i * LB + j] = CMI ? R2g[(int64_t)j * ldi + i] : R2g[(int64_t)i * ldi + j];
+      M[i * LB + j] = R2g[(int64_t)i * ldi + j];
     }
   }
   __syncthreads();

@@ -811,7 +811,7 @@ __device__ __attribute__((noinline)) int tile_chol128(const double* G, int f, do
 __device__ __attribute__((noinline)) void tile_small_qr_big(double* lds, const double* R1g, const double* R2g,
                                                             int f, double* Qh, double* Rh, double* scr) {
   constexpr int LB = TileSlot::LB;
-  small_qr_mid<false>(lds, R1g, R2g, f, LB, scr, [&](int i, int j, double v) { Qh[i * LB + j] = v; },
+  small_qr_mid(lds, R1g, R2g, f, LB, scr, [&](int i, int j, double v) { Qh[i * LB + j] = v; },
                       [&](int i, int j, double v) { Rh[i * LB + j] = v; });
 }
 
