@@ -74,7 +74,8 @@ def measured_traffic(workload: str, kernel: str):
     if not os.path.exists(path):
         return None
     h = hashlib.sha256()
-    for f in ("paper_2506_22713_amd/csrc/eodabe_kernels.hpp", "paper_2506_22713_amd/csrc/eodabe_tiles.hpp",
+    for f in ("paper_2506_22713_amd/csrc/eodabe_sizes.hpp",
+              "paper_2506_22713_amd/csrc/eodabe_kernels.hpp", "paper_2506_22713_amd/csrc/eodabe_tiles.hpp",
               "paper_2506_22713_amd/csrc/eodabe_mlp.hpp", "paper_2506_22713_amd/csrc/eodabe_apps.hpp",
               "paper_2506_22713_amd/csrc/eodabe.hip"):
         with open(os.path.join(ROOT, f), "rb") as fh:
